@@ -12,9 +12,10 @@ BUILD = os.path.join(HERE, "_build")
 LIB = os.path.join(HERE, "libtumordb.so")
 
 SOURCES = ["api.cpp", "pack.hip", "scan.hip", "select.hip", "batch.hip", "nn.hip", "embed.hip",
-           "resample.hip", "sparse.hip", "hash.hip", "vae.hip", "noalloc.hip", "knn.hip"]
+           "resample.hip", "sparse.hip", "hash.hip", "vae.hip", "noalloc.hip", "knn.hip",
+           "train.hip"]
 # Sources with floating-point arithmetic that may be contracted into FMAs.
-CONTRACT_OK = {"nn.hip"}
+CONTRACT_OK = {"nn.hip", "train.hip"}
 
 HIPCC = os.environ.get("HIPCC", "hipcc")
 COMMON = ["--offload-arch=gfx950", "-O3", "-fPIC", "-std=c++17", "-Wall",

@@ -196,6 +196,13 @@ hipError_t launch_rerank_rank(const db_t *db, int nq, const uint32_t *acnt, int 
                               int32_t *idx, double *score, db_counts_t *counts, const void *ws,
                               hipStream_t s);
 
+// Training kernels (train.hip), float activations.
+// Weight gradient dW [Co][Ci][27] and, unless NULL, dbias [Co], through ws (float [chunks of
+// 4,096 positions][Co][Ci][28]); sizes for which conv_wgrad_ok holds.
+bool conv_wgrad_ok(int Ci, int Co, int D, int H, int W);
+hipError_t launch_conv_wgrad(int B, int Ci, int Co, int D, int H, int W, const float *X,
+                             const float *dY, float *dW, float *dbias, float *ws, hipStream_t s);
+
 // Row boxes, moments, box-restricted scan, centre-of-mass distances (sparse.hip).
 // Per entry of recs: box (rows with a set bit), tbox (rows with a T1Gd bit), mom, and the
 // per z-slice y-ranges of its FLAIR and T1Gd rows zrange [nz][2] (y0 | y1 << 16; 0: none).

@@ -2467,7 +2467,10 @@ int nn_conv3d_s2_bwd_weight(int dtype, int B, int Ci, int Co, int D, int H, int 
     const dim3 g1(chunks, Ci, Co);
     const dim3 g1f(chunks, Ci, (Co + kWgCB - 1) / kWgCB);
     const unsigned g2 = (unsigned)((Co * Ci * 28 + 255) / 256);
-    if (dtype == NN_F32) {
+    if (dtype == NN_F32 && conv_wgrad_ok(Ci, Co, D, H, W)) {
+        (void)launch_conv_wgrad(B, Ci, Co, D, H, W, (const float *)X, (const float *)dY,
+                                (float *)dWt, (float *)dbias, (float *)ws, s);
+    } else if (dtype == NN_F32) {   // samples of 2 GiB and more
         hipLaunchKernelGGL((conv_bwd_weight_partial<float, kWgCB>), g1f, dim3(256), 0, s, B, Ci, Co,
                            D, H, W, (const float *)X, (const float *)dY, (float *)ws);
         hipLaunchKernelGGL(conv_bwd_weight_final<float>, dim3(g2), dim3(256), 0, s, chunks, Ci, Co,
