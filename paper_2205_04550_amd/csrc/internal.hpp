@@ -202,6 +202,11 @@ hipError_t launch_rerank_rank(const db_t *db, int nq, const uint32_t *acnt, int 
 bool conv_wgrad_ok(int Ci, int Co, int D, int H, int W);
 hipError_t launch_conv_wgrad(int B, int Ci, int Co, int D, int H, int W, const float *X,
                              const float *dY, float *dW, float *dbias, float *ws, hipStream_t s);
+// Adjoint map dX = conv^T(dY) + bias, sizes for which conv_adjoint_ok holds.
+bool conv_adjoint_ok(int B, int Ci, int Co, int D, int H, int W);
+hipError_t launch_conv_adjoint(bool bf16w, int B, int Ci, int Co, int D, int H, int W,
+                               const float *dY, const void *Wt, const float *bias, int relu,
+                               float *dX, hipStream_t s);
 
 // Row boxes, moments, box-restricted scan, centre-of-mass distances (sparse.hip).
 // Per entry of recs: box (rows with a set bit), tbox (rows with a T1Gd bit), mom, and the

@@ -2425,6 +2425,11 @@ int nn_conv3d_s2_bwd_data(int dtype, int B, int Ci, int Co, int D, int H, int W,
     if (pair < 0 || !conv_dims_ok(B, Ci, Co, D, H, W) || !dY || !Wt || !dX)
         return tdb_set_error(DB_EINVAL, "nn_conv3d_s2_bwd_data: bad arguments");
     const hipStream_t s = static_cast<hipStream_t>(stream);
+    if (pair <= 1 && conv_adjoint_ok(B, Ci, Co, D, H, W)) {
+        (void)launch_conv_adjoint(pair == 0, B, Ci, Co, D, H, W, (const float *)dY, Wt,
+                                  (const float *)bias, relu, (float *)dX, s);
+        return launched("nn_conv3d_s2_bwd_data");
+    }
     const int64_t isp = (int64_t)D * H * W;
     const dim3 grid((unsigned)((B * isp + 255) / 256), (Ci + kCB - 1) / kCB);
     if (pair == 0)

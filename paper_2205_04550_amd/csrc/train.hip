@@ -43,6 +43,19 @@ __device__ __forceinline__ float2 buf_f32x2(rsrc_t r, uint32_t off, uint32_t sof
     return make_float2(__uint_as_float(u.x), __uint_as_float(u.y));
 }
 
+// Weight i of a buffer, or 0 unless ok (a plain conditional load would become a branch that waits
+// for the load before the next one is issued).
+__device__ __forceinline__ uint16_t buf_w(rsrc_t r, bool ok, uint32_t i, uint16_t)
+{
+    return (uint16_t)__builtin_amdgcn_raw_buffer_load_b16(r, ok ? 2 * i : kOut, 0, 0);
+}
+__device__ __forceinline__ float buf_w(rsrc_t r, bool ok, uint32_t i, float)
+{
+    return buf_f32(r, ok ? 4 * i : kOut);
+}
+
+typedef float f32x2_u __attribute__((ext_vector_type(2), aligned(4)));   // 4-byte aligned pair
+
 // ---- wave sums of many values ------------------------------------------------------------------
 //
 // The sum over the 64 lanes of each of N values, as the butterfly (lane ^ 32, ^ 16, ... ^ 1)
@@ -93,6 +106,26 @@ __device__ __forceinline__ void wave_sums(float (&v)[N], int lane)
 #undef TDB_HALVE
 }
 
+// A number of coarse voxels in mixed radix, to advance a position without divisions.
+struct Step {
+    int b, z, y, x;
+};
+Step step_of(int n, int OD, int OH, int OW)
+{
+    return {n / OW / OH / OD, n / OW / OH % OD, n / OW % OH, n % OW};
+}
+__device__ __forceinline__ void advance(int &b, int &z, int &y, int &x, const Step &st, int OD,
+                                        int OH, int OW)
+{
+    x += st.x;
+    y += st.y;
+    z += st.z;
+    b += st.b;
+    if (x >= OW) { x -= OW; ++y; }
+    if (y >= OH) { y -= OH; ++z; }
+    if (z >= OD) { z -= OD; ++b; }
+}
+
 // ---- weight gradient ------------------------------------------------------------------------
 //
 // dW[co][ci][tap] = sum over (sample, coarse voxel o) of dY[co][o] X[ci][2 o + tap - 1]. Grid
@@ -112,13 +145,11 @@ __device__ __forceinline__ void wave_sums(float (&v)[N], int lane)
 constexpr int kWgChunkF = 4096;
 constexpr int kWgCBF = 4;
 
-struct WgStep {   // 256 positions as (samples, z, y, x)
-    int b, z, y, x;
-};
+
 
 template <bool SHIFT>
 __global__ void __launch_bounds__(256, 3) conv_wgrad_kernel(int B, int Ci, int Co, int D, int H,
-                                                            int W, WgStep st,
+                                                            int W, Step st,
                                                             const float *__restrict__ X,
                                                             const float *__restrict__ dY,
                                                             float *__restrict__ partial)
@@ -180,13 +211,7 @@ __global__ void __launch_bounds__(256, 3) conv_wgrad_kernel(int B, int Ci, int C
             for (int r = 0; r < 27; ++r) acc[c * 28 + r] = __builtin_fmaf(g[c], v[r / 3][r % 3], acc[c * 28 + r]);
             acc[c * 28 + 27] += g[c];
         }
-        x += st.x;
-        y += st.y;
-        z += st.z;
-        b += st.b;
-        if (x >= OW) { x -= OW; ++y; }
-        if (y >= OH) { y -= OH; ++z; }
-        if (z >= OD) { z -= OD; ++b; }
+        advance(b, z, y, x, st, OD, OH, OW);
     }
     wave_sums(acc, lane);
     const int at = (int)(__brev((unsigned)lane) >> 26);
@@ -247,7 +272,7 @@ hipError_t launch_conv_wgrad(int B, int Ci, int Co, int D, int H, int W, const f
     const int OD = D / 2, OH = H / 2, OW = W / 2;
     const int64_t P = (int64_t)B * OD * OH * OW;
     const int chunks = (int)((P + kWgChunkF - 1) / kWgChunkF);
-    const WgStep st = {256 / (OW * OH * OD), 256 / (OW * OH) % OD, 256 / OW % OH, 256 % OW};
+    const Step st = step_of(256, OD, OH, OW);
     const dim3 grid((unsigned)chunks, (unsigned)Ci, (unsigned)((Co + kWgCBF - 1) / kWgCBF));
     if (64 % OW == 0)
         hipLaunchKernelGGL((conv_wgrad_kernel<true>), grid, dim3(256), 0, s, B, Ci, Co, D, H, W, st,
@@ -259,6 +284,274 @@ hipError_t launch_conv_wgrad(int B, int Ci, int Co, int D, int H, int W, const f
     hipLaunchKernelGGL(conv_wgrad_final_kernel, dim3((unsigned)((N + 31) / 32)), dim3(512), 0, s,
                        chunks, Ci, N, (const float *)ws, dW, dbias);
     return hipGetLastError();
+}
+
+namespace {
+
+// ---- adjoint (input gradient; transposed-convolution forward) ----------------------------------
+//
+// dX[ci][i] = bias[ci] + sum over co and the taps with i + 1 - tap even of W[co][ci][tap]
+// dY[co][(i + 1 - tap) / 2], in the order co, kd, kh, kw. Along an axis the even fine voxel 2 j
+// has tap 1 on coarse voxel j, the odd one 2 j + 1 has tap 0 on j + 1, then tap 2 on j. So for 16
+// coarse voxels (the N of a product) the eight parities of the fine voxels are rows of M, k runs
+// over co and the neighbours j + 1, j of each odd axis, and a row whose parity lacks a neighbour
+// has weight zero there: the sum's terms keep their order.
+//   few fine channels (Ci <= 2): the 16 rows are (pz, py, ci, px), one tile, 8 Co terms;
+//   otherwise a tile is (pz, py) and eight fine channels, rows (ci, px), and k has only the
+//   neighbours its z and y parities use: 2, 4, 4 or 8 terms per co.
+// A wave keeps a tile's weights in registers (through LDS, which the four waves of a block
+// fill once) and walks its share of the voxels; lane l needs dY at voxel l % 16 and neighbour
+// l / 16, one buffer load per product straight from the caches, with no vector instruction
+// in between: the lane's offset is fixed per voxel (out of range where the neighbour is) and
+// the channel is the load's scalar offset. Zero weights times an infinity would leave a NaN
+// that the direct loop does not have: a wave that finds a NaN in its results redoes them as
+// that loop. Loads run three batches of eight products ahead (one batch: the 32 -> 64 layer took
+// 32 us, the latency of each batch being longer than its products). Batch 32, transposes of
+// the layers 2 -> 8 (64^3), 8 -> 16, 16 -> 32, 32 -> 64: 40 / 28 / 18 / 15 us, where a thread
+// per fine voxel with its weights broadcast from LDS (conv_bwd_data_kernel, kept for the sizes
+// launch_conv_adjoint does not take and for double) took 262 / 73 / 55 / 79 us. The first is
+// bound by its writes (67 MB), the others by the matrix products and the first loads' latency.
+__device__ __forceinline__ float wt_f32(uint16_t w) { return __uint_as_float((uint32_t)w << 16); }
+__device__ __forceinline__ float wt_f32(float w) { return w; }
+
+struct AdjArgs {
+    int B, Ci, Co, D, H, W, relu, groups, gpw;   // groups of 16 coarse voxels; groups per wave
+    Step st;                                     // kAdjNG groups
+    const float *dY, *bias;
+    float *dX;
+};
+constexpr int kAdjNG = 2;                        // groups that go together (shared weights)
+
+// One output by the direct loop.
+template <class WT>
+__device__ float adjoint_direct(const AdjArgs &a, const WT *Wt, int b, int ci, int id, int ih, int iw)
+{
+    const int OD = a.D / 2, OH = a.H / 2, OW = a.W / 2;
+    const int64_t osp = (int64_t)OD * OH * OW;
+    float s = a.bias ? a.bias[ci] : 0.f;
+    for (int co = 0; co < a.Co; ++co)
+        for (int t = 0; t < 27; ++t) {
+            const int z = id + 1 - t / 9, y = ih + 1 - t / 3 % 3, x = iw + 1 - t % 3;
+            if (((z | y | x) & 1) || (z >> 1) >= OD || (y >> 1) >= OH || (x >> 1) >= OW) continue;
+            const float g = a.dY[((int64_t)b * a.Co + co) * osp + ((z >> 1) * OH + (y >> 1)) * OW + (x >> 1)];
+            s = __builtin_fmaf(wt_f32(Wt[((int64_t)co * a.Ci + ci) * 27 + t]), g, s);
+        }
+    return s;
+}
+
+// Tap of parity p for neighbour i (0: j + 1, 1: j); -1: none.
+__device__ __forceinline__ int adj_tap(int p, int i) { return p ? 2 * i : (i ? 1 : -1); }
+
+// PZ, PY = 1, 1 with ROWS8: the tile of few fine channels (all eight parities); otherwise the
+// tile of z and y parity PZ, PY. CO: Co rounded up to the registers' size.
+template <class WT, int PZ, int PY, bool ROWS8, int CO>
+__device__ __forceinline__ void adjoint_tile(const AdjArgs &a, const WT *Wt, const WT *wsh, int ci0)
+{
+    constexpr int CIB = ROWS8 ? 2 : 8;
+    constexpr int NK = PZ && PY ? 2 * CO : (PZ || PY ? CO : CO / 2);   // products per 16 voxels
+    constexpr int KC = NK < 8 ? NK : 8, NG = kAdjNG, NCH = NK / KC, R = 4;
+    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6, l16 = lane & 15, kq = lane >> 4;
+    const int OD = a.D / 2, OH = a.H / 2, OW = a.W / 2;
+    const int osp = OD * OH * OW;
+    const int nci = min(CIB, a.Ci - ci0);
+    // Row of this lane's weights, and its neighbours: x always by kq's low bit; z and y by the
+    // high bit or the product's parity.
+    const int cil = ROWS8 ? (l16 >> 1) & 1 : l16 >> 1, px = l16 & 1;
+    const int pz = ROWS8 ? l16 >> 3 : PZ, py = ROWS8 ? (l16 >> 2) & 1 : PY;
+    const int xi = kq & 1, hi = kq >> 1;
+    float w[NK];
+#pragma unroll
+    for (int s = 0; s < NK; ++s) {
+        int co, zi, yi;
+        if (PZ && PY) { co = s / 2; zi = s & 1; yi = hi; }
+        else if (PZ) { co = s; zi = hi; yi = 1; }
+        else if (PY) { co = s; zi = 1; yi = hi; }
+        else { co = 2 * s + hi; zi = 1; yi = 1; }
+        const int tz = adj_tap(pz, zi), ty = adj_tap(py, yi), tx = adj_tap(px, xi);
+        const bool ok = tz >= 0 && ty >= 0 && tx >= 0 && cil < nci && co < a.Co;
+        w[s] = wt_f32(wsh[ok ? (co * CIB + cil) * 27 + tz * 9 + ty * 3 + tx : CO * CIB * 27]);
+    }
+    float binit[4];
+#pragma unroll
+    for (int r = 0; r < 4; ++r) {
+        const int c = ROWS8 ? r >> 1 : 2 * kq + (r >> 1);
+        binit[r] = a.bias && c < nci ? a.bias[ci0 + c] : 0.f;
+    }
+    const int g0 = (blockIdx.x * 4 + wave) * a.gpw, g1 = min(a.groups, g0 + a.gpw);
+    // The buffer starts at this block's first sample; the host checks the block's samples.
+    const int64_t pb = (int64_t)blockIdx.x * 4 * a.gpw * 16;
+    const int b0 = (int)(pb / osp);
+    const rsrc_t yr = make_rsrc(a.dY + (int64_t)b0 * a.Co * osp, (int64_t)(a.B - b0) * a.Co * osp * 4);
+    const int64_t fsp = 8 * (int64_t)osp;
+    int vb[NG], vz[NG], vy[NG], vx[NG];
+#pragma unroll
+    for (int j = 0; j < NG; ++j) {
+        const int o = (int)((int64_t)(g0 + j) * 16 + l16 - (int64_t)b0 * osp);
+        vx[j] = o % OW;
+        vy[j] = o / OW % OH;
+        vz[j] = o / (OW * OH);
+        vb[j] = vz[j] / OD;
+        vz[j] -= vb[j] * OD;
+    }
+    for (int g = g0; g < g1; g += NG) {
+        uint32_t off[NG][2];
+        f32x4 acc[NG];
+#pragma unroll
+        for (int j = 0; j < NG; ++j) {
+            const bool in = g + j < g1 && b0 + vb[j] < a.B;
+            const int nx = 1 - xi;
+#pragma unroll
+            for (int e = 0; e < 2; ++e) {
+                int ny, nz, dc = 0;
+                if (PZ && PY) { nz = 1 - e; ny = 1 - hi; }
+                else if (PZ) { nz = 1 - hi; ny = 0; }
+                else if (PY) { nz = 0; ny = 1 - hi; }
+                else { nz = ny = 0; dc = hi; }
+                const bool ok = in & (vz[j] + nz < OD) & (vy[j] + ny < OH) & (vx[j] + nx < OW);
+                off[j][e] = ok ? 4u * (uint32_t)((vb[j] * a.Co + dc) * osp +
+                                                 ((vz[j] + nz) * OH + vy[j] + ny) * OW + vx[j] + nx)
+                               : kOut;
+            }
+#pragma unroll
+            for (int r = 0; r < 4; ++r) acc[j][r] = binit[r];
+        }
+        float v[R][KC][NG];                      // loads three batches of products ahead
+        auto load = [&](int c) {
+#pragma unroll
+            for (int k = 0; k < KC; ++k) {
+                const int s = c * KC + k;
+                const int co = PZ && PY ? s / 2 : (PZ || PY ? s : 2 * s);
+                const uint32_t so = 4u * (uint32_t)osp * (uint32_t)min(co, a.Co - 1);
+#pragma unroll
+                for (int j = 0; j < NG; ++j)
+                    v[c % R][k][j] = buf_f32(yr, off[j][PZ && PY ? s & 1 : 0], so);
+            }
+        };
+#pragma unroll
+        for (int c = 0; c < R - 1 && c < NCH; ++c) load(c);
+#pragma unroll
+        for (int c = 0; c < NCH; ++c) {
+            if (c + R - 1 < NCH) load(c + R - 1);
+#pragma unroll
+            for (int k = 0; k < KC; ++k)
+#pragma unroll
+                for (int j = 0; j < NG; ++j)
+                    acc[j] = __builtin_amdgcn_mfma_f32_16x16x4f32(w[c * KC + k], v[c % R][k][j], acc[j], 0, 0, 0);
+        }
+        int redo = 0;                            // groups in which this lane found a NaN
+#pragma unroll
+        for (int j = 0; j < NG; ++j) {
+            const bool in = g + j < g1 && b0 + vb[j] < a.B;
+            const int oz = ROWS8 ? kq >> 1 : PZ, oy = ROWS8 ? kq & 1 : PY;
+            float *d = a.dX + ((int64_t)(b0 + vb[j]) * a.Ci + ci0) * fsp +
+                       ((int64_t)(2 * vz[j] + oz) * a.H + 2 * vy[j] + oy) * a.W + 2 * vx[j];
+#pragma unroll
+            for (int e = 0; e < 2; ++e) {
+                const int c = ROWS8 ? e : 2 * kq + e;
+                float r0 = acc[j][2 * e], r1 = acc[j][2 * e + 1];
+                if (in && c < nci && (!(r0 == r0) || !(r1 == r1))) redo |= 1 << j;
+                if (a.relu && r0 < 0.f) r0 = 0.f;
+                if (a.relu && r1 < 0.f) r1 = 0.f;
+                if (in && c < nci) *reinterpret_cast<f32x2_u *>(d + c * fsp) = (f32x2_u){r0, r1};
+            }
+            advance(vb[j], vz[j], vy[j], vx[j], a.st, OD, OH, OW);
+        }
+        if (__any(redo)) {
+#pragma unroll 1
+            for (int q = 0; q < 4 * NG; ++q) {
+                if (!(redo >> (q >> 2) & 1)) continue;
+                const int o = (int)((int64_t)(g + (q >> 2)) * 16 + l16 - (int64_t)b0 * osp);
+                const int b = b0 + o / osp, e = (q >> 1) & 1, c = ROWS8 ? e : 2 * kq + e;
+                const int id = 2 * (o / (OW * OH) % OD) + (ROWS8 ? kq >> 1 : PZ);
+                const int ih = 2 * (o / OW % OH) + (ROWS8 ? kq & 1 : PY), iw = 2 * (o % OW) + (q & 1);
+                if (c >= nci) continue;
+                float r = adjoint_direct(a, Wt, b, ci0 + c, id, ih, iw);
+                if (a.relu && r < 0.f) r = 0.f;
+                a.dX[((int64_t)b * a.Ci + ci0 + c) * fsp + ((int64_t)id * a.H + ih) * a.W + iw] = r;
+            }
+        }
+    }
+}
+
+// grid (shares of the voxels, tiles): tiles of one fine-channel block are (pz, py) = (1, 1),
+// (1, 0), (0, 1), (0, 0), the longest first.
+template <class WT, bool ROWS8, int CO>
+__global__ void __launch_bounds__(256) conv_adjoint_kernel(AdjArgs a, const WT *__restrict__ Wt)
+{
+    constexpr int CIB = ROWS8 ? 2 : 8;
+    __shared__ WT wsh[CO * CIB * 27 + 1];                // and a zero for the taps a row lacks
+    const int ci0 = (ROWS8 ? 0 : blockIdx.y / 4) * CIB, nci = min(CIB, a.Ci - ci0);
+    // Loads in batches: one at a time, their latency was most of the small layers' time.
+    constexpr int N = CO * CIB * 27, NB = (N + 255) / 256, U = 18;
+    const rsrc_t wr = make_rsrc(Wt, (int64_t)a.Co * a.Ci * 27 * sizeof(WT));
+    if (threadIdx.x == 0) wsh[N] = (WT)0;
+#pragma unroll
+    for (int k0 = 0; k0 < NB; k0 += U) {
+        WT v[U];
+#pragma unroll
+        for (int k = 0; k < U; ++k) {
+            const int t = (k0 + k) * 256 + threadIdx.x, co = t / (CIB * 27), r = t - co * (CIB * 27);
+            v[k] = buf_w(wr, k0 + k < NB && co < a.Co && r < nci * 27,
+                         (uint32_t)((co * a.Ci + ci0) * 27 + r), (WT)0);
+        }
+#pragma unroll
+        for (int k = 0; k < U; ++k) {
+            const int t = (k0 + k) * 256 + threadIdx.x;
+            if (t < N) wsh[t] = v[k];
+        }
+    }
+    __syncthreads();
+    if (ROWS8) adjoint_tile<WT, 1, 1, true, CO>(a, Wt, wsh, ci0);
+    else if (blockIdx.y % 4 == 0) adjoint_tile<WT, 1, 1, false, CO>(a, Wt, wsh, ci0);
+    else if (blockIdx.y % 4 == 1) adjoint_tile<WT, 1, 0, false, CO>(a, Wt, wsh, ci0);
+    else if (blockIdx.y % 4 == 2) adjoint_tile<WT, 0, 1, false, CO>(a, Wt, wsh, ci0);
+    else adjoint_tile<WT, 0, 0, false, CO>(a, Wt, wsh, ci0);
+}
+
+template <class WT>
+hipError_t adjoint_launch(const AdjArgs &a, const WT *Wt, hipStream_t s)
+{
+    const unsigned gx = (unsigned)((a.groups + 4 * a.gpw - 1) / (4 * a.gpw));
+    const unsigned gy = a.Ci <= 2 ? 1 : 4 * ((a.Ci + 7) / 8);
+#define TDB_ADJ(ROWS8_, CO_)                                                                       \
+    hipLaunchKernelGGL((conv_adjoint_kernel<WT, ROWS8_, CO_>), dim3(gx, gy), dim3(256), 0, s, a, Wt)
+    if (a.Ci <= 2) {
+        if (a.Co <= 8) TDB_ADJ(true, 8);
+        else TDB_ADJ(true, 64);
+    } else {
+        if (a.Co <= 16) TDB_ADJ(false, 16);
+        else if (a.Co <= 32) TDB_ADJ(false, 32);
+        else TDB_ADJ(false, 64);
+    }
+#undef TDB_ADJ
+    return hipGetLastError();
+}
+
+}  // namespace
+
+bool conv_adjoint_ok(int B, int Ci, int Co, int D, int H, int W)
+{
+    const int64_t osp = (int64_t)(D / 2) * (H / 2) * (W / 2), P = (int64_t)B * osp;
+    // More coarse channels would not fit the registers; an odd count would pair its last one
+    // with a channel past the end.
+    if (Co > 64 || (Co & 1) || P >= ((int64_t)1 << 31) - 65536) return false;
+    // A block's voxels (at most 1,024, see launch_conv_adjoint) and their neighbours lie in
+    // these samples, addressed with 31-bit byte offsets.
+    return (1023 / osp + 2) * Co * osp * 4 < ((int64_t)1 << 31);
+}
+
+hipError_t launch_conv_adjoint(bool bf16w, int B, int Ci, int Co, int D, int H, int W,
+                               const float *dY, const void *Wt, const float *bias, int relu,
+                               float *dX, hipStream_t s)
+{
+    const int64_t P = (int64_t)B * (D / 2) * (H / 2) * (W / 2);
+    AdjArgs a = {B, Ci, Co, D, H, W, relu, (int)((P + 15) / 16), kAdjNG,
+                 step_of(16 * kAdjNG, D / 2, H / 2, W / 2), dY, bias, dX};
+    // Two 16-voxel groups go together; up to 16 per wave while 1,024 blocks remain.
+    const int tiles = Ci <= 2 ? 1 : 4 * ((Ci + 7) / 8);
+    while (a.gpw < 16 && (int64_t)a.groups * tiles / (8 * a.gpw) >= 1024) a.gpw *= 2;
+    return bf16w ? adjoint_launch(a, (const uint16_t *)Wt, s)
+                 : adjoint_launch(a, (const float *)Wt, s);
 }
 
 }  // namespace tdb

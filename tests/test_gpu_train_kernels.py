@@ -61,3 +61,56 @@ def test_conv_weight_gradient(shape):
     assert ok, (shape, "dw of the transpose", worst)
     ok, worst = _within(gb, f64.sum((0, 2, 3, 4)), f64.abs().sum((0, 2, 3, 4)), 8 * K)
     assert ok, (shape, "db of the transpose", worst)
+
+
+# (B, Ci, Co, D, H, W): the tile of one and two fine channels and the four parity tiles, each
+# register size (8, 16, 32, 64 coarse channels, exact and with a rest), channel blocks of eight
+# with a rest, groups of 16 voxels across rows and samples and past the last one; odd channel
+# counts take the direct loop.
+ADJOINT = [(2, 2, 8, 10, 12, 32), (3, 1, 4, 6, 10, 6), (1, 2, 16, 4, 4, 34), (2, 2, 40, 4, 6, 8),
+           (2, 8, 16, 6, 8, 32), (3, 3, 10, 6, 10, 14), (2, 16, 32, 10, 6, 18), (5, 9, 18, 2, 6, 2),
+           (3, 32, 64, 8, 8, 8), (4, 20, 34, 4, 2, 6), (7, 1, 8, 2, 2, 2), (2, 4, 7, 6, 4, 8)]
+
+
+@pytest.mark.parametrize("shape", ADJOINT)
+def test_conv_adjoint(shape):
+    need_gpu()
+    from paper_2205_04550_amd import nn
+    B, Ci, Co, D, H, W = shape
+    g = torch.Generator().manual_seed(sum(shape) + 1)
+    coarse = torch.randn(B, Co, D // 2, H // 2, W // 2, generator=g)
+    w = torch.randn(Co, Ci, 3, 3, 3, generator=g) * 0.2
+    b = torch.randn(Ci, generator=g)
+    for wc in (w.to(torch.bfloat16), w):
+        for bias in (b, None):
+            for relu in (False, True):
+                say(f"adjoint {shape} {wc.dtype} bias={bias is not None} relu={relu}")
+                bd = None if bias is None else bias.cuda()
+                y = nn.ConvT3dS2.apply(coarse.cuda(), w.cuda(), bd, wc.cuda(), relu)
+                b64 = None if bias is None else bias.double()
+                yr = E.conv_t(coarse.double(), wc.double(), b64, relu)
+                S = E.conv_t(coarse.double().abs(), wc.double().abs(),
+                             None if b64 is None else b64.abs(), False)
+                ok, worst = _within(y, yr, S, 8 * Co)
+                assert ok, (shape, wc.dtype, relu, worst)
+
+
+@pytest.mark.parametrize("shape", [(2, 2, 8, 8, 8, 32), (2, 12, 16, 6, 8, 10), (2, 16, 64, 4, 4, 4)])
+def test_conv_adjoint_keeps_infinities_and_nans_local(shape):
+    """An infinity or a NaN reaches only the outputs whose taps hold it, with the direct loop's
+    result (the float64 kernel's)."""
+    need_gpu()
+    from paper_2205_04550_amd import nn
+    B, Ci, Co, D, H, W = shape
+    g = torch.Generator().manual_seed(5)
+    coarse = torch.randn(B, Co, D // 2, H // 2, W // 2, generator=g)
+    w = torch.randn(Co, Ci, 3, 3, 3, generator=g) * 0.2
+    for c, z, y, x, val in ((0, 0, 0, 0, float("inf")), (Co - 1, D // 2 - 1, H // 2 - 1, W // 2 - 1, float("-inf")),
+                            (1, 1, 0, 1, float("nan"))):
+        coarse[0, c, z, y, x] = val
+    got = nn.ConvT3dS2.apply(coarse.cuda(), w.cuda(), None, w.cuda(), False).cpu()
+    want = nn.ConvT3dS2.apply(coarse.cuda().double(), w.cuda().double(), None, w.cuda().double(), False).cpu()
+    assert torch.equal(torch.isnan(got), torch.isnan(want))
+    assert torch.equal(torch.isposinf(got), torch.isposinf(want))
+    assert torch.equal(torch.isneginf(got), torch.isneginf(want))
+    assert torch.isfinite(got).any() and not torch.isfinite(got).all()
