@@ -2380,8 +2380,14 @@ int nn_conv3d_s2_fwd(int dtype, int B, int Ci, int Co, int D, int H, int W, cons
     if (pair < 0 || !conv_dims_ok(B, Ci, Co, D, H, W) || !X || !Wt || !Y)
         return tdb_set_error(DB_EINVAL, "nn_conv3d_s2_fwd: bad arguments");
     const hipStream_t s = static_cast<hipStream_t>(stream);
-    if (pair <= 1 && Ci % 4 == 0 && W % 4 == 0 && (uintptr_t)X % 16 == 0 && Co <= 64 &&
-        B <= 65535 && (int64_t)D * H * W * 4 < ((int64_t)1 << 31)) {
+    const bool staged = Ci % 4 == 0 && W % 4 == 0 && (uintptr_t)X % 16 == 0 && Co <= 64 &&
+                        B <= 65535 && (int64_t)D * H * W * 4 < ((int64_t)1 << 31);
+    if (pair <= 1 && conv_fwd_direct_ok(B, Ci, Co, D, H, W, staged)) {
+        (void)launch_conv_fwd_direct(pair == 0, staged, B, Ci, Co, D, H, W, (const float *)X, Wt,
+                                     (const float *)bias, relu, (float *)Y, s);
+        return launched("nn_conv3d_s2_fwd");
+    }
+    if (pair <= 1 && staged) {
         const int e = conv_fwd_mfma(pair == 0, B, Ci, Co, D, H, W, X, Wt, bias, relu, Y, s);
         if (e <= 0) return e;                     // launched (or failed); > 0: shape not covered
     }

@@ -554,4 +554,331 @@ hipError_t launch_conv_adjoint(bool bf16w, int B, int Ci, int Co, int D, int H, 
                  : adjoint_launch(a, (const float *)Wt, s);
 }
 
+namespace {
+
+// ---- forward (also the transposed convolution's input gradient) ---------------------------------
+//
+// Y[co][o] = sum over ci and taps of W[co][ci][tap] X[ci][2 o + tap - 1]: M = 16 coarse channels,
+// N = 16 coarse voxels, one tile per wave at a time. Two orders of k, those of the kernels in
+// nn.hip that this one stands in for:
+//   by channel (CHUNK4 = false; conv_fwd_kernel): from bias[co], over ci, then the taps. Lane
+//     group kq of product s has term 4 s + kq, so its channel and tap differ by lane: a table of
+//     27 offsets per lane repeats every 27 products (4 channels).
+//   by chunk (CHUNK4 = true; conv_mfma_kernel): from 0, over chunks of four channels, the taps,
+//     the four channels; the bias last. Lane group kq is channel kq of the chunk.
+// A block's weights lie in LDS as floats in product order (64 consecutive floats per product);
+// lane l needs X at voxel l % 16: one buffer load per product straight from the caches. The
+// padding is a load out of range; it can only be at the low edge of an axis (2 o + 1 is in
+// range), so eight offsets per voxel (by chunk) or three bit masks per lane (by channel) hold
+// all of it. The buffer starts one plane, row and element before X, which the masked taps alone
+// would read, so that every tap is a positive offset. Batch 32: 20 / 21 us for 16 -> 32 and
+// 32 -> 64, where the staged kernel's few blocks (one 4^3 box of all channels each) took 28 / 67;
+// 32 -> 64 on 6^3 (rows not of fours) 19 us, where the vector kernel took 112. Bound by the chain
+// of its products (216 of 32 cycles for 32 fine channels) and the first loads.
+struct FwdArgs {
+    int B, Ci, Co, D, H, W, relu, groups, gpw, NK;   // NK: products per tile
+    Step st;
+    const float *X, *bias;
+    float *Y;
+};
+constexpr int kFwdMaxNK = 216;   // 32 fine channels: 55 KB of weights
+
+template <class WT, bool CHUNK4, int NG>
+__global__ void __launch_bounds__(256) conv_fwd_direct_kernel(FwdArgs a, const WT *__restrict__ Wt)
+{
+    extern __shared__ float wsh[];                       // [NK][64]: product, lane
+    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6, l16 = lane & 15, kq = lane >> 4;
+    const int OD = a.D / 2, OH = a.H / 2, OW = a.W / 2, HW = a.H * a.W;
+    const int osp = OD * OH * OW, isp = a.D * HW;
+    const int co0 = blockIdx.y * 16, K = a.Ci * 27;
+    const rsrc_t wr = make_rsrc(Wt, (int64_t)a.Co * K * sizeof(WT));
+    // Weights of the tile: thread t takes channel t / 16 of it, terms t % 16 + 16 i.
+    for (int i0 = 0; i0 * 16 < K; i0 += 18) {
+        WT v[18];
+#pragma unroll
+        for (int i = 0; i < 18; ++i) {
+            const int k = (i0 + i) * 16 + (tid & 15), co = co0 + (tid >> 4);
+            v[i] = buf_w(wr, k < K && co < a.Co, (uint32_t)(co * K + k), (WT)0);
+        }
+#pragma unroll
+        for (int i = 0; i < 18; ++i) {
+            const int k = (i0 + i) * 16 + (tid & 15);
+            int s, q;
+            if (CHUNK4) {
+                const int ci = k / 27;
+                s = (ci >> 2) * 27 + k - ci * 27;
+                q = ci & 3;
+            } else {
+                s = k >> 2;
+                q = k & 3;
+            }
+            if (s < a.NK) wsh[s * 64 + q * 16 + (tid >> 4)] = wt_f32(v[i]);
+        }
+    }
+    __syncthreads();
+
+    // By channel: this lane's terms of the 27 products of a period.
+    int tap[CHUNK4 ? 1 : 27];
+    uint32_t mz = 0, my = 0, mx = 0;
+    if (!CHUNK4) {
+#pragma unroll
+        for (int s = 0; s < 27; ++s) {
+            const int k = 4 * s + kq, ci = k / 27, t = k - ci * 27;
+            tap[s] = 4 * (ci * isp + (t / 9) * HW + (t / 3 % 3) * a.W + t % 3);
+            mz |= (uint32_t)(t / 9 == 0) << s;
+            my |= (uint32_t)(t / 3 % 3 == 0) << s;
+            mx |= (uint32_t)(t % 3 == 0) << s;
+        }
+    }
+    const int g0 = (blockIdx.x * 4 + wave) * a.gpw, g1 = min(a.groups, g0 + a.gpw);
+    const int64_t pb = (int64_t)blockIdx.x * 4 * a.gpw * 16;
+    const int b0 = (int)(pb / osp);
+    const int before = HW + a.W + 1;
+    const rsrc_t xr = make_rsrc(a.X + (int64_t)b0 * a.Ci * isp - before,
+                                ((int64_t)(a.B - b0) * a.Ci * isp + before) * 4);
+    int vb[NG], vz[NG], vy[NG], vx[NG];
+#pragma unroll
+    for (int j = 0; j < NG; ++j) {
+        const int o = (int)((int64_t)(g0 + j) * 16 + l16 - (int64_t)b0 * osp);
+        vx[j] = o % OW;
+        vy[j] = o / OW % OH;
+        vz[j] = o / (OW * OH);
+        vb[j] = vz[j] / OD;
+        vz[j] -= vb[j] * OD;
+    }
+    float bq[4];
+#pragma unroll
+    for (int r = 0; r < 4; ++r) {
+        const int co = co0 + 4 * kq + r;
+        bq[r] = a.bias && co < a.Co ? a.bias[co] : 0.f;
+    }
+    constexpr int KC = 9, R = 8 / NG;                    // NK is padded to whole batches
+    for (int g = g0; g < g1; g += NG) {
+        uint32_t off[NG][8], inv[NG];
+        f32x4 acc[NG];
+#pragma unroll
+        for (int j = 0; j < NG; ++j) {
+            const bool in = g + j < g1 && b0 + vb[j] < a.B;
+            const uint32_t o = 4u * (uint32_t)((vb[j] * a.Ci + (CHUNK4 ? kq : 0)) * isp +
+                                               2 * vz[j] * HW + 2 * vy[j] * a.W + 2 * vx[j]);
+            if (CHUNK4) {
+#pragma unroll
+                for (int e = 0; e < 8; ++e) {
+                    const bool ok = in & (!(e & 4) | (vz[j] != 0)) & (!(e & 2) | (vy[j] != 0)) &
+                                    (!(e & 1) | (vx[j] != 0));
+                    off[j][e] = ok ? o : kOut;
+                }
+            } else {
+                off[j][0] = o;
+                inv[j] = in ? (vz[j] ? 0u : mz) | (vy[j] ? 0u : my) | (vx[j] ? 0u : mx) : ~0u;
+            }
+#pragma unroll
+            for (int r = 0; r < 4; ++r) acc[j][r] = CHUNK4 ? 0.f : bq[r];
+        }
+        float v[R][KC][NG];
+        // Batch c: products 9 c .. 9 c + 8, a third of a period, e = c % 3.
+        auto load = [&](int c, int e, float (&d)[KC][NG]) {
+            const uint32_t s0 = 16u * (uint32_t)isp * (uint32_t)(c / 3);
+#pragma unroll
+            for (int k = 0; k < KC; ++k)
+#pragma unroll
+                for (int j = 0; j < NG; ++j) {
+                    if (CHUNK4) {
+                        const int t = 9 * e + k;         // the tap
+                        const uint32_t so = s0 + 4u * (uint32_t)((t / 9) * HW + (t / 3 % 3) * a.W + t % 3);
+                        d[k][j] = buf_f32(xr, off[j][(t / 9 == 0) * 4 + (t / 3 % 3 == 0) * 2 + (t % 3 == 0)], so);
+                    } else {
+                        const int t = 9 * e + k;         // product of the period
+                        d[k][j] = buf_f32(xr, (inv[j] >> t & 1) ? kOut : off[j][0] + (uint32_t)tap[t], s0);
+                    }
+                }
+        };
+        const int nch = a.NK / KC;
+        // Unrolled by lcm(3, R) batches so that every register index is a constant.
+        constexpr int U = R * 3;
+#pragma unroll
+        for (int c = 0; c < R - 1; ++c)
+            if (c < nch) load(c, c % 3, v[c]);
+        for (int cb = 0; cb < nch; cb += U) {
+#pragma unroll
+            for (int u = 0; u < U; ++u) {
+                const int c = cb + u;
+                if (c < nch) {
+                    if (c + R - 1 < nch) load(c + R - 1, (u + R - 1) % 3, v[(u + R - 1) % R]);
+                    const float *w = wsh + c * KC * 64 + lane;
+#pragma unroll
+                    for (int k = 0; k < KC; ++k) {
+                        const float wk = w[k * 64];
+#pragma unroll
+                        for (int j = 0; j < NG; ++j)
+                            acc[j] = __builtin_amdgcn_mfma_f32_16x16x4f32(wk, v[u % R][k][j], acc[j], 0, 0, 0);
+                    }
+                }
+            }
+        }
+#pragma unroll
+        for (int j = 0; j < NG; ++j) {
+            const bool in = g + j < g1 && b0 + vb[j] < a.B;
+            float *d = a.Y + ((int64_t)(b0 + vb[j]) * a.Co + co0 + 4 * kq) * osp +
+                       (vz[j] * OH + vy[j]) * OW + vx[j];
+#pragma unroll
+            for (int r = 0; r < 4; ++r) {
+                float y = CHUNK4 ? acc[j][r] + bq[r] : acc[j][r];
+                if (a.relu && y < 0.f) y = 0.f;
+                if (in && co0 + 4 * kq + r < a.Co) d[(int64_t)r * osp] = y;
+            }
+            advance(vb[j], vz[j], vy[j], vx[j], a.st, OD, OH, OW);
+        }
+    }
+}
+
+// The first layer's forward (at most two fine channels, rows of whole fours): the matrix cores
+// would work on half-empty tiles and lanes would fetch every second element, so here a thread
+// takes four voxels of a row and eight coarse channels: per fine row one pair of 16-byte loads
+// (and the element before them, from the lane before where a wave starts a row), 96 multiply-adds
+// against weights broadcast from LDS. The order is by channel, as above, from the bias. 26 us for
+// 2 -> 8 at 64^3, batch 32 (two voxels per thread with an element per load: 49 us); the
+// multiply-adds alone are 12 us.
+typedef float f32x4_u __attribute__((ext_vector_type(4), aligned(4)));
+template <class WT, bool SHIFT>
+__global__ void __launch_bounds__(256) conv_fwd_first_kernel(FwdArgs a, const WT *__restrict__ Wt)
+{
+    __shared__ __attribute__((aligned(16))) float wsh[2 * 27 * 8];   // [ci][tap][co]
+    const int tid = threadIdx.x, lane = tid & 63;
+    const int OD = a.D / 2, OH = a.H / 2, OW = a.W / 2, HW = a.H * a.W, Q = OW / 4;
+    const int osp = OD * OH * OW, isp = a.D * HW, qsp = osp / 4;
+    const int co0 = blockIdx.y * 8, nco = min(8, a.Co - co0);
+    for (int t = tid; t < a.Ci * 27 * 8; t += 256) {
+        const int c = t & 7, r = t >> 3;
+        wsh[t] = c < nco ? wt_f32(Wt[(int64_t)(co0 + c) * a.Ci * 27 + r]) : 0.f;
+    }
+    __syncthreads();
+    const int64_t t0 = (int64_t)blockIdx.x * 256;
+    const int b0 = (int)(t0 / qsp);
+    const int t = (int)(t0 - (int64_t)b0 * qsp) + tid;
+    const int b = t / qsp, q = t - b * qsp;
+    const int x = q % Q, y = q / Q % OH, z = q / (Q * OH);
+    const bool in = b0 + b < a.B;
+    const rsrc_t xr = make_rsrc(a.X + (int64_t)b0 * a.Ci * isp, (int64_t)(a.B - b0) * a.Ci * isp * 4);
+    float acc[4][8];
+#pragma unroll
+    for (int c = 0; c < 8; ++c) {
+        const float bc = a.bias && c < nco ? a.bias[co0 + c] : 0.f;
+#pragma unroll
+        for (int v = 0; v < 4; ++v) acc[v][c] = bc;
+    }
+    for (int ci = 0; ci < a.Ci; ++ci) {
+        const uint32_t base = 4u * (uint32_t)((b * a.Ci + ci) * isp + 2 * z * HW + 2 * y * a.W + 8 * x);
+        u32x4 lo[9], hi[9];
+        float l[9];
+#pragma unroll
+        for (int r = 0; r < 9; ++r) {
+            const bool ok = in & ((r / 3 != 0) | (z != 0)) & ((r % 3 != 0) | (y != 0));
+            const uint32_t o = ok ? base + 4 * ((r / 3 - 1) * HW + (r % 3 - 1) * a.W) : kOut;
+            lo[r] = __builtin_bit_cast(u32x4, __builtin_amdgcn_raw_buffer_load_b128(xr, o, 0, 0));
+            hi[r] = __builtin_bit_cast(u32x4, __builtin_amdgcn_raw_buffer_load_b128(xr, ok ? o + 16 : kOut, 0, 0));
+            if (!SHIFT) l[r] = buf_f32(xr, ok & (x != 0) ? o - 4 : kOut);
+        }
+#pragma unroll
+        for (int r = 0; r < 9; ++r) {
+            if (SHIFT) {
+                l[r] = __uint_as_float(__builtin_amdgcn_update_dpp(0, hi[r].w, 0x138, 0xf, 0xf, true));   // wave_shr:1
+                l[r] = x ? l[r] : 0.f;
+            }
+            const float e[9] = {l[r], __uint_as_float(lo[r].x), __uint_as_float(lo[r].y),
+                                __uint_as_float(lo[r].z), __uint_as_float(lo[r].w),
+                                __uint_as_float(hi[r].x), __uint_as_float(hi[r].y),
+                                __uint_as_float(hi[r].z), __uint_as_float(hi[r].w)};
+#pragma unroll
+            for (int k = 0; k < 3; ++k) {
+                const f32x4 *w = reinterpret_cast<const f32x4 *>(wsh + ((ci * 9 + r) * 3 + k) * 8);
+                const f32x4 w0 = w[0], w1 = w[1];
+#pragma unroll
+                for (int v = 0; v < 4; ++v)
+#pragma unroll
+                    for (int c = 0; c < 8; ++c)
+                        acc[v][c] = __builtin_fmaf(c < 4 ? w0[c & 3] : w1[c & 3], e[2 * v + k], acc[v][c]);
+            }
+        }
+    }
+    if (!in) return;
+    float *d = a.Y + ((int64_t)(b0 + b) * a.Co + co0) * osp + 4 * q;
+#pragma unroll
+    for (int c = 0; c < 8; ++c) {
+        if (c >= nco) break;
+        f32x4_u o;
+#pragma unroll
+        for (int v = 0; v < 4; ++v) o[v] = a.relu && acc[v][c] < 0.f ? 0.f : acc[v][c];
+        *reinterpret_cast<f32x4_u *>(d + (int64_t)c * osp) = o;
+    }
+}
+
+template <class WT>
+hipError_t fwd_first_launch(const FwdArgs &a, const WT *Wt, hipStream_t s)
+{
+    const int64_t T = (int64_t)a.B * (a.D / 2) * (a.H / 2) * (a.W / 8);
+    const dim3 grid((unsigned)((T + 255) / 256), (unsigned)((a.Co + 7) / 8));
+    if (64 % (a.W / 8) == 0)
+        hipLaunchKernelGGL((conv_fwd_first_kernel<WT, true>), grid, dim3(256), 0, s, a, Wt);
+    else
+        hipLaunchKernelGGL((conv_fwd_first_kernel<WT, false>), grid, dim3(256), 0, s, a, Wt);
+    return hipGetLastError();
+}
+
+template <class WT, bool CHUNK4>
+hipError_t fwd_launch(FwdArgs a, const WT *Wt, hipStream_t s)
+{
+    const int tiles = (a.Co + 15) / 16;
+    // Two groups of voxels share a product's weights where there are waves enough; fewer leave
+    // the small layers' chains side by side.
+    const bool two = (int64_t)a.groups * tiles >= 8192;
+    a.gpw = two ? 2 : 1;
+    while (a.gpw < 16 && (int64_t)a.groups * tiles / (8 * a.gpw) >= 1024) a.gpw *= 2;
+    a.st = step_of(two ? 32 : 16, a.D / 2, a.H / 2, a.W / 2);
+    const dim3 grid((unsigned)((a.groups + 4 * a.gpw - 1) / (4 * a.gpw)), (unsigned)tiles);
+    const size_t lds = (size_t)a.NK * 64 * sizeof(float);
+    if (two)
+        hipLaunchKernelGGL((conv_fwd_direct_kernel<WT, CHUNK4, 2>), grid, dim3(256), lds, s, a, Wt);
+    else
+        hipLaunchKernelGGL((conv_fwd_direct_kernel<WT, CHUNK4, 1>), grid, dim3(256), lds, s, a, Wt);
+    return hipGetLastError();
+}
+
+// Products per tile, in whole batches of nine.
+int fwd_products(int Ci, bool chunk4)
+{
+    const int n = chunk4 ? Ci / 4 * 27 : (Ci * 27 + 3) / 4;
+    return (n + 8) / 9 * 9;
+}
+
+}  // namespace
+
+bool conv_fwd_direct_ok(int B, int Ci, int Co, int D, int H, int W, bool chunk4)
+{
+    const int64_t osp = (int64_t)(D / 2) * (H / 2) * (W / 2), P = (int64_t)B * osp;
+    // By chunk with rows of 16 and more voxels the staged kernel is as fast (24 us against 26 for
+    // 8 -> 16 at batch 32); by channel, two fine channels leave the lanes half idle (72 us
+    // against 49 for the vector kernel, 2 -> 8 at 64^3) unless the first layer's kernel takes them.
+    if (chunk4 ? (W / 2) % 16 == 0 : Ci <= 2 && W % 8 != 0) return false;
+    if (fwd_products(Ci, chunk4) > kFwdMaxNK || Co > 1024 || P >= ((int64_t)1 << 31) - 65536) return false;
+    // A block's voxels (at most 1,024) lie in these samples, addressed with 31-bit byte offsets.
+    return ((1023 / osp + 2) * Ci + 4) * (8 * osp) * 4 < ((int64_t)1 << 31);
+}
+
+hipError_t launch_conv_fwd_direct(bool bf16w, bool chunk4, int B, int Ci, int Co, int D, int H,
+                                  int W, const float *X, const void *Wt, const float *bias, int relu,
+                                  float *Y, hipStream_t s)
+{
+    const int64_t P = (int64_t)B * (D / 2) * (H / 2) * (W / 2);
+    const FwdArgs a = {B, Ci, Co, D, H, W, relu, (int)((P + 15) / 16), 0, fwd_products(Ci, chunk4),
+                       {}, X, bias, Y};
+    if (Ci <= 2 && !chunk4)
+        return bf16w ? fwd_first_launch(a, (const uint16_t *)Wt, s) : fwd_first_launch(a, (const float *)Wt, s);
+    if (bf16w)
+        return chunk4 ? fwd_launch<uint16_t, true>(a, (const uint16_t *)Wt, s)
+                      : fwd_launch<uint16_t, false>(a, (const uint16_t *)Wt, s);
+    return chunk4 ? fwd_launch<float, true>(a, (const float *)Wt, s)
+                  : fwd_launch<float, false>(a, (const float *)Wt, s);
+}
+
 }  // namespace tdb

@@ -114,3 +114,34 @@ def test_conv_adjoint_keeps_infinities_and_nans_local(shape):
     assert torch.equal(torch.isposinf(got), torch.isposinf(want))
     assert torch.equal(torch.isneginf(got), torch.isneginf(want))
     assert torch.isfinite(got).any() and not torch.isfinite(got).all()
+
+
+# (B, Ci, Co, D, H, W): the first layer's kernel (one and two fine channels, rows of fours that
+# start a wave and that do not, coarse channels past eight); by chunk (channels in fours, rows of
+# fours) and by channel (the rest) with one and two groups of voxels per wave, terms that do not
+# fill a product or a batch, 16-channel tiles with a rest, up to 32 fine channels and past them.
+FORWARD = [(2, 2, 8, 8, 6, 64), (3, 1, 11, 6, 10, 24), (2, 2, 5, 4, 4, 8), (1, 1, 8, 10, 6, 256),
+           (2, 2, 8, 4, 6, 12), (3, 4, 16, 6, 4, 8), (2, 32, 64, 8, 8, 8), (5, 12, 20, 4, 6, 12),
+           (2, 3, 9, 6, 8, 10), (3, 32, 33, 4, 4, 6), (2, 5, 16, 8, 6, 32), (2, 36, 16, 4, 4, 8),
+           (9, 8, 16, 32, 32, 24), (17, 6, 16, 32, 32, 18)]
+
+
+@pytest.mark.parametrize("shape", FORWARD)
+def test_conv_forward(shape):
+    need_gpu()
+    from paper_2205_04550_amd import nn
+    B, Ci, Co, D, H, W = shape
+    g = torch.Generator().manual_seed(sum(shape) + 2)
+    fine = torch.randn(B, Ci, D, H, W, generator=g)
+    w = torch.randn(Co, Ci, 3, 3, 3, generator=g) * 0.2
+    b = torch.randn(Co, generator=g)
+    S = E.conv(fine.double().abs(), w.double().abs() * 1.01, b.double().abs(), False)
+    for wc in (w.to(torch.bfloat16), w):
+        for bias in (b, None):
+            for relu in (False, True):
+                say(f"forward {shape} {wc.dtype} bias={bias is not None} relu={relu}")
+                y = nn.Conv3dS2.apply(fine.cuda(), w.cuda(), None if bias is None else bias.cuda(),
+                                      wc.cuda(), relu)
+                yr = E.conv(fine.double(), wc.double(), None if bias is None else bias.double(), relu)
+                ok, worst = _within(y, yr, S, 27 * Ci)
+                assert ok, (shape, wc.dtype, relu, worst)
