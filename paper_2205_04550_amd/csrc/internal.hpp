@@ -213,6 +213,14 @@ bool conv_fwd_direct_ok(int B, int Ci, int Co, int D, int H, int W, bool chunk4)
 hipError_t launch_conv_fwd_direct(bool bf16w, bool chunk4, int B, int Ci, int Co, int D, int H,
                                   int W, const float *X, const void *Wt, const float *bias, int relu,
                                   float *Y, hipStream_t s);
+// C[m][n] = act(bias[n] + sum_k A[m][k] W(k, n)) of a small batch, W [N][K] or (kn) [K][N]; K and
+// (kn) N multiples of 4, sizes for which linear_small_ok holds. The bits of linear_mfma_kernel.
+bool linear_small_ok(int M, int N, int K);
+hipError_t launch_linear_small(bool bf16w, bool kn, int M, int N, int K, const float *A, const void *Wt,
+                               const float *bias, int relu, float *C, hipStream_t s);
+bool linear_wgrad_ok(int B, int In, int Out);
+hipError_t launch_linear_wgrad(int B, int In, int Out, const float *X, const float *dY, float *dW,
+                               float *dbias, hipStream_t s);
 
 // Row boxes, moments, box-restricted scan, centre-of-mass distances (sparse.hip).
 // Per entry of recs: box (rows with a set bit), tbox (rows with a T1Gd bit), mom, and the

@@ -2529,7 +2529,10 @@ int nn_linear_fwd(int dtype, int B, int In, int Out, const void *X, const void *
     // The matrix-core path loads four k at a time: rows and bases must be aligned to that.
     const size_t wal = pair == 0 ? 8 : 16;
     const bool vec = In % 4 == 0 && (uintptr_t)X % 16 == 0 && (uintptr_t)Wt % wal == 0;
-    if (pair == 0 && vec)
+    if (pair <= 1 && vec && linear_small_ok(B, Out, In))
+        (void)launch_linear_small(pair == 0, false, B, Out, In, (const float *)X, Wt,
+                                  (const float *)bias, relu, (float *)Y, s);
+    else if (pair == 0 && vec)
         hipLaunchKernelGGL((linear_mfma_kernel<uint16_t, false>), mgrid, dim3(512), 0, s, B, Out, In,
                            (const float *)X, (const uint16_t *)Wt, (const float *)bias, relu,
                            (float *)Y);
@@ -2565,7 +2568,10 @@ int nn_linear_bwd_data(int dtype, int B, int In, int Out, const void *dY, const 
     const size_t wal = pair == 0 ? 8 : 16;
     const bool vec = In % 4 == 0 && Out % 4 == 0 && (uintptr_t)dY % 16 == 0 &&
                      (uintptr_t)Wt % wal == 0;
-    if (pair == 0 && vec)
+    if (pair <= 1 && vec && linear_small_ok(B, In, Out))
+        (void)launch_linear_small(pair == 0, true, B, In, Out, (const float *)dY, Wt, nullptr, 0,
+                                  (float *)dX, s);
+    else if (pair == 0 && vec)
         hipLaunchKernelGGL((linear_mfma_kernel<uint16_t, true>), mgrid, dim3(512), 0, s, B, In, Out,
                            (const float *)dY, (const uint16_t *)Wt, (const float *)nullptr, 0,
                            (float *)dX);
@@ -2596,7 +2602,10 @@ int nn_linear_bwd_weight(int dtype, int B, int In, int Out, const void *X, const
         return tdb_set_error(DB_EINVAL, "nn_linear_bwd_weight: bad arguments");
     const hipStream_t s = static_cast<hipStream_t>(stream);
     const dim3 grid((In + 255) / 256, Out);
-    if (dtype == NN_F32)
+    if (dtype == NN_F32 && linear_wgrad_ok(B, In, Out))
+        (void)launch_linear_wgrad(B, In, Out, (const float *)X, (const float *)dY, (float *)dWt,
+                                  (float *)dbias, s);
+    else if (dtype == NN_F32)
         hipLaunchKernelGGL(linear_bwd_weight_kernel<float>, grid, dim3(256), 0, s, B, In, Out,
                            (const float *)X, (const float *)dY, (float *)dWt, (float *)dbias);
     else

@@ -881,4 +881,256 @@ hipError_t launch_conv_fwd_direct(bool bf16w, bool chunk4, int B, int Ci, int Co
                   : fwd_launch<float, false>(a, (const float *)Wt, s);
 }
 
+namespace {
+
+// ---- linear layers of a small batch --------------------------------------------------------------
+//
+// C[m][n] = act(bias[n] + sum over k of A[m][k] W(k, n)), W [N][K] (forward) or [K][N] (input
+// gradient, KN). The order of linear_mfma_kernel, bit for bit: two chains over k, wave kh of a
+// pair taking of every 64 terms 16 kh + s and 32 + 16 kh + s alternately (s = 0 .. 15), added at
+// the end. That kernel's 64 x 64 tiles leave a batch of 32 eight blocks; here a pair of waves
+// takes 16 rows and NT x 16 columns straight from the caches, so the same batch runs 64 to 256
+// pairs side by side, each as long as its chain of products. In product p of 64 terms lane group
+// kq holds term 32 (kq & 1) + 2 p + (kq >> 1): it loads its 16 consecutive terms and uses every
+// second. KN: lane n holds columns 4 (l % 16) .. + 3 (NT = 4), one for each of four tiles.
+// Batch 32: 33 / 13 us forward (4096 -> 512 / 512 -> 4096; 128 / 19 for the 64 x 64 tiles), 16 / 31
+// us for the input gradients (25 / 171). The long chains (4,096 terms) run at half a microsecond
+// per 64 terms, five times their products: every row starts at a multiple of 8 KB, so the blocks,
+// all at the same k, read from few of the L2's channels at a time.
+template <class WT>
+struct Frag;   // 16 consecutive values, loaded in fours
+template <>
+struct Frag<uint16_t> {
+    u32x2_t v[4];
+    __device__ void load4(rsrc_t r, int i, uint32_t off)
+    {
+        v[i] = __builtin_bit_cast(u32x2_t, __builtin_amdgcn_raw_buffer_load_b64(r, off, 8 * i, 0));
+    }
+    // Element 2 p or (odd) 2 p + 1.
+    __device__ float get(int p, bool odd) const
+    {
+        const uint32_t u = v[p >> 1][p & 1];
+        return __uint_as_float(odd ? u & 0xffff0000u : u << 16);
+    }
+};
+template <>
+struct Frag<float> {
+    u32x4 v[4];
+    __device__ void load4(rsrc_t r, int i, uint32_t off)
+    {
+        v[i] = __builtin_bit_cast(u32x4, __builtin_amdgcn_raw_buffer_load_b128(r, off, 16 * i, 0));
+    }
+    __device__ float get(int p, bool odd) const
+    {
+        const uint32_t a = v[p >> 1][2 * (p & 1)], b = v[p >> 1][2 * (p & 1) + 1];
+        return __uint_as_float(odd ? b : a);
+    }
+};
+
+struct LinArgs {
+    int M, N, K, relu;
+    const float *A, *bias;
+    float *C;
+};
+
+template <class WT, bool KN, int NT>
+__global__ void __launch_bounds__(128) linear_small_kernel(LinArgs a, const WT *__restrict__ Wt)
+{
+    __shared__ f32x4 other[NT][64];
+    const int lane = threadIdx.x & 63, kh = threadIdx.x >> 6, l16 = lane & 15, kq = lane >> 4;
+    const int m0 = blockIdx.y * 16, n0 = blockIdx.x * 16 * NT;
+    const rsrc_t ar = make_rsrc(a.A, (int64_t)a.M * a.K * 4);
+    const rsrc_t wr = make_rsrc(Wt, (int64_t)a.N * a.K * sizeof(WT));
+    const int m = m0 + l16, n = KN ? n0 + NT * l16 : n0 + l16;
+    const bool odd = kq >> 1;
+    const int kb = 16 * kh + 32 * (kq & 1);              // first of this lane's 16 terms of 64
+    constexpr int R = NT == 4 ? 4 : 8;                   // 64-term chunks in flight
+    Frag<float> fa[R];
+    Frag<WT> fb[KN ? 1 : R];
+    uint32_t kw[KN ? R : 1][8][NT];                      // KN: the lane's eight terms, raw
+    const int nch = (a.K + 63) / 64;
+    auto load = [&](int c, int u) {
+        const int k = 64 * c + kb;
+        // K is a multiple of 4: a group of four terms is inside or outside as a whole.
+        const uint32_t e = (uint32_t)m * (uint32_t)a.K + k;
+#pragma unroll
+        for (int i = 0; i < 4; ++i)
+            fa[u].load4(ar, i, m < a.M && k + 4 * i < a.K ? 4 * e : kOut);
+        if (!KN) {
+            const uint32_t w = (uint32_t)n * (uint32_t)a.K + k;
+#pragma unroll
+            for (int i = 0; i < 4; ++i)
+                fb[u].load4(wr, i, n < a.N && k + 4 * i < a.K ? (uint32_t)sizeof(WT) * w : kOut);
+        } else {
+#pragma unroll
+            for (int p = 0; p < 8; ++p) {
+                const int kk = k + 2 * p + (odd ? 1 : 0);
+                const uint32_t w = (uint32_t)kk * (uint32_t)a.N + n;
+                const bool in = kk < a.K && n < a.N;
+                if (NT == 4 && sizeof(WT) == 2) {
+                    const u32x2_t v = __builtin_bit_cast(u32x2_t, __builtin_amdgcn_raw_buffer_load_b64(
+                        wr, in ? 2 * w : kOut, 0, 0));
+                    kw[u][p][0] = v.x;
+                    kw[u][p][1 % NT] = v.y;
+                } else if (NT == 4) {
+                    const u32x4 v = __builtin_bit_cast(u32x4, __builtin_amdgcn_raw_buffer_load_b128(
+                        wr, in ? 4 * w : kOut, 0, 0));
+#pragma unroll
+                    for (int t = 0; t < NT; ++t) kw[u][p][t] = v[t % 4];
+                } else if (sizeof(WT) == 2) {
+                    kw[u][p][0] = (uint32_t)buf_w(wr, in, w, (WT)0);
+                } else {
+                    kw[u][p][0] = __float_as_uint((float)buf_w(wr, in, w, (WT)0));
+                }
+            }
+        }
+    };
+    // Column t of term p of chunk slot u.
+    auto bval = [&](int u, int p, int t) {
+        if (!KN) return fb[KN ? 0 : u].get(p, odd);
+        if (sizeof(WT) == 4) return __uint_as_float(kw[KN ? u : 0][p][t]);
+        if (NT == 1) return __uint_as_float(kw[KN ? u : 0][p][0] << 16);
+        const uint32_t v = kw[KN ? u : 0][p][(t >> 1) % NT];
+        return __uint_as_float(t & 1 ? v & 0xffff0000u : v << 16);
+    };
+    f32x4 acc[NT];
+#pragma unroll
+    for (int t = 0; t < NT; ++t) acc[t] = (f32x4){0.f, 0.f, 0.f, 0.f};
+    // Loads are unconditional (zeros past the end), so that each wait counts those in flight.
+#pragma unroll
+    for (int u = 0; u < R - 1; ++u) load(u, u);
+    for (int cb = 0; cb < nch; cb += R) {
+#pragma unroll
+        for (int u = 0; u < R; ++u) {
+            load(cb + u + R - 1, (u + R - 1) % R);
+            if (cb + u < nch) {
+#pragma unroll
+                for (int p = 0; p < 8; ++p) {
+                    const float av = fa[u].get(p, odd);
+#pragma unroll
+                    for (int t = 0; t < NT; ++t)
+                        acc[t] = __builtin_amdgcn_mfma_f32_16x16x4f32(av, bval(u, p, t), acc[t], 0, 0, 0);
+                }
+            }
+        }
+    }
+    if (kh) {
+#pragma unroll
+        for (int t = 0; t < NT; ++t) other[t][lane] = acc[t];
+    }
+    __syncthreads();
+    if (kh) return;
+#pragma unroll
+    for (int t = 0; t < NT; ++t) {
+        const int nn = KN ? n + t : n0 + l16;
+        if (nn >= a.N) continue;
+        const f32x4 o = other[t][lane];
+        const float bn = a.bias ? a.bias[nn] : 0.f;
+#pragma unroll
+        for (int r = 0; r < 4; ++r) {
+            const int mm = m0 + 4 * kq + r;
+            float v = acc[t][r] + o[r];
+            v += bn;
+            if (a.relu && v < 0.f) v = 0.f;
+            if (mm < a.M) a.C[(int64_t)mm * a.N + nn] = v;
+        }
+    }
+}
+
+// dW[j][i] = sum over b of dY[b][j] X[b][i], b ascending as in linear_bwd_weight_kernel, and
+// dbias[j]. A wave takes 16 rows j and 64 columns i: four products per four samples, lane n
+// holding columns 4 (l % 16) .. + 3 as one 16-byte load; dbias is a fifth product with ones, in
+// the first columns' waves. Bound by the writes of dW: 5 us for 512 x 4096 at batch 32 (one thread
+// per element: 32 us).
+__global__ void __launch_bounds__(256) linear_wgrad_kernel(int B, int In, int Out,
+                                                           const float *__restrict__ X,
+                                                           const float *__restrict__ dY,
+                                                           float *__restrict__ dW,
+                                                           float *__restrict__ dbias)
+{
+    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6, l16 = lane & 15, kq = lane >> 4;
+    const int i = (blockIdx.x * 4 + wave) * 64 + 4 * l16, j0 = blockIdx.y * 16;
+    const rsrc_t xr = make_rsrc(X, (int64_t)B * In * 4), yr = make_rsrc(dY, (int64_t)B * Out * 4);
+    f32x4 acc[4], ab = (f32x4){0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+    for (int t = 0; t < 4; ++t) acc[t] = ab;
+    const bool first = blockIdx.x == 0 && wave == 0 && dbias;
+    constexpr int U = 8;                                 // loads of 32 samples before their use
+    for (int b0 = 0; b0 < B; b0 += 4 * U) {
+        u32x4 x[U];
+        float y[U];
+#pragma unroll
+        for (int u = 0; u < U; ++u) {
+            const int b = b0 + 4 * u + kq;
+            y[u] = buf_f32(yr, b < B && j0 + l16 < Out ? 4u * ((uint32_t)b * Out + j0 + l16) : kOut);
+            x[u] = __builtin_bit_cast(u32x4, __builtin_amdgcn_raw_buffer_load_b128(
+                xr, b < B && i < In ? 4u * ((uint32_t)b * In + i) : kOut, 0, 0));
+        }
+#pragma unroll
+        for (int u = 0; u < U; ++u) {
+#pragma unroll
+            for (int t = 0; t < 4; ++t)
+                acc[t] = __builtin_amdgcn_mfma_f32_16x16x4f32(y[u], __uint_as_float(x[u][t]), acc[t], 0, 0, 0);
+            if (first) ab = __builtin_amdgcn_mfma_f32_16x16x4f32(y[u], 1.f, ab, 0, 0, 0);
+        }
+    }
+#pragma unroll
+    for (int r = 0; r < 4; ++r) {
+        const int j = j0 + 4 * kq + r;
+        if (j >= Out) continue;
+        if (i < In)
+            *reinterpret_cast<f32x4_u *>(dW + (int64_t)j * In + i) =
+                (f32x4_u){acc[0][r], acc[1][r], acc[2][r], acc[3][r]};
+        if (first && l16 == 0) dbias[j] = ab[r];
+    }
+}
+
+template <class WT, bool KN>
+hipError_t linear_small_launch(const LinArgs &a, const WT *Wt, hipStream_t s)
+{
+    const unsigned my = (unsigned)((a.M + 15) / 16);
+    // Four column tiles per wave where that still gives 128 pairs (the weights' rows are read in
+    // wider pieces), one otherwise.
+    if (KN && (int64_t)my * ((a.N + 63) / 64) >= 128)
+        hipLaunchKernelGGL((linear_small_kernel<WT, KN, KN ? 4 : 1>), dim3((unsigned)((a.N + 63) / 64), my),
+                           dim3(128), 0, s, a, Wt);
+    else
+        hipLaunchKernelGGL((linear_small_kernel<WT, KN, 1>), dim3((unsigned)((a.N + 15) / 16), my),
+                           dim3(128), 0, s, a, Wt);
+    return hipGetLastError();
+}
+
+}  // namespace
+
+bool linear_small_ok(int M, int N, int K)
+{
+    // 31-bit byte offsets; up to 1,024 pairs of waves, beyond which the 64 x 64 tiles' reuse wins.
+    return (int64_t)((M + 15) / 16) * ((N + 15) / 16) <= 1024 && (int64_t)M * K * 4 < ((int64_t)1 << 31) &&
+           (int64_t)N * K * 4 < ((int64_t)1 << 31);
+}
+
+hipError_t launch_linear_small(bool bf16w, bool kn, int M, int N, int K, const float *A, const void *Wt,
+                               const float *bias, int relu, float *C, hipStream_t s)
+{
+    const LinArgs a = {M, N, K, relu, A, bias, C};
+    if (bf16w)
+        return kn ? linear_small_launch<uint16_t, true>(a, (const uint16_t *)Wt, s)
+                  : linear_small_launch<uint16_t, false>(a, (const uint16_t *)Wt, s);
+    return kn ? linear_small_launch<float, true>(a, (const float *)Wt, s)
+              : linear_small_launch<float, false>(a, (const float *)Wt, s);
+}
+
+bool linear_wgrad_ok(int B, int In, int Out)
+{
+    return In % 4 == 0 && (int64_t)B * std::max(In, Out) * 4 < ((int64_t)1 << 31);
+}
+
+hipError_t launch_linear_wgrad(int B, int In, int Out, const float *X, const float *dY, float *dW,
+                               float *dbias, hipStream_t s)
+{
+    hipLaunchKernelGGL(linear_wgrad_kernel, dim3((unsigned)((In + 255) / 256), (unsigned)((Out + 15) / 16)),
+                       dim3(256), 0, s, B, In, Out, X, dY, dW, dbias);
+    return hipGetLastError();
+}
+
 }  // namespace tdb

@@ -145,3 +145,34 @@ def test_conv_forward(shape):
                 yr = E.conv(fine.double(), wc.double(), None if bias is None else bias.double(), relu)
                 ok, worst = _within(y, yr, S, 27 * Ci)
                 assert ok, (shape, wc.dtype, relu, worst)
+
+
+# (B, In, Out): tiles of 16 rows and 16 or 64 columns with a rest, terms that end inside a chunk of
+# 64, one chunk, several chunks in flight and past them; In not a multiple of 4 (the direct loop).
+LINEAR = [(32, 512, 640), (7, 68, 36), (17, 1028, 20), (1, 4, 4), (33, 64, 2116), (5, 4096, 16), (3, 30, 8)]
+
+
+@pytest.mark.parametrize("shape", LINEAR)
+def test_linear_small_batch(shape):
+    """Forward and all gradients; the split head with one slice gives the same bits."""
+    need_gpu()
+    from paper_2205_04550_amd import nn
+    B, In, Out = shape
+    g = torch.Generator().manual_seed(B + In + Out + 3)
+    x, w = torch.randn(B, In, generator=g), torch.randn(Out, In, generator=g) * 0.1
+    b, gy = torch.randn(Out, generator=g), torch.randn(B, Out, generator=g)
+    for wc in (w.to(torch.bfloat16), w):
+        say(f"linear {shape} {wc.dtype}")
+        xd, wd, bd = x.cuda().requires_grad_(), w.cuda().requires_grad_(), b.cuda().requires_grad_()
+        y = nn.Linear.apply(xd, wd, bd, wc.cuda(), False)
+        if wc.dtype == torch.bfloat16 and In % 4 == 0:
+            assert torch.equal(y, nn.linear_split(x.cuda(), wc.cuda(), b.cuda(), False, splits=1))
+        gx, gw, gb = torch.autograd.grad(y, (xd, wd, bd), gy.cuda())
+        x64, w64, g64 = x.double(), wc.double(), gy.double()
+        for name, got, want, S, K in (
+                ("y", y, x64 @ w64.T + b.double(), x64.abs() @ w64.abs().T + b.double().abs(), In),
+                ("dx", gx, g64 @ w64, g64.abs() @ w64.abs(), Out),
+                ("dw", gw, g64.T @ x64, g64.abs().T @ x64.abs(), B),
+                ("db", gb, g64.sum(0), g64.abs().sum(0), B)):
+            ok, worst = _within(got, want, S, K)
+            assert ok, (shape, name, worst)
