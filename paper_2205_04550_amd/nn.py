@@ -43,6 +43,7 @@ _SIGS = {
     "nn_mse_fwd": (_i32, [_i32, _i64, _vp, _vp, _vp, _vp, _sz, _vp]),
     "nn_mse_bwd": (_i32, [_i32, _i64, _vp, _vp, _vp, _vp, _vp]),
     "nn_adam_step": (_i32, [_i64, _vp, _vp, _vp, _vp, _vp, _f32, _f32, _f32, _f32, _i32, _vp]),
+    "nn_adam_step_multi": (_i32, [_i32] + [_vp] * 6 + [_f32, _f32, _f32, _f32, _i32, _vp]),
     "nn_to_bf16": (_i32, [_i64, _vp, _vp, _vp]),
     "nn_bihalf_fwd": (_i32, [_i32, _i32, _i32, _vp, _vp, _vp]),
     "nn_meanpool_db_mask": (_i32, [_vp, _vp, _i32, _i32, _vp, _i32, _vp]),
@@ -788,14 +789,21 @@ class Adam:
 
     def step(self) -> None:
         self.t += 1
-        for k, p in self.model.params.items():
-            if p.grad is None:
-                continue
-            wb = self.model.work.get(k) if (self.model.bf16 and k.endswith(".w")) else None
-            _check(LIB.nn_adam_step(p.numel(), p.data_ptr(), self.m[k].data_ptr(), self.v[k].data_ptr(),
-                                    p.grad.data_ptr(), _p(wb), self.lr, self.b1, self.b2, self.eps,
-                                    self.t, _s()))
-            p.grad = None
+        some = [(k, p) for k, p in self.model.params.items() if p.grad is not None]
+        if some:
+            n = len(some)
+            wb = [self.model.work.get(k) if (self.model.bf16 and k.endswith(".w")) else None
+                  for k, _ in some]
+            ptrs = ctypes.c_void_p * n
+            _check(LIB.nn_adam_step_multi(
+                n, (ctypes.c_int64 * n)(*(p.numel() for _, p in some)),
+                ptrs(*(p.data_ptr() for _, p in some)),
+                ptrs(*(self.m[k].data_ptr() for k, _ in some)),
+                ptrs(*(self.v[k].data_ptr() for k, _ in some)),
+                ptrs(*(p.grad.data_ptr() for _, p in some)), ptrs(*(_p(t) for t in wb)),
+                self.lr, self.b1, self.b2, self.eps, self.t, _s()))
+            for _, p in some:
+                p.grad = None
         self.model.work_version += 1
 
 

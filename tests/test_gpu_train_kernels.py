@@ -176,3 +176,35 @@ def test_linear_small_batch(shape):
                 ("db", gb, g64.sum(0), g64.abs().sum(0), B)):
             ok, worst = _within(got, want, S, K)
             assert ok, (shape, name, worst)
+
+
+def test_adam_of_several_tensors_equals_one_by_one():
+    """One launch for 37 tensors (more than a table holds, sizes around a block of 1,024 and
+    pointers off 16 bytes) leaves the bits of a launch per tensor."""
+    need_gpu()
+    import ctypes
+    from paper_2205_04550_amd.binding import LIB, _check
+    g = torch.Generator().manual_seed(3)
+    sizes = [1, 3, 4, 1023, 1024, 1025, 5000] + [17 + 64 * i for i in range(30)]
+    st = torch.cuda.current_stream().cuda_stream
+
+    def tensors():
+        g.manual_seed(3)
+        out = []
+        for i, n in enumerate(sizes):
+            t = [torch.randn(n + 1, generator=g).cuda()[i % 2:][:n] for _ in range(4)]
+            t[2].abs_()
+            out.append(t + [torch.zeros(n, dtype=torch.bfloat16, device="cuda") if i % 3 else None])
+        return out
+
+    one, many = tensors(), tensors()
+    p = lambda t: None if t is None else t.data_ptr()
+    for w, m, v, gr, wb in one:
+        _check(LIB.nn_adam_step(w.numel(), p(w), p(m), p(v), p(gr), p(wb), 1e-3, 0.9, 0.999, 1e-8, 2, st))
+    k = len(sizes)
+    col = lambda i: (ctypes.c_void_p * k)(*(p(t[i]) for t in many))
+    _check(LIB.nn_adam_step_multi(k, (ctypes.c_int64 * k)(*sizes), col(0), col(1), col(2), col(3), col(4),
+                                  1e-3, 0.9, 0.999, 1e-8, 2, st))
+    for a, b in zip(one, many):
+        for x, y in zip(a, b):
+            assert (x is None) == (y is None) and (x is None or torch.equal(x, y))
