@@ -206,6 +206,27 @@ int nn_channel_sum(int dtype, int B, int C, int64_t S, const void *X, void *out,
 /* dX = dY where Y > 0 else 0 (n elements). */
 int nn_relu_bwd(int dtype, int64_t n, const void *Y, const void *dY, void *dX, void *stream);
 
+/* A layer's whole backward pass in one call: the gradient before the ReLU (Y: the forward's
+ * output when it applied one, else NULL), the input gradient dX (unless NULL), dWt and dbias
+ * (or NULL), with the results of the calls above one after another. Arguments as theirs; ws
+ * (device, 256-byte aligned) of the matching _ws_bytes (relu: whether Y is given; the linear
+ * layer needs none without Y). nn_conv3d_t_s2_backward is the transposed convolution's: X
+ * [B][Co][D/2][H/2][W/2], Y and dY [B][Ci][D][H][W], dbias [Ci]. */
+size_t nn_conv3d_s2_backward_ws_bytes(int dtype, int B, int Ci, int Co, int D, int H, int W,
+                                      int relu);
+int nn_conv3d_s2_backward(int dtype, int B, int Ci, int Co, int D, int H, int W, const void *X,
+                          const void *Wt, int wdtype, const void *Y, const void *dY, void *dX,
+                          void *dWt, void *dbias, void *ws, size_t ws_bytes, void *stream);
+size_t nn_conv3d_t_s2_backward_ws_bytes(int dtype, int B, int Ci, int Co, int D, int H, int W,
+                                        int relu);
+int nn_conv3d_t_s2_backward(int dtype, int B, int Ci, int Co, int D, int H, int W, const void *X,
+                            const void *Wt, int wdtype, const void *Y, const void *dY, void *dX,
+                            void *dWt, void *dbias, void *ws, size_t ws_bytes, void *stream);
+size_t nn_linear_backward_ws_bytes(int dtype, int B, int Out, int relu);
+int nn_linear_backward(int dtype, int B, int In, int Out, const void *X, const void *Wt, int wdtype,
+                       const void *Y, const void *dY, void *dX, void *dWt, void *dbias, void *ws,
+                       size_t ws_bytes, void *stream);
+
 /* loss[0] = mean((A - B)^2) over n elements (deterministic; ws of
  * nn_mse_ws_bytes(n) bytes). */
 size_t nn_mse_ws_bytes(int dtype, int64_t n);

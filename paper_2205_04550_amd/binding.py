@@ -110,9 +110,11 @@ def _ptr(t) -> int | None:
     return None if t is None else t.data_ptr()
 
 
-def _stream(stream) -> int:
+def _stream(stream=None) -> int:
+    """The handle of `stream`, or of the current device's current stream (read directly: a
+    torch.cuda.Stream object per call costs several microseconds of a small call)."""
     if stream is None:
-        stream = torch.cuda.current_stream()
+        return torch._C._cuda_getCurrentRawStream(torch._C._cuda_getDevice())
     return stream.cuda_stream
 
 

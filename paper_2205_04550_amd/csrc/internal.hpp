@@ -198,10 +198,12 @@ hipError_t launch_rerank_rank(const db_t *db, int nq, const uint32_t *acnt, int 
 
 // Training kernels (train.hip), float activations.
 // Weight gradient dW [Co][Ci][27] and, unless NULL, dbias [Co], through ws (float [chunks of
-// 4,096 positions][Co][Ci][28]); sizes for which conv_wgrad_ok holds.
+// 4,096 positions][Co][Ci][28]); Y (or NULL): dY counts where Y > 0. Sizes for which
+// conv_wgrad_ok holds.
 bool conv_wgrad_ok(int Ci, int Co, int D, int H, int W);
 hipError_t launch_conv_wgrad(int B, int Ci, int Co, int D, int H, int W, const float *X,
-                             const float *dY, float *dW, float *dbias, float *ws, hipStream_t s);
+                             const float *dY, const float *Y, float *dW, float *dbias, float *ws,
+                             hipStream_t s);
 // Adjoint map dX = conv^T(dY) + bias, sizes for which conv_adjoint_ok holds.
 bool conv_adjoint_ok(int B, int Ci, int Co, int D, int H, int W);
 hipError_t launch_conv_adjoint(bool bf16w, int B, int Ci, int Co, int D, int H, int W,

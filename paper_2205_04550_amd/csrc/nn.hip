@@ -530,9 +530,12 @@ constexpr int kCsChunk = 16384;
 
 // Every 256th position per thread; eight loads before their adds (one at a time, with a division
 // each, the pass took 25 us for 8 M values; now it is bound by the read).
-template <class T>
+// RELU: X counts where Y > 0 (the gradient before a ReLU) and is written to G as it is summed.
+template <class T, bool RELU>
 __global__ void __launch_bounds__(256) channel_sum_partial(int B, int C, int64_t S,
                                                            const T *__restrict__ X,
+                                                           const T *__restrict__ Y,
+                                                           T *__restrict__ G,
                                                            T *__restrict__ partial)
 {
     __shared__ T red[4];
@@ -544,11 +547,13 @@ __global__ void __launch_bounds__(256) channel_sum_partial(int B, int C, int64_t
     T acc = T(0);
     constexpr int U = 8;
     for (int i = threadIdx.x; i < n; i += 256 * U) {
-        T v[U];
+        T v[U], m[U];
+        int64_t at[U];
 #pragma unroll
         for (int u = 0; u < U; ++u) {
-            const T t = X[i + 256 * u < n ? (b * C + c) * S + sidx : (int64_t)c * S];
-            v[u] = i + 256 * u < n ? t : T(0);
+            at[u] = i + 256 * u < n ? (b * C + c) * S + sidx : (int64_t)c * S;
+            v[u] = X[at[u]];
+            if (RELU) m[u] = Y[at[u]];
             sidx += 256;
             while (sidx >= S) {
                 sidx -= S;
@@ -556,7 +561,12 @@ __global__ void __launch_bounds__(256) channel_sum_partial(int B, int C, int64_t
             }
         }
 #pragma unroll
-        for (int u = 0; u < U; ++u) acc += v[u];
+        for (int u = 0; u < U; ++u) {
+            const bool in = i + 256 * u < n;
+            if (RELU && !(m[u] > T(0))) v[u] = T(0);
+            if (RELU && in) G[at[u]] = v[u];
+            acc += in ? v[u] : T(0);
+        }
     }
     acc = wsum(acc);
     if ((threadIdx.x & 63) == 0) red[threadIdx.x >> 6] = acc;
@@ -2572,7 +2582,7 @@ int nn_conv3d_s2_bwd_weight(int dtype, int B, int Ci, int Co, int D, int H, int 
     const dim3 g1f(chunks, Ci, (Co + kWgCB - 1) / kWgCB);
     const unsigned g2 = (unsigned)((Co * Ci * 28 + 255) / 256);
     if (dtype == NN_F32 && conv_wgrad_ok(Ci, Co, D, H, W)) {
-        (void)launch_conv_wgrad(B, Ci, Co, D, H, W, (const float *)X, (const float *)dY,
+        (void)launch_conv_wgrad(B, Ci, Co, D, H, W, (const float *)X, (const float *)dY, nullptr,
                                 (float *)dWt, (float *)dbias, (float *)ws, s);
     } else if (dtype == NN_F32) {   // samples of 2 GiB and more
         hipLaunchKernelGGL((conv_bwd_weight_partial<float, kWgCB>), g1f, dim3(256), 0, s, B, Ci, Co,
@@ -2724,13 +2734,13 @@ int nn_channel_sum(int dtype, int B, int C, int64_t S, const void *X, void *out,
     const hipStream_t s = static_cast<hipStream_t>(stream);
     const int chunks = (int)(((int64_t)B * S + kCsChunk - 1) / kCsChunk);
     if (dtype == NN_F32) {
-        hipLaunchKernelGGL(channel_sum_partial<float>, dim3(chunks, C), dim3(256), 0, s, B, C, S,
-                           (const float *)X, (float *)ws);
+        hipLaunchKernelGGL((channel_sum_partial<float, false>), dim3(chunks, C), dim3(256), 0, s, B,
+                           C, S, (const float *)X, nullptr, nullptr, (float *)ws);
         hipLaunchKernelGGL(channel_sum_final<float>, dim3(C), dim3(256), 0, s, chunks,
                            (const float *)ws, (float *)out);
     } else {
-        hipLaunchKernelGGL(channel_sum_partial<double>, dim3(chunks, C), dim3(256), 0, s, B, C, S,
-                           (const double *)X, (double *)ws);
+        hipLaunchKernelGGL((channel_sum_partial<double, false>), dim3(chunks, C), dim3(256), 0, s, B,
+                           C, S, (const double *)X, nullptr, nullptr, (double *)ws);
         hipLaunchKernelGGL(channel_sum_final<double>, dim3(C), dim3(256), 0, s, chunks,
                            (const double *)ws, (double *)out);
     }
@@ -2749,6 +2759,122 @@ int nn_relu_bwd(int dtype, int64_t n, const void *Y, const void *dY, void *dX, v
         hipLaunchKernelGGL(relu_bwd_kernel<double>, dim3(grid1(n)), dim3(256), 0, s, n,
                            (const double *)Y, (const double *)dY, (double *)dX);
     return launched("nn_relu_bwd");
+}
+
+// ---- whole layers' backward passes --------------------------------------------------------------
+
+static size_t up256(size_t n) { return (n + 255) / 256 * 256; }
+static size_t elem_bytes(int dtype) { return dtype == NN_F32 ? 4 : 8; }
+
+size_t nn_conv3d_s2_backward_ws_bytes(int dtype, int B, int Ci, int Co, int D, int H, int W,
+                                      int relu)
+{
+    const size_t wg = nn_conv3d_s2_bwd_weight_ws_bytes(dtype, B, Ci, Co, D, H, W);
+    if (!wg) return 0;
+    const size_t n = (size_t)B * Co * (D / 2) * (H / 2) * (W / 2);
+    return up256(wg) + (relu ? up256(n * elem_bytes(dtype)) : 0);
+}
+
+int nn_conv3d_s2_backward(int dtype, int B, int Ci, int Co, int D, int H, int W, const void *X,
+                          const void *Wt, int wdtype, const void *Y, const void *dY, void *dX,
+                          void *dWt, void *dbias, void *ws, size_t ws_bytes, void *stream)
+{
+    const size_t need = nn_conv3d_s2_backward_ws_bytes(dtype, B, Ci, Co, D, H, W, Y != nullptr);
+    if (need == 0 || dtype_pair(dtype, wdtype) < 0 || !X || !Wt || !dY || !dWt || !ws)
+        return tdb_set_error(DB_EINVAL, "nn_conv3d_s2_backward: bad arguments");
+    if (ws_bytes < need)
+        return tdb_set_error(DB_ENOSPC, "nn_conv3d_s2_backward: workspace %zu < %zu", ws_bytes, need);
+    if (Y && !dX && dtype == NN_F32 && conv_wgrad_ok(Ci, Co, D, H, W)) {
+        // Only the weight gradient reads the gradient before the ReLU: masked as it is read.
+        (void)launch_conv_wgrad(B, Ci, Co, D, H, W, (const float *)X, (const float *)dY,
+                                (const float *)Y, (float *)dWt, (float *)dbias, (float *)ws,
+                                static_cast<hipStream_t>(stream));
+        return launched("nn_conv3d_s2_backward");
+    }
+    const size_t wg = up256(nn_conv3d_s2_bwd_weight_ws_bytes(dtype, B, Ci, Co, D, H, W));
+    const void *g = dY;
+    int e = DB_OK;
+    if (Y) {
+        void *gb = static_cast<char *>(ws) + wg;
+        e = nn_relu_bwd(dtype, (int64_t)B * Co * (D / 2) * (H / 2) * (W / 2), Y, dY, gb, stream);
+        g = gb;
+    }
+    if (!e && dX)
+        e = nn_conv3d_s2_bwd_data(dtype, B, Ci, Co, D, H, W, g, Wt, wdtype, nullptr, 0, dX, stream);
+    return e ? e : nn_conv3d_s2_bwd_weight(dtype, B, Ci, Co, D, H, W, X, g, dWt, dbias, ws, wg, stream);
+}
+
+size_t nn_conv3d_t_s2_backward_ws_bytes(int dtype, int B, int Ci, int Co, int D, int H, int W,
+                                        int relu)
+{
+    const size_t wg = nn_conv3d_s2_bwd_weight_ws_bytes(dtype, B, Ci, Co, D, H, W);
+    if (!wg) return 0;
+    const size_t S = (size_t)D * H * W;
+    return up256(wg) + up256(nn_channel_sum_ws_bytes(dtype, B, Ci, (int64_t)S)) +
+           (relu ? up256((size_t)B * Ci * S * elem_bytes(dtype)) : 0);
+}
+
+int nn_conv3d_t_s2_backward(int dtype, int B, int Ci, int Co, int D, int H, int W, const void *X,
+                            const void *Wt, int wdtype, const void *Y, const void *dY, void *dX,
+                            void *dWt, void *dbias, void *ws, size_t ws_bytes, void *stream)
+{
+    const size_t need = nn_conv3d_t_s2_backward_ws_bytes(dtype, B, Ci, Co, D, H, W, Y != nullptr);
+    if (need == 0 || dtype_pair(dtype, wdtype) < 0 || !X || !Wt || !dY || !dWt || !ws)
+        return tdb_set_error(DB_EINVAL, "nn_conv3d_t_s2_backward: bad arguments");
+    if (ws_bytes < need)
+        return tdb_set_error(DB_ENOSPC, "nn_conv3d_t_s2_backward: workspace %zu < %zu", ws_bytes, need);
+    const int64_t S = (int64_t)D * H * W;
+    const size_t wg = up256(nn_conv3d_s2_bwd_weight_ws_bytes(dtype, B, Ci, Co, D, H, W));
+    const size_t csn = nn_channel_sum_ws_bytes(dtype, B, Ci, S), cs = up256(csn);
+    char *csw = static_cast<char *>(ws) + wg;
+    const void *g = dY;
+    int e = DB_OK;
+    if (Y && dbias && dtype == NN_F32) {                 // the ReLU and the bias sums in one pass
+        const int chunks = (int)(((int64_t)B * S + kCsChunk - 1) / kCsChunk);
+        const hipStream_t s = static_cast<hipStream_t>(stream);
+        float *gb = reinterpret_cast<float *>(csw + cs);
+        hipLaunchKernelGGL((channel_sum_partial<float, true>), dim3(chunks, Ci), dim3(256), 0, s, B,
+                           Ci, S, (const float *)dY, (const float *)Y, gb, (float *)csw);
+        hipLaunchKernelGGL(channel_sum_final<float>, dim3(Ci), dim3(256), 0, s, chunks,
+                           (const float *)csw, (float *)dbias);
+        e = launched("nn_conv3d_t_s2_backward");
+        g = gb;
+    } else {
+        if (Y) {
+            e = nn_relu_bwd(dtype, (int64_t)B * Ci * S, Y, dY, csw + cs, stream);
+            g = csw + cs;
+        }
+        if (!e && dbias) e = nn_channel_sum(dtype, B, Ci, S, g, dbias, csw, cs, stream);
+    }
+    if (!e && dX)
+        e = nn_conv3d_s2_fwd(dtype, B, Ci, Co, D, H, W, g, Wt, wdtype, nullptr, 0, dX, stream);
+    return e ? e : nn_conv3d_s2_bwd_weight(dtype, B, Ci, Co, D, H, W, g, X, dWt, nullptr, ws, wg, stream);
+}
+
+size_t nn_linear_backward_ws_bytes(int dtype, int B, int Out, int relu)
+{
+    if ((dtype != NN_F32 && dtype != NN_F64) || B <= 0 || Out <= 0) return 0;
+    return relu ? up256((size_t)B * Out * elem_bytes(dtype)) : 1;
+}
+
+int nn_linear_backward(int dtype, int B, int In, int Out, const void *X, const void *Wt, int wdtype,
+                       const void *Y, const void *dY, void *dX, void *dWt, void *dbias, void *ws,
+                       size_t ws_bytes, void *stream)
+{
+    const size_t need = nn_linear_backward_ws_bytes(dtype, B, Out, Y != nullptr);
+    if (need == 0 || dtype_pair(dtype, wdtype) < 0 || B > 65535 || In <= 0 || Out > 65535 || !X ||
+        !Wt || !dY || !dWt || (Y && !ws))
+        return tdb_set_error(DB_EINVAL, "nn_linear_backward: bad arguments");
+    if (Y && ws_bytes < need)
+        return tdb_set_error(DB_ENOSPC, "nn_linear_backward: workspace %zu < %zu", ws_bytes, need);
+    const void *g = dY;
+    int e = DB_OK;
+    if (Y) {
+        e = nn_relu_bwd(dtype, (int64_t)B * Out, Y, dY, ws, stream);
+        g = ws;
+    }
+    if (!e && dX) e = nn_linear_bwd_data(dtype, B, In, Out, g, Wt, wdtype, dX, stream);
+    return e ? e : nn_linear_bwd_weight(dtype, B, In, Out, X, g, dWt, dbias, stream);
 }
 
 size_t nn_mse_ws_bytes(int dtype, int64_t n)

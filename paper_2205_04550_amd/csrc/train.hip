@@ -131,7 +131,8 @@ __device__ __forceinline__ void advance(int &b, int &z, int &y, int &x, const St
 // dW[co][ci][tap] = sum over (sample, coarse voxel o) of dY[co][o] X[ci][2 o + tap - 1]. Grid
 // (chunks of kWgChunkF positions, Ci, ceil(Co / CB)); a thread takes every 256th position of
 // the chunk, CB coarse channels and all 27 taps (and the sum of dY, tap 27), 28 CB sums in
-// registers. Per position the fine values come as nine pairs (x = 2 ow, 2 ow + 1) by buffer
+// registers. MASK: dY counts only where Y > 0 (the layer's ReLU), so that the gradient before the
+// ReLU need not be written where only this kernel reads it. Per position the fine values come as nine pairs (x = 2 ow, 2 ow + 1) by buffer
 // loads, whose out-of-range answer 0 is the padding; the left column (2 ow - 1) is the second
 // value of the lane before (SHIFT: rows of 64 / n voxels, so that a wave starts a row) or a
 // load of its own. Positions advance by 256 in mixed radix: no division in the loop, and a
@@ -147,11 +148,12 @@ constexpr int kWgCBF = 4;
 
 
 
-template <bool SHIFT>
+template <bool SHIFT, bool MASK>
 __global__ void __launch_bounds__(256, 3) conv_wgrad_kernel(int B, int Ci, int Co, int D, int H,
                                                             int W, Step st,
                                                             const float *__restrict__ X,
                                                             const float *__restrict__ dY,
+                                                            const float *__restrict__ Y,
                                                             float *__restrict__ partial)
 {
     constexpr int CB = kWgCBF, NV = CB * 28, NR = (NV + 63) / 64;
@@ -165,6 +167,7 @@ __global__ void __launch_bounds__(256, 3) conv_wgrad_kernel(int B, int Ci, int C
     // Buffers from this chunk's first sample on; the host checks that its samples stay below 2 GiB.
     const rsrc_t xr = make_rsrc(X + (b0 * Ci + ci) * isp, ((B - b0) * Ci - ci) * isp * 4);
     const rsrc_t yr = make_rsrc(dY + (b0 * Co + co0) * osp, ((B - b0) * Co - co0) * osp * 4);
+    const rsrc_t mr = make_rsrc((MASK ? Y : dY) + (b0 * Co + co0) * osp, ((B - b0) * Co - co0) * osp * 4);
     int o = (int)(p0 - b0 * osp) + tid;
     int x = o % OW, y = (o / OW) % OH, z = o / (OW * OH), b = z / OD;
     z -= b * OD;
@@ -182,6 +185,10 @@ __global__ void __launch_bounds__(256, 3) conv_wgrad_kernel(int B, int Ci, int C
 #pragma unroll
         for (int c = 0; c < CB; ++c)                     // a channel past the last is not stored
             g[c] = buf_f32(yr, yo, 4u * (uint32_t)min(c, Co - 1 - co0) * (uint32_t)osp);
+        float mk[CB];
+#pragma unroll
+        for (int c = 0; MASK && c < CB; ++c)
+            mk[c] = buf_f32(mr, yo, 4u * (uint32_t)min(c, Co - 1 - co0) * (uint32_t)osp);
         float2 p[9];                                     // all loads before their first use
         float l[9];
 #pragma unroll
@@ -205,6 +212,8 @@ __global__ void __launch_bounds__(256, 3) conv_wgrad_kernel(int B, int Ci, int C
             v[r][1] = p[r].x;
             v[r][2] = p[r].y;
         }
+#pragma unroll
+        for (int c = 0; MASK && c < CB; ++c) g[c] = mk[c] > 0.f ? g[c] : 0.f;
 #pragma unroll
         for (int c = 0; c < CB; ++c) {
 #pragma unroll
@@ -267,19 +276,23 @@ bool conv_wgrad_ok(int Ci, int Co, int D, int H, int W)
 }
 
 hipError_t launch_conv_wgrad(int B, int Ci, int Co, int D, int H, int W, const float *X,
-                             const float *dY, float *dW, float *dbias, float *ws, hipStream_t s)
+                             const float *dY, const float *Y, float *dW, float *dbias, float *ws,
+                             hipStream_t s)
 {
     const int OD = D / 2, OH = H / 2, OW = W / 2;
     const int64_t P = (int64_t)B * OD * OH * OW;
     const int chunks = (int)((P + kWgChunkF - 1) / kWgChunkF);
     const Step st = step_of(256, OD, OH, OW);
     const dim3 grid((unsigned)chunks, (unsigned)Ci, (unsigned)((Co + kWgCBF - 1) / kWgCBF));
-    if (64 % OW == 0)
-        hipLaunchKernelGGL((conv_wgrad_kernel<true>), grid, dim3(256), 0, s, B, Ci, Co, D, H, W, st,
-                           X, dY, ws);
-    else
-        hipLaunchKernelGGL((conv_wgrad_kernel<false>), grid, dim3(256), 0, s, B, Ci, Co, D, H, W, st,
-                           X, dY, ws);
+#define TDB_WGRAD(SHIFT_, MASK_)                                                                   \
+    hipLaunchKernelGGL((conv_wgrad_kernel<SHIFT_, MASK_>), grid, dim3(256), 0, s, B, Ci, Co, D, H, W, \
+                       st, X, dY, Y, ws)
+    if (64 % OW == 0) {
+        if (Y) TDB_WGRAD(true, true); else TDB_WGRAD(true, false);
+    } else {
+        if (Y) TDB_WGRAD(false, true); else TDB_WGRAD(false, false);
+    }
+#undef TDB_WGRAD
     const int64_t N = (int64_t)Co * Ci * 28;
     hipLaunchKernelGGL(conv_wgrad_final_kernel, dim3((unsigned)((N + 31) / 32)), dim3(512), 0, s,
                        chunks, Ci, N, (const float *)ws, dW, dbias);

@@ -21,7 +21,7 @@ import math
 
 import torch
 
-from .binding import LIB, _check
+from .binding import LIB, _check, _stream as _s
 
 NN_F32, NN_F64, NN_BF16 = 0, 1, 2
 
@@ -39,6 +39,12 @@ _SIGS = {
     "nn_channel_sum_ws_bytes": (_sz, [_i32, _i32, _i32, _i64]),
     "nn_channel_sum": (_i32, [_i32, _i32, _i32, _i64, _vp, _vp, _vp, _sz, _vp]),
     "nn_relu_bwd": (_i32, [_i32, _i64, _vp, _vp, _vp, _vp]),
+    "nn_conv3d_s2_backward_ws_bytes": (_sz, [_i32] * 8),
+    "nn_conv3d_s2_backward": (_i32, [_i32] * 7 + [_vp, _vp, _i32] + [_vp] * 6 + [_sz, _vp]),
+    "nn_conv3d_t_s2_backward_ws_bytes": (_sz, [_i32] * 8),
+    "nn_conv3d_t_s2_backward": (_i32, [_i32] * 7 + [_vp, _vp, _i32] + [_vp] * 6 + [_sz, _vp]),
+    "nn_linear_backward_ws_bytes": (_sz, [_i32] * 4),
+    "nn_linear_backward": (_i32, [_i32] * 4 + [_vp, _vp, _i32] + [_vp] * 6 + [_sz, _vp]),
     "nn_mse_ws_bytes": (_sz, [_i32, _i64]),
     "nn_mse_fwd": (_i32, [_i32, _i64, _vp, _vp, _vp, _vp, _sz, _vp]),
     "nn_mse_bwd": (_i32, [_i32, _i64, _vp, _vp, _vp, _vp, _vp]),
@@ -77,10 +83,6 @@ for _n, (_r, _a) in _SIGS.items():
 NN_SYMBOLS = tuple(_SIGS)
 
 
-def _s() -> int:
-    return torch.cuda.current_stream().cuda_stream
-
-
 def _dt(t: torch.Tensor) -> int:
     if t.dtype == torch.float32:
         return NN_F32
@@ -89,8 +91,11 @@ def _dt(t: torch.Tensor) -> int:
     raise TypeError(f"activations must be float32 or float64, got {t.dtype}")
 
 
+_WDT = {torch.bfloat16: NN_BF16, torch.float32: NN_F32, torch.float64: NN_F64}
+
+
 def _wdt(w: torch.Tensor) -> int:
-    return {torch.bfloat16: NN_BF16, torch.float32: NN_F32, torch.float64: NN_F64}[w.dtype]
+    return _WDT[w.dtype]
 
 
 def _p(t):
@@ -345,22 +350,15 @@ class Conv3dS2(torch.autograd.Function):
         B, Ci, D, H, W = x.shape
         Co = wc.shape[0]
         gy = _c(gy)
-        if ctx.relu:
-            g = torch.empty_like(gy)
-            _check(LIB.nn_relu_bwd(_dt(gy), gy.numel(), y.data_ptr(), gy.data_ptr(), g.data_ptr(), _s()))
-        else:
-            g = gy
-        dx = None
-        if ctx.needs_input_grad[0]:
-            dx = torch.empty_like(x)
-            _check(LIB.nn_conv3d_s2_bwd_data(_dt(x), B, Ci, Co, D, H, W, g.data_ptr(), wc.data_ptr(),
-                                             _wdt(wc), None, 0, dx.data_ptr(), _s()))
+        dx = torch.empty_like(x) if ctx.needs_input_grad[0] else None
         dw = torch.empty((Co, Ci, 3, 3, 3), dtype=x.dtype, device=x.device)
         db_ = torch.empty(Co, dtype=x.dtype, device=x.device) if ctx.has_bias else None
-        nb = LIB.nn_conv3d_s2_bwd_weight_ws_bytes(_dt(x), B, Ci, Co, D, H, W)
+        nb = LIB.nn_conv3d_s2_backward_ws_bytes(_dt(x), B, Ci, Co, D, H, W, ctx.relu)
         ws = torch.empty(nb, dtype=torch.uint8, device=x.device)
-        _check(LIB.nn_conv3d_s2_bwd_weight(_dt(x), B, Ci, Co, D, H, W, x.data_ptr(), g.data_ptr(),
-                                           dw.data_ptr(), _p(db_), ws.data_ptr(), nb, _s()))
+        _check(LIB.nn_conv3d_s2_backward(_dt(x), B, Ci, Co, D, H, W, x.data_ptr(), wc.data_ptr(),
+                                         _wdt(wc), y.data_ptr() if ctx.relu else None,
+                                         gy.data_ptr(), _p(dx), dw.data_ptr(), _p(db_),
+                                         ws.data_ptr(), nb, _s()))
         return dx, dw, db_, None, None
 
 
@@ -394,28 +392,15 @@ class ConvT3dS2(torch.autograd.Function):
         Cout = wc.shape[1]
         D, H, W = 2 * d, 2 * h, 2 * wd
         gy = _c(gy)
-        if ctx.relu:
-            g = torch.empty_like(gy)
-            _check(LIB.nn_relu_bwd(_dt(gy), gy.numel(), y.data_ptr(), gy.data_ptr(), g.data_ptr(), _s()))
-        else:
-            g = gy
-        dx = None
-        if ctx.needs_input_grad[0]:
-            dx = torch.empty_like(x)
-            _check(LIB.nn_conv3d_s2_fwd(_dt(x), B, Cout, Cin, D, H, W, g.data_ptr(), wc.data_ptr(),
-                                        _wdt(wc), None, 0, dx.data_ptr(), _s()))
+        dx = torch.empty_like(x) if ctx.needs_input_grad[0] else None
         dw = torch.empty((Cin, Cout, 3, 3, 3), dtype=x.dtype, device=x.device)
-        nb = LIB.nn_conv3d_s2_bwd_weight_ws_bytes(_dt(x), B, Cout, Cin, D, H, W)
+        db_ = torch.empty(Cout, dtype=x.dtype, device=x.device) if ctx.has_bias else None
+        nb = LIB.nn_conv3d_t_s2_backward_ws_bytes(_dt(x), B, Cout, Cin, D, H, W, ctx.relu)
         ws = torch.empty(nb, dtype=torch.uint8, device=x.device)
-        _check(LIB.nn_conv3d_s2_bwd_weight(_dt(x), B, Cout, Cin, D, H, W, g.data_ptr(), x.data_ptr(),
-                                           dw.data_ptr(), None, ws.data_ptr(), nb, _s()))
-        db_ = None
-        if ctx.has_bias:
-            db_ = torch.empty(Cout, dtype=x.dtype, device=x.device)
-            nbs = LIB.nn_channel_sum_ws_bytes(_dt(x), B, Cout, D * H * W)
-            wss = torch.empty(nbs, dtype=torch.uint8, device=x.device)
-            _check(LIB.nn_channel_sum(_dt(x), B, Cout, D * H * W, g.data_ptr(), db_.data_ptr(),
-                                      wss.data_ptr(), nbs, _s()))
+        _check(LIB.nn_conv3d_t_s2_backward(_dt(x), B, Cout, Cin, D, H, W, x.data_ptr(),
+                                           wc.data_ptr(), _wdt(wc),
+                                           y.data_ptr() if ctx.relu else None, gy.data_ptr(),
+                                           _p(dx), dw.data_ptr(), _p(db_), ws.data_ptr(), nb, _s()))
         return dx, dw, db_, None, None
 
 
@@ -441,20 +426,14 @@ class Linear(torch.autograd.Function):
         B, In = x.shape
         Out = wc.shape[0]
         gy = _c(gy)
-        if ctx.relu:
-            g = torch.empty_like(gy)
-            _check(LIB.nn_relu_bwd(_dt(gy), gy.numel(), y.data_ptr(), gy.data_ptr(), g.data_ptr(), _s()))
-        else:
-            g = gy
-        dx = None
-        if ctx.needs_input_grad[0]:
-            dx = torch.empty_like(x)
-            _check(LIB.nn_linear_bwd_data(_dt(x), B, In, Out, g.data_ptr(), wc.data_ptr(), _wdt(wc),
-                                          dx.data_ptr(), _s()))
+        dx = torch.empty_like(x) if ctx.needs_input_grad[0] else None
         dw = torch.empty((Out, In), dtype=x.dtype, device=x.device)
         db_ = torch.empty(Out, dtype=x.dtype, device=x.device) if ctx.has_bias else None
-        _check(LIB.nn_linear_bwd_weight(_dt(x), B, In, Out, x.data_ptr(), g.data_ptr(), dw.data_ptr(),
-                                        _p(db_), _s()))
+        nb = LIB.nn_linear_backward_ws_bytes(_dt(x), B, Out, ctx.relu)
+        ws = torch.empty(nb, dtype=torch.uint8, device=x.device) if ctx.relu else None
+        _check(LIB.nn_linear_backward(_dt(x), B, In, Out, x.data_ptr(), wc.data_ptr(), _wdt(wc),
+                                      y.data_ptr() if ctx.relu else None, gy.data_ptr(), _p(dx),
+                                      dw.data_ptr(), _p(db_), _p(ws), nb, _s()))
         return dx, dw, db_, None, None
 
 

@@ -208,3 +208,21 @@ def test_adam_of_several_tensors_equals_one_by_one():
     for a, b in zip(one, many):
         for x, y in zip(a, b):
             assert (x is None) == (y is None) and (x is None or torch.equal(x, y))
+
+
+@pytest.mark.parametrize("shape", [(2, 2, 8, 8, 8, 64), (3, 1, 6, 6, 10, 12)])
+def test_first_layer_gradient_masked_as_it_is_read(shape):
+    """A layer whose input needs no gradient masks dY by its ReLU inside the weight gradient:
+    the same bits as with the input gradient (the masked gradient written first)."""
+    need_gpu()
+    from paper_2205_04550_amd import nn
+    B, Ci, Co, D, H, W = shape
+    g = torch.Generator().manual_seed(8)
+    x = torch.randn(B, Ci, D, H, W, generator=g).cuda()
+    w = (torch.randn(Co, Ci, 3, 3, 3, generator=g) * 0.2).cuda().requires_grad_()
+    b = torch.randn(Co, generator=g).cuda().requires_grad_()
+    gy = torch.randn(B, Co, D // 2, H // 2, W // 2, generator=g).cuda()
+    a = torch.autograd.grad(nn.Conv3dS2.apply(x, w, b, w.detach(), True), (w, b), gy)
+    xr = x.clone().requires_grad_()
+    c = torch.autograd.grad(nn.Conv3dS2.apply(xr, w, b, w.detach(), True), (w, b, xr), gy)
+    assert torch.equal(a[0], c[0]) and torch.equal(a[1], c[1])
