@@ -131,6 +131,12 @@ int nn_pool_conv_counts_bf16(const uint8_t *counts, int B, int nx, int ny, int n
 int nn_counts_conv12_bf16(const uint8_t *counts, int B, int nx, int ny, int nz, int mask,
                           const void *Wt1, const float *b1, const void *Wtm2, const float *b2,
                           void *Y, void *stream);
+/* nn_counts_conv12_bf16 from packed masks (planes, sample_words and idx as for
+ * nn_pool_conv_planes_bf16): equal to nn_pool_conv_planes_bf16 followed by
+ * nn_conv3d_s2_fwd_bf16, both with ReLU, bit for bit. B <= 65535. */
+int nn_planes_conv12_bf16(const uint32_t *planes, int64_t sample_words, const int32_t *idx, int B,
+                          int nx, int ny, int nz, int mask, const void *Wt1, const float *b1,
+                          const void *Wtm2, const float *b2, void *Y, void *stream);
 /* The encoder's third and fourth layers in one pass (Sec. 2.3, "Autoencoders"), one block per
  * sample: nn_conv3d_s2_fwd_bf16 with (Ci, Co) = (16, 32), ReLU, bfloat16 output, then with
  * (32, 64), ReLU, float output, bit for bit, the third layer's output kept on chip.

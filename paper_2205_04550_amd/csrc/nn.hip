@@ -1685,9 +1685,42 @@ __device__ __forceinline__ void c12_item(int it, int ns, int &s, int &r, int &p,
     p = halo ? 4 : rem & 3;
 }
 
-template <int CI>
-__global__ void __launch_bounds__(256, 4) counts_conv12_kernel(
-    const uint8_t *__restrict__ C, int nx, int ny, int nz, int mask, int zc, int units,
+// PLANES: instead of the counts, the packed masks of sample idx[b] (or b), as for
+// pool_conv_labels_kernel: 16 counts are one word of each mask in four voxel rows, pooled as
+// they go into the ring. Against the two kernels from packed masks (0.96 + 0.35 ms for 2,048
+// samples of 128^3) one pass takes 0.64 ms: bound by instruction issue, the pooling (about 65
+// vector instructions per 16 counts, a fifth of them twice at the patches' borders) added to
+// the layers' own (0.45 ms from counts). Three blocks per CU: at four the raw words spill
+// (0.66 ms).
+//
+// The counts of 16 pooled x from a word of either mask in each of four rows: two-bit sums per
+// pair of voxels, then nibbles of every second pair summed over the rows; byte x of the result
+// holds both masks' counts as the packing writes them.
+__device__ __forceinline__ u32x4 pool16(const uint32_t (&w)[8])
+{
+    uint32_t qe[2] = {0u, 0u}, qo[2] = {0u, 0u};       // pairs 2 i and 2 i + 1 in nibble i
+#pragma unroll
+    for (int r = 0; r < 4; ++r)
+#pragma unroll
+        for (int m = 0; m < 2; ++m) {
+            const uint32_t v = w[2 * r + m], p = (v & 0x55555555u) + ((v >> 1) & 0x55555555u);
+            qe[m] += p & 0x33333333u;
+            qo[m] += (p >> 2) & 0x33333333u;
+        }
+    const uint32_t lo = 0x0f0f0f0fu;
+    const uint32_t e0 = (qe[0] & lo) | ((qe[1] & lo) << 4), e1 = ((qe[0] >> 4) & lo) | (qe[1] & ~lo);
+    const uint32_t o0 = (qo[0] & lo) | ((qo[1] & lo) << 4), o1 = ((qo[0] >> 4) & lo) | (qo[1] & ~lo);
+    // Byte i of e0, o0, e1, o1 are x = 4 i, 4 i + 1, 4 i + 2, 4 i + 3.
+    const uint32_t a0 = __builtin_amdgcn_perm(o0, e0, 0x05010400u), a1 = __builtin_amdgcn_perm(o1, e1, 0x05010400u);
+    const uint32_t b0 = __builtin_amdgcn_perm(o0, e0, 0x07030602u), b1 = __builtin_amdgcn_perm(o1, e1, 0x07030602u);
+    return (u32x4){__builtin_amdgcn_perm(a1, a0, 0x05040100u), __builtin_amdgcn_perm(a1, a0, 0x07060302u),
+                   __builtin_amdgcn_perm(b1, b0, 0x05040100u), __builtin_amdgcn_perm(b1, b0, 0x07060302u)};
+}
+
+template <int CI, bool PLANES>
+__global__ void __launch_bounds__(256, PLANES ? 3 : 4) counts_conv12_kernel(
+    const uint8_t *__restrict__ C, const uint32_t *__restrict__ planes, int64_t sample_words,
+    const int32_t *__restrict__ idx, int nx, int ny, int nz, int mask, int zc, int units,
     const uint16_t *__restrict__ Wt1, const float *__restrict__ b1,
     const uint16_t *__restrict__ Wtm2, const float *__restrict__ b2, uint16_t *__restrict__ Y)
 {
@@ -1705,7 +1738,19 @@ __global__ void __launch_bounds__(256, 4) counts_conv12_kernel(
     const int b = u / (tx_n * ty_n * zc_n);
     const int X0 = 16 * tx, Y0 = 4 * ty, oz0 = zi * zc;
     const int64_t slice = (int64_t)PY * PX;
-    const uint8_t *Cb = C + (int64_t)b * (nz / 2) * slice + 4 * X0;
+    const uint8_t *Cb = PLANES ? nullptr : C + (int64_t)b * (nz / 2) * slice + 4 * X0;
+    const int nxw = nx / 32;
+    const uint32_t *Pb = PLANES ? planes + (int64_t)(idx ? idx[b] : b) * sample_words + X0 / 4 : nullptr;
+    const int64_t Wp = sample_words / 2;
+    // The eight words of 16 pooled x from word p on (-1: the one before) of pooled row (pz, py).
+    auto words8 = [&](int pz, int py, int p, uint32_t (&w)[8]) {
+        const uint32_t *q = Pb + (int64_t)(2 * pz * ny + 2 * py) * nxw + p;
+#pragma unroll
+        for (int r = 0; r < 4; ++r)
+#pragma unroll
+            for (int m = 0; m < 2; ++m)
+                w[2 * r + m] = CI == 1 && m != mask ? 0u : q[((r >> 1) * ny + (r & 1)) * nxw + m * Wp];
+    };
     const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6, g = lane >> 4, j = lane & 15;
 
     // First layer: this lane's weights and biases (first_layer_setup's layout), and per tap
@@ -1755,12 +1800,22 @@ __global__ void __launch_bounds__(256, 4) counts_conv12_kernel(
         c12_item(tid + 256 * k, 4, s, r, p, halo);
         is[k] = s;
         iy[k] = 4 * Y0 - 3 + r;
-        ig[k] = (int)(s * slice) + iy[k] * PX + (halo ? -4 : 16 * p);
+        ig[k] = PLANES ? (halo ? -1 : p) : (int)(s * slice) + iy[k] * PX + (halo ? -4 : 16 * p);
         il[k] = r * kPlRow + (halo ? 0 : 4 + 16 * p);
         ih[k] = halo;
     }
     u32x4 v[2];
+    uint32_t vw[2][8];
     auto load4 = [&](int pzf) {
+        if constexpr (PLANES) {
+#pragma unroll
+            for (int k = 0; k < 2; ++k) {
+#pragma unroll
+                for (int i = 0; i < 8; ++i) vw[k][i] = 0u;
+                if (tid + 256 * k < nit && iy[k] >= 0 && iy[k] < PY) words8(pzf + is[k], iy[k], ig[k], vw[k]);
+            }
+            return;
+        }
         const uint8_t *base = Cb + (int64_t)pzf * slice;
 #pragma unroll
         for (int k = 0; k < 2; ++k) {
@@ -1781,6 +1836,10 @@ __global__ void __launch_bounds__(256, 4) counts_conv12_kernel(
         for (int k = 0; k < 2; ++k) {
             if (tid + 256 * k < nit) {
                 uint32_t *d = pool + ((pzf + is[k] + 5) % 5) * kC12Rows * kPlRow + il[k];
+                if constexpr (PLANES) {
+                    v[k] = pool16(vw[k]);
+                    if (ih[k]) v[k].x = v[k].w;        // the last four before the row
+                }
                 if (!ih[k]) {
 #pragma unroll
                     for (int e = 0; e < 4; ++e) words(v[k][e], d + 4 * e);
@@ -1893,7 +1952,12 @@ __global__ void __launch_bounds__(256, 4) counts_conv12_kernel(
                 const int pz = pzf + s, py = 4 * Y0 - 3 + r;
                 uint32_t *d = pool + ((pz + 5) % 5) * kC12Rows * kPlRow + r * kPlRow;
                 u32x4 x = {0u, 0u, 0u, 0u};
-                if (pz >= 0 && py >= 0 && py < PY) {
+                if (PLANES && pz >= 0 && py >= 0 && py < PY) {
+                    uint32_t w8[8];
+                    words8(pz, py, halo ? -1 : p, w8);
+                    x = pool16(w8);
+                    if (halo) x.x = x.w;
+                } else if (pz >= 0 && py >= 0 && py < PY) {
                     const uint8_t *row = Cb + pz * slice + (int64_t)py * PX;
                     if (!halo) x = *reinterpret_cast<const u32x4 *>(row + 16 * p);
                     else x.x = *reinterpret_cast<const uint32_t *>(row - 4);
@@ -2384,14 +2448,15 @@ int nn_pool_conv_counts_bf16(const uint8_t *counts, int B, int nx, int ny, int n
     return launched("nn_pool_conv_counts_bf16");
 }
 
-int nn_counts_conv12_bf16(const uint8_t *counts, int B, int nx, int ny, int nz, int mask,
-                          const void *Wt1, const float *b1, const void *Wtm2, const float *b2,
-                          void *Y, void *stream)
+static int conv12(const char *fn, const uint8_t *counts, const uint32_t *planes,
+                  int64_t sample_words, const int32_t *idx, int B, int nx, int ny, int nz, int mask,
+                  const void *Wt1, const float *b1, const void *Wtm2, const float *b2, void *Y,
+                  void *stream)
 {
-    if (!counts || !Wt1 || !Wtm2 || !Y || B <= 0 || nx <= 0 || ny <= 0 || nz <= 0 || nx % 128 ||
-        ny % 32 || nz % 16 || mask < -1 || mask > 1 || (uintptr_t)counts % 16 ||
+    if ((!counts && !planes) || !Wt1 || !Wtm2 || !Y || B <= 0 || nx <= 0 || ny <= 0 || nz <= 0 ||
+        nx % 128 || ny % 32 || nz % 16 || mask < -1 || mask > 1 || (uintptr_t)counts % 16 ||
         (uintptr_t)Wtm2 % 16 || (uintptr_t)Y % 8 || (int64_t)nx * ny * nz >= ((int64_t)1 << 31))
-        return tdb_set_error(DB_EINVAL, "nn_counts_conv12_bf16: bad arguments");
+        return tdb_set_error(DB_EINVAL, "%s: bad arguments", fn);
     const int OD2 = nz / 8;
     const int64_t cols = (int64_t)B * (nx / 128) * (ny / 32);   // 4 x 16 output columns
     // Output slices per block: all of them, halved (each chunk recomputes one first-layer
@@ -2399,19 +2464,40 @@ int nn_counts_conv12_bf16(const uint8_t *counts, int B, int nx, int ny, int nz, 
     int zc = OD2;
     while (zc % 2 == 0 && zc > 4 && cols * (OD2 / zc) < 2048) zc /= 2;
     const int64_t units = cols * (OD2 / zc);
-    if (units >= ((int64_t)1 << 31))
-        return tdb_set_error(DB_EINVAL, "nn_counts_conv12_bf16: too large");
+    if (units >= ((int64_t)1 << 31)) return tdb_set_error(DB_EINVAL, "%s: too large", fn);
     const hipStream_t s = static_cast<hipStream_t>(stream);
     const auto *w1 = static_cast<const uint16_t *>(Wt1);
     const auto *w2 = static_cast<const uint16_t *>(Wtm2);
     auto *y = static_cast<uint16_t *>(Y);
-    if (mask < 0)
-        hipLaunchKernelGGL(counts_conv12_kernel<2>, dim3((unsigned)units), dim3(256), 0, s, counts,
-                           nx, ny, nz, mask, zc, (int)units, w1, b1, w2, b2, y);
-    else
-        hipLaunchKernelGGL(counts_conv12_kernel<1>, dim3((unsigned)units), dim3(256), 0, s, counts,
-                           nx, ny, nz, mask, zc, (int)units, w1, b1, w2, b2, y);
-    return launched("nn_counts_conv12_bf16");
+#define TDB_CONV12(CI_, PLANES_)                                                                   \
+    hipLaunchKernelGGL((counts_conv12_kernel<CI_, PLANES_>), dim3((unsigned)units), dim3(256), 0, s, \
+                       counts, planes, sample_words, idx, nx, ny, nz, mask, zc, (int)units, w1, b1,  \
+                       w2, b2, y)
+    if (planes) {
+        if (mask < 0) TDB_CONV12(2, true); else TDB_CONV12(1, true);
+    } else {
+        if (mask < 0) TDB_CONV12(2, false); else TDB_CONV12(1, false);
+    }
+#undef TDB_CONV12
+    return launched(fn);
+}
+
+int nn_counts_conv12_bf16(const uint8_t *counts, int B, int nx, int ny, int nz, int mask,
+                          const void *Wt1, const float *b1, const void *Wtm2, const float *b2,
+                          void *Y, void *stream)
+{
+    return conv12("nn_counts_conv12_bf16", counts, nullptr, 0, nullptr, B, nx, ny, nz, mask, Wt1, b1,
+                  Wtm2, b2, Y, stream);
+}
+
+int nn_planes_conv12_bf16(const uint32_t *planes, int64_t sample_words, const int32_t *idx, int B,
+                          int nx, int ny, int nz, int mask, const void *Wt1, const float *b1,
+                          const void *Wtm2, const float *b2, void *Y, void *stream)
+{
+    if (B > 65535 || sample_words % 2 || sample_words / 2 < (int64_t)nx * ny * nz / 32)
+        return tdb_set_error(DB_EINVAL, "nn_planes_conv12_bf16: bad arguments");
+    return conv12("nn_planes_conv12_bf16", nullptr, planes, sample_words, idx, B, nx, ny, nz, mask,
+                  Wt1, b1, Wtm2, b2, Y, stream);
 }
 
 int nn_conv34_bf16(int B, const void *X, const void *Wtm3, const float *b3, const void *Wtm4,

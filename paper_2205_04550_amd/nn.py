@@ -70,6 +70,8 @@ _SIGS = {
                                         _vp, _vp]),
     "nn_counts_conv12_bf16": (_i32, [_vp, _i32, _i32, _i32, _i32, _i32, _vp, _vp, _vp, _vp, _vp,
                                      _vp]),
+    "nn_planes_conv12_bf16": (_i32, [_vp, _i64, _vp, _i32, _i32, _i32, _i32, _i32, _vp, _vp, _vp,
+                                     _vp, _vp, _vp]),
     "nn_conv34_bf16": (_i32, [_i32, _vp, _vp, _vp, _vp, _vp, _vp, _vp]),
     "nn_conv3d_weights_tapmajor": (_i32, [_vp, _i32, _i32, _vp, _vp]),
     "nn_linear_fwd_split": (_i32, [_i32, _i32, _i32, _vp, _vp, _vp, _i32, _vp, _i32, _vp, _sz,
@@ -262,6 +264,28 @@ def counts_conv12_bf16(counts: torch.Tensor, w1_bf16: torch.Tensor, b1: torch.Te
     _check(LIB.nn_counts_conv12_bf16(counts.data_ptr(), B, nx, ny, nz, -1 if mask is None else mask,
                                      w1_bf16.data_ptr(), _p(b1), w2_tm.data_ptr(), _p(b2),
                                      y.data_ptr(), _s()))
+    return y
+
+
+def planes_conv12_bf16(planes: torch.Tensor, dims, w1_bf16: torch.Tensor, b1: torch.Tensor | None,
+                       w2_tm: torch.Tensor, b2: torch.Tensor | None, mask: int | None = None,
+                       idx: torch.Tensor | None = None) -> torch.Tensor:
+    """counts_conv12_bf16 from packed masks (as pool_conv_planes_bf16 takes them):
+    conv3d_bf16(pool_conv_planes_bf16(...)) bit for bit."""
+    nx, ny, nz = dims
+    S, two, Wp = planes.shape
+    assert two == 2 and planes.is_contiguous()
+    B = S if idx is None else idx.numel()
+    assert w1_bf16.dtype == torch.bfloat16 and w1_bf16.shape[:2] == (8, 2 if mask is None else 1)
+    assert w2_tm.dtype == torch.bfloat16 and tuple(w2_tm.shape) == (16, 28, 8)
+    w1_bf16, w2_tm = _c(w1_bf16), _c(w2_tm)
+    b1 = None if b1 is None else _c(b1.detach())
+    b2 = None if b2 is None else _c(b2.detach())
+    idx = None if idx is None else _c(idx.to(torch.int32))
+    y = torch.empty((B, nz // 8, ny // 8, nx // 8, 16), dtype=torch.bfloat16, device=planes.device)
+    _check(LIB.nn_planes_conv12_bf16(planes.data_ptr(), 2 * Wp, _p(idx), B, nx, ny, nz,
+                                     -1 if mask is None else mask, w1_bf16.data_ptr(), _p(b1),
+                                     w2_tm.data_ptr(), _p(b2), y.data_ptr(), _s()))
     return y
 
 
@@ -708,9 +732,10 @@ class AutoEncoder:
         equal to it bit for bit for the labels that packed to these masks."""
         assert self.bf16_inference_ok(dims)
         with torch.no_grad():
-            w, b, wc = self._w("enc0")
-            h = pool_conv_planes_bf16(planes, dims, wc, b, True, mask, idx)
-        return self.encode_after_first_bf16(h)
+            _, b1, wc1 = self._w("enc0")
+            _, b2, _ = self._w("enc1")
+            h = planes_conv12_bf16(planes, dims, wc1, b1, self._tapmajor()["enc1"], b2, mask, idx)
+        return self.encode_after_first_bf16(h, first=2)
 
     def _head(self, h: torch.Tensor) -> torch.Tensor:
         w, b, wc = self._w("enc_fc")

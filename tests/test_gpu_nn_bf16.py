@@ -325,3 +325,33 @@ def test_third_and_fourth_layers_in_one_kernel(B):
         got = nn.conv34_bf16(x, t3, b3, t4, b4)
         assert torch.equal(got.view(torch.int32), want.view(torch.int32)), bias
         assert float((want != 0).double().mean()) > 0.05
+
+
+@pytest.mark.parametrize("dims,B", [((128, 128, 128), 3), ((256, 96, 48), 2), ((128, 32, 16), 5)])
+def test_first_two_layers_from_packed_masks(dims, B):
+    """nn_planes_conv12_bf16 equals the first layer from packed masks followed by the second
+    convolution (two kernels) bit for bit: both masks and each alone, one and two x tiles (the
+    halo words), a sample chosen twice by idx, padding words between the samples' planes."""
+    need_gpu()
+    from paper_2205_04550_amd import nn
+    nx, ny, nz = dims
+    g = torch.Generator().manual_seed(nx + ny + B)
+    Wp = nx * ny * nz // 32 + 4
+    planes = torch.randint(-2 ** 31, 2 ** 31 - 1, (B, 2, Wp), generator=g, dtype=torch.int64).to(torch.int32)
+    planes[:, 1] &= planes[:, 0]
+    planes[0, :, : Wp // 3] = 0
+    planes = planes.cuda()
+    idx = torch.tensor([B - 1, 0, B - 1], dtype=torch.int32, device="cuda")
+    for mask, bias in ((None, True), (None, False), (0, True), (1, True)):
+        ci = 2 if mask is None else 1
+        w1 = (torch.randn(8, ci, 3, 3, 3, generator=g) * 0.3).to(torch.bfloat16).cuda()
+        w2 = (torch.randn(16, 8, 3, 3, 3, generator=g) * 0.2).to(torch.bfloat16).cuda()
+        b1 = torch.randn(8, generator=g).cuda() * 0.1 if bias else None
+        b2 = torch.randn(16, generator=g).cuda() * 0.1 if bias else None
+        w2tm = nn.conv_weights_tapmajor(w2)
+        for i in (None, idx):
+            want = nn.conv3d_bf16(nn.pool_conv_planes_bf16(planes, dims, w1, b1, True, mask, i), w2tm, b2, True)
+            got = nn.planes_conv12_bf16(planes, dims, w1, b1, w2tm, b2, mask, i)
+            assert got.shape == want.shape
+            assert torch.equal(got.view(torch.int16), want.view(torch.int16)), (mask, bias)
+        assert float((want != 0).double().mean()) > 0.05
