@@ -431,7 +431,16 @@ int db_append(db_t *db, const float *conc, int64_t n, void *stream)
     hipStream_t s = static_cast<hipStream_t>(stream);
     uint32_t *planes = db->planes + db->count * 2 * (int64_t)db->g.Wp;
     uint32_t *pc = db->popcnt + db->count * 2;
-    hipError_t e = launch_pack_db(db, conc, n, planes, pc, s);
+    if (append_one_pass_ok(db->g)) {
+        const hipError_t e = launch_append(db, conc, n, planes, pc, db->box + db->count * 4,
+                                           db->tbox + db->count * 4, db->mom + db->count * 4,
+                                           db->zrange + db->count * db->g.nz * 2,
+                                           block_counts_at(db, db->count), s);
+        if (e != hipSuccess) return hip_fail(e, "db_append: launch");
+        db->count += n;
+        return DB_OK;
+    }
+    hipError_t e = launch_pack_db(db, conc, n, planes, pc, s);   // grids deeper than 512 slices
     if (e == hipSuccess)
         e = launch_meta(planes, n, db->g, db->box + db->count * 4, db->tbox + db->count * 4,
                         db->mom + db->count * 4, db->zrange + db->count * db->g.nz * 2, s);

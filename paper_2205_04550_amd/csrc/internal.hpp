@@ -116,6 +116,12 @@ int64_t topk_blocks(int64_t n);
 // ---- launchers (each returns hipGetLastError of its launch) ----
 hipError_t launch_pack_db(const db_t *db, const float *conc, int64_t n, uint32_t *planes,
                           uint32_t *popcnt, hipStream_t s);
+// All of an entry's parts in one pass over its densities (launch_pack_db, launch_meta and
+// launch_block_counts in one; bcnt NULL: no block counts kept), where append_one_pass_ok holds.
+bool append_one_pass_ok(const Geometry &g);
+hipError_t launch_append(const db_t *db, const float *conc, int64_t n, uint32_t *planes,
+                         uint32_t *popcnt, int32_t *box, int32_t *tbox, uint64_t *mom,
+                         uint32_t *zrange, uint16_t *bcnt, hipStream_t s);
 hipError_t launch_pack_queries(const db_t *db, const uint8_t *labels, int nq, const int32_t *rois,
                                uint32_t *qpack, QueryPart *qpart, hipStream_t s);
 // launch_pack_queries without ROI that also writes the labels' 2x2x2 pooled counts,
