@@ -332,13 +332,16 @@ def bench_batch(args, db, gen, n, build_s) -> int:
         "queries_per_s": nq / (ms * 1e-3),
         "roofline": {"bound": "alu", "achieved": achieved / 1e12, "peak": VALU_PEAK_OPS / 1e12,
                      "unit": "Tops/s", "frac": achieved / VALU_PEAK_OPS, "traffic": None,
-                     "kernel": "batch_lds_kernel (from a HIP graph)",
+                     "kernel": ("batch_lds_kernel" if any(best[:4]) else
+                                "the handle's own choice: batch_mfma_kernel for many large boxes")
+                               + " (from a HIP graph)",
                      "kernel_avg_ms": g_avg,
                      "algorithmic_ops_per_launch": ops,
                      "dense_box_ops_per_launch": dense_ops,
                      "note": "ops over the rows of each box clipped to the union of the tile's "
                              "row boxes, the rows the kernel scans; the dense count treats every "
-                             "box row of every entry as work",
+                             "box row of every entry as work; the matrix-core kernel makes the same "
+                             "counts as FP4 products in place of these vector operations",
                      "hbm_floor_gb_per_launch": n * 2 * gen.nvox / 8 / 1e9},
         "autotune": {"picked": {"slab_planes": best[0], "block_threads": best[1],
                                 "tile_entries": best[2], "query_chunk": best[3]},

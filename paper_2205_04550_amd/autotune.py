@@ -11,10 +11,11 @@ import torch
 
 
 def candidates(nz: int, nq: int):
-    """(slab_planes, block_threads, tile_entries, query_chunk) shapes to time."""
+    """(slab_planes, block_threads, tile_entries, query_chunk) shapes to time; all zero is the
+    kernel that a handle takes by itself."""
     planes = sorted({p for p in (0, 4, 8) if p <= nz})
     chunks = sorted({c for c in (0, 128, 512) if c == 0 or c < max(nq, 129)})
-    return [(p, t, tile, c) for p in planes for t in (512, 1024) for tile in (4, 8)
+    return [(0, 0, 0, 0)] + [(p, t, tile, c) for p in planes for t in (512, 1024) for tile in (4, 8)
             for c in chunks]
 
 
@@ -46,7 +47,7 @@ def tune_batch(db, labels: torch.Tensor, rois, k: int, reps: int = 3, configs=No
         ms = sorted(times)[len(times) // 2]
         table.append((planes, threads, tile, chunk, ms))
         if log:
-            log(f"  slab planes {planes or 'max'} x {threads} threads, tile {tile or 4}, "
+            log(f"  slab planes {planes or 'max'} x {threads or 'default'} threads, tile {tile or 4}, "
                 f"query chunk {chunk or 256}: {ms:.2f} ms")
     best = min(table, key=lambda t: t[-1])
     db.tune_batch(*best[:4])

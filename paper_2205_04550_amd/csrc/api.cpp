@@ -2,6 +2,7 @@
 #include <hip/hip_runtime.h>
 
 #include <algorithm>
+#include <cmath>
 #include <cstdarg>
 #include <cstdio>
 #include <cstring>
@@ -107,6 +108,8 @@ struct BatchGraph {
     hipGraphExec_t exec = nullptr;
     int32_t *staging = nullptr;  // pinned upload buffer: rois [nq][6] + order [nq]
     size_t staging_elems = 0;
+    int32_t *order = nullptr;    // device: entry order of the matrix-core kernel's tiles
+    int64_t order_n = 0, order_cap = 0;
     hipEvent_t uploaded = nullptr;
     bool upload_pending = false;
 
@@ -123,6 +126,7 @@ struct BatchGraph {
             (void)hipEventDestroy(uploaded);
         }
         if (staging) (void)hipHostFree(staging);
+        if (order) (void)hipFree(order);
         if (cap) (void)hipStreamDestroy(cap);
     }
 };
@@ -268,13 +272,41 @@ static hipError_t dist_launch(int fmt, int M, int N, int dim, const void *q_code
                            static_cast<const uint8_t *>(x_codes), x_scale, x_sq, D, mode, gmin, s);
 }
 
+// Order queries so that groups of 32 have neighbouring boxes (box [.][6] = x0, y0, z0, x1, y1, z1):
+// halve along the axis on which the box centres spread most, at a multiple of 32, until 32 are left.
+static void neighbour_order(const int32_t *box, int32_t *order, int n)
+{
+    if (n <= 32) return;
+    int axis = 0, most = -1;
+    auto centre = [&](int32_t q, int a) { return box[6 * (size_t)q + a] + box[6 * (size_t)q + a + 3]; };
+    for (int a = 0; a < 3; ++a) {
+        int lo = INT32_MAX, hi = INT32_MIN;
+        for (int i = 0; i < n; ++i) {
+            const int c = centre(order[i], a);
+            lo = std::min(lo, c);
+            hi = std::max(hi, c);
+        }
+        if (hi - lo > most) {
+            most = hi - lo;
+            axis = a;
+        }
+    }
+    const int half = (n / 2 + 31) / 32 * 32;
+    std::nth_element(order, order + half, order + n, [&](int32_t a, int32_t b) {
+        const int ca = centre(a, axis), cb = centre(b, axis);
+        return ca < cb || (ca == cb && a < b);
+    });
+    neighbour_order(box, order, half);
+    neighbour_order(box, order + half, n - half);
+}
+
 // Sort the entries by the centre of their row boxes (z in bands of 8 planes,
 // then y), so that the batched kernel's tiles (groups of `tile` consecutive
 // entries) hold overlapping boxes; then order the tiles by the size of the union
 // of their members' row boxes, largest first (blocks are dispatched in this
 // order, so the longest items start first). Reads the boxes back after a
 // device synchronisation; host sort; one upload.
-static int build_tile_order(db_t *db, int tile)
+static int build_tile_order(db_t *db, int tile, int32_t *dst)
 {
     const int64_t n = db->count;
     std::vector<int32_t> box((size_t)n * 4);
@@ -287,9 +319,15 @@ static int build_tile_order(db_t *db, int tile)
         const int32_t *b = &box[(size_t)i * 4];
         return !(b[1] > b[0] && b[3] > b[2]);
     };
+    // Tiles of many entries: bands of z centre and of y centre, then by size, as many of each as
+    // make about one tile of a band of all three.
+    const int64_t bands = tile >= 64 ? std::max<int64_t>(1, std::llround(std::cbrt((double)n / tile))) : 0;
     auto key = [&](int32_t i) {
         const int32_t *b = &box[(size_t)i * 4];
         const int64_t zc = b[0] + b[1], yc = b[2] + b[3];
+        if (bands && !empty(i))
+            return ((zc * bands / (2 * db->g.nz)) << 48) | ((yc * bands / (2 * db->g.ny)) << 32) |
+                   ((int64_t)(b[1] - b[0]) * (b[3] - b[2]));
         return empty(i) ? INT64_MAX : ((zc / 16) << 32) | (yc << 16) | (b[1] - b[0]);
     };
     std::stable_sort(order.begin(), order.end(),
@@ -319,10 +357,8 @@ static int build_tile_order(db_t *db, int tile)
     for (int64_t t : tperm)
         for (int64_t j = t * tile; j < std::min<int64_t>(n, (t + 1) * tile); ++j)
             sorted.push_back(order[j]);
-    e = hipMemcpy(db->tile_order, sorted.data(), (size_t)n * 4, hipMemcpyHostToDevice);
+    e = hipMemcpy(dst, sorted.data(), (size_t)n * 4, hipMemcpyHostToDevice);
     if (e != hipSuccess) return hip_fail(e, "db_query_batch: upload tile order");
-    db->tile_order_n = n;
-    db->tile_order_tile = tile;
     return DB_OK;
 }
 
@@ -644,7 +680,8 @@ int db_query_batch(const db_t *db_c, int nq, const uint8_t *q_labels, const db_r
     std::stable_sort(order.begin(), order.end(),
                      [&](int32_t a, int32_t b) { return cost[a] > cost[b]; });
     // Per (query chunk, z-slab): the queries whose box meets the slab, costliest first.
-    const BatchPlan P = batch_plan(db, nq);
+    BatchPlan P = batch_plan(db, nq, std::accumulate(cost.begin(), cost.end(), (int64_t)0));
+    if (P.te) neighbour_order(box.data(), order.data(), nq);
     std::vector<int32_t> list_off, list_q;
     if (P.use_lds) {
         list_off.reserve((size_t)P.nchunks * P.nslabs + 1);
@@ -661,11 +698,6 @@ int db_query_batch(const db_t *db_c, int nq, const uint8_t *q_labels, const db_r
             }
     }
 
-    // Entries grouped by row-box centre for the LDS kernel's tiles (rebuilt after appends).
-    if (P.use_lds && (db->tile_order_n != db->count || db->tile_order_tile != P.tile)) {
-        rc = build_tile_order(db, P.tile);
-        if (rc) return rc;
-    }
     if (!db->graph) {
         db->graph = new (std::nothrow) BatchGraph();
         if (!db->graph) return fail(DB_ENOMEM, "db_query_batch: out of host memory");
@@ -676,6 +708,40 @@ int db_query_batch(const db_t *db_c, int nq, const uint8_t *q_labels, const db_r
         e = hipStreamCreateWithFlags(&G.cap, hipStreamNonBlocking);
         if (e == hipSuccess) e = hipEventCreateWithFlags(&G.uploaded, hipEventDisableTiming);
         if (e != hipSuccess) return hip_fail(e, "db_query_batch: stream/event create");
+    }
+    // Entries grouped by row-box centre for the tiles (rebuilt after appends); the matrix-core
+    // kernel's have an order of their own, so that calls of both kinds may alternate.
+    if (P.use_lds) {
+        if (db->tile_order_n != db->count || db->tile_order_tile != P.tile) {
+            db->tile_order_n = 0;
+            rc = build_tile_order(db, P.tile, db->tile_order);
+            if (rc) return rc;
+            db->tile_order_n = db->count;
+            db->tile_order_tile = P.tile;
+        }
+        P.tile_order = db->tile_order;
+    } else if (P.te) {
+        if (G.order_cap < db->count) {
+            G.drop_exec();                               // recorded with the old buffer
+            e = hipDeviceSynchronize();
+            if (e != hipSuccess) return hip_fail(e, "db_query_batch: tile order");
+            if (G.order) (void)hipFree(G.order);
+            G.order = nullptr;
+            G.order_n = G.order_cap = 0;
+            if (hipMalloc((void **)&G.order, (size_t)db->capacity * 4) == hipSuccess) {
+                G.order_cap = db->capacity;
+            } else {                                     // no memory left: entries as they stand
+                (void)hipGetLastError();
+                G.order = nullptr;
+            }
+        }
+        if (G.order && G.order_n != db->count) {
+            G.order_n = 0;
+            rc = build_tile_order(db, P.tile, G.order);
+            if (rc) return rc;
+            G.order_n = db->count;
+        }
+        P.tile_order = G.order;
     }
     // Pinned staging buffer; wait for the previous upload before reusing it.
     const size_t elems = (size_t)nq * 7 + list_off.size() + list_q.size();

@@ -136,13 +136,17 @@ hipError_t launch_sum_parts(const QueryPart *qpart, int nq, uint32_t *acnt, int3
                             uint64_t *qmom, hipStream_t s, int32_t *qtbox = nullptr);
 hipError_t launch_scan(const db_t *db, int64_t n, const uint32_t *qpack, uint32_t *inter,
                        hipStream_t s);
-// Shape of a batched launch: LDS slabs of Z planes (use_lds) or the L2 fallback.
+// Shape of a batched launch: the matrix-core kernel (te > 0: its entry tiles per wave), LDS
+// slabs of Z planes (use_lds) or the L2 fallback.
 struct BatchPlan {
+    int te;
     bool use_lds;
     int Z, nslabs, qchunk, nchunks, threads, tile;
     size_t lds_bytes;
+    const int32_t *tile_order;   // entries in the order of the tiles, or NULL: as they stand
 };
-BatchPlan batch_plan(const db_t *db, int nq);
+// box_words: 32-voxel words of all queries' boxes.
+BatchPlan batch_plan(const db_t *db, int nq, int64_t box_words);
 int batch_tile(const db_t *db);   // entries per tile of the LDS kernel (4 or 8)
 hipError_t batch_set_lds_limit(int bytes);
 hipError_t launch_batch_scan(const db_t *db, int64_t n, int nq, const BatchPlan &p,

@@ -157,3 +157,34 @@ def test_batch_more_queries_than_one_chunk(planes, tile):
     res = db.query_batch(torch.from_numpy(labels).cuda(), rois, k)
     db.sync()
     _compare(res, [(cnt[q], sc[q], oracle.rank(sc[q], k)) for q in range(nq)], k)
+
+
+@pytest.mark.parametrize("nq,n,dims", [(96, 61, (128, 64, 96)), (128, 130, (128, 45, 136)), (129, 63, (128, 128, 48)),
+                                       (257, 65, (128, 6, 1024)), (300, 5, (128, 101, 61))])
+def test_batch_matrix_core_kernel(nq, n, dims):
+    """The matrix-core kernel (96 queries and more on rows of 128 voxels) with each split of its
+    waves, groups of 32 queries and tiles of 64 entries with a rest, uneven boxes and empty
+    entries, against the oracle's loop; the vector kernel asked for gives the same bytes."""
+    need_gpu()
+    gen = synth.GenConfig(*dims, 2.0, min(dims) / 2, 0.5, 3.0, 41)
+    k = 5
+    say(f"batch on matrix cores: {nq} queries, {n} entries, {dims}")
+    conc = gen.conc_cpu(0, n)
+    conc[3] = 0.0
+    db, conc = build_db_from_host(gen, n, T_LO, T_HI, conc=conc)
+    labels, _ = synth.make_queries(gen, n, nq, synth.BATCH_QUERY_SEED)
+    rng = np.random.default_rng(nq)
+    rois = _edge_rois(dims, nq, rng) if min(dims) > 9 else np.tile((0, 0, 0) + dims, (nq, 1)).astype(np.int32)
+    for q in range(6, nq, 2):                            # every other box nearly the whole grid
+        rois[q] = [*(int(rng.integers(0, d // 8 + 1)) for d in dims),
+                   *(d - int(rng.integers(0, d // 8 + 1)) for d in dims)]
+    cnt, sc = oracle.scan_block_multi(conc, labels, T_LO, T_HI, rois)
+    ref = [(cnt[q], sc[q], oracle.rank(sc[q], k)) for q in range(nq)]
+    lab_d = torch.from_numpy(labels).cuda()
+    res = db.query_batch(lab_d, rois, k)
+    db.sync()
+    _compare(res, ref, k)
+    db.tune_batch(0, 1024, 4, 0)
+    res = db.query_batch(lab_d, rois, k)
+    db.sync()
+    _compare(res, ref, k)
