@@ -18,6 +18,19 @@ __device__ __forceinline__ u32x4 load_stream(const u32x4 *p)
     return __builtin_nontemporal_load(p);
 }
 
+// A buffer of n bytes at p (wave-uniform): loads at kBufferOut (or past the end) give 0 and no
+// memory traffic, so a lane without data needs no branch. AUX 2: the load streams past the caches.
+constexpr uint32_t kBufferOut = 0x80000000u;
+__device__ __forceinline__ __amdgpu_buffer_rsrc_t buffer_of(const void *p, uint32_t n)
+{
+    return __builtin_amdgcn_make_buffer_rsrc(const_cast<void *>(p), 0, n, 0x00020000);
+}
+template <int AUX>
+__device__ __forceinline__ u32x4 buffer_b128(__amdgpu_buffer_rsrc_t r, uint32_t off, uint32_t soff)
+{
+    return __builtin_bit_cast(u32x4, __builtin_amdgcn_raw_buffer_load_b128(r, off, soff, AUX));
+}
+
 __device__ __forceinline__ uint32_t popc(uint32_t x) { return (uint32_t)__builtin_popcount(x); }
 
 // acc + popcount(x) as the single instruction the hardware has for it. Written out

@@ -497,21 +497,28 @@ static_assert(kRC == 4, "the LDS staging of the per-slice ranges picks among fou
 constexpr int kRerankPerBlock = 4 * kRC;   // candidates scored per block (4 waves)
 constexpr int kZStage = 128;           // z-slices of per-slice row ranges a wave stages in LDS
 
-// 1-D grid of nbq * 8 * ceil(nq / 8) blocks (nbq = ceil(count / candidates per block): 4 kRC,
-// or kRC with SPLIT = 4), 256 threads (4 waves). Blocks go to the 8 XCDs round-robin; the mapping below
-// gives every block of query q to XCD q % 8, so the query's rows are fetched into
+// 1-D grid of nbq * 8 * ceil(nq / 8) blocks (nbq = ceil(count / candidates per block): 4 kRC
+// with SPLIT = 1, else kRC), max(SPLIT, 4) waves. Blocks go to the 8 XCDs round-robin; the mapping
+// below gives every block of query q to XCD q % 8, so the query's rows are fetched into
 // one L2 only. Each wave scores
 // kRC candidates of query q at once: lanes sweep the rows where the query's row
 // boxes meet the candidates' stored row boxes (outside either box one side is
 // zero and adds nothing; the T1Gd plane has boxes of its own, smaller than those
 // of both masks), AND + popcount against each candidate's planes; the score and
 // overlaps go to ws (score bits [nq][nc], index [nq][nc], I [nq][nc][2]).
-// SPLIT = 4: a block scores kRC candidates (not 4 kRC), its four waves taking every fourth
-// pass over the rows and adding their overlaps in LDS: four times the waves per candidate, for
-// launches with few candidates per query. ALLZR: nz <= kZStage, so every query's slices have
-// their ranges staged.
-template <int SPLIT, bool ALLZR>
-__global__ void __launch_bounds__(256) rerank_score_kernel(const uint32_t *__restrict__ planes,
+// SPLIT > 1: a block scores kRC candidates (not 4 kRC), its SPLIT waves sharing the staged
+// ranges, taking the passes over the rows in turn and adding their overlaps in LDS: more waves per
+// candidate, for launches with few candidates per query. ALLZR: nz <= kZStage, so every query's
+// slices have their ranges staged.
+// NXW = 1 .. 4: rows of so many words are read as 16 bytes per lane and plane (4, 2, 1, 1 rows of a
+// slice; words past the slice's last row are taken out of the query's side), two groups per pass,
+// by buffer loads that a lane without a row turns off with its offset: all 20 loads of a pass are
+// in flight at once, where loads under conditions wait for one another. NXW = 0: any width, a word
+// at a time. 200 queries on 96 x 112 x 77 and 1,000 candidates, the first 16 of each / the rest:
+// 28 / 151 us, a word at a time 97 / 331. With rows of 128 voxels a full chip is bound by the
+// candidates' bytes (1,024 queries: 220 us either way).
+template <int SPLIT, bool ALLZR, int NXW>
+__global__ void __launch_bounds__(SPLIT > 4 ? 64 * SPLIT : 256) rerank_score_kernel(const uint32_t *__restrict__ planes,
                                                            const uint32_t *__restrict__ popcnt,
                                                            const int32_t *__restrict__ ebox,
                                                            const int32_t *__restrict__ etbox,
@@ -535,7 +542,12 @@ __global__ void __launch_bounds__(256) rerank_score_kernel(const uint32_t *__res
     const int xcd = blockIdx.x % 8, slot = blockIdx.x / 8;
     const int q = (slot / nbq) * 8 + xcd, qb = slot % nbq;
     if (q >= nq) return;                       // whole block, before any barrier
-    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+    const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    // This wave's candidates: positions first + c0 .. + kRC - 1 of the query's list, count of
+    // them (qcount: the query's own count; most blocks of a round find nothing and leave here).
+    const int c0 = SPLIT == 1 ? qb * kRerankPerBlock + wave * kRC : qb * kRC;
+    const int cnt = min(qcount ? qcount[q] : count, nc - first);
+    if (c0 >= cnt) return;  // a whole wave (SPLIT > 1: the block) leaves, before any barrier
     const uint32_t *Q0 = qpack + (int64_t)q * 2 * Wp, *Q1 = Q0 + Wp;
     const int32_t *b = box + 4 * q, *tb = tbox + 4 * q;
     const int qz0 = b[0], qz1 = b[1], qy0 = b[2], qy1 = b[3];
@@ -545,51 +557,51 @@ __global__ void __launch_bounds__(256) rerank_score_kernel(const uint32_t *__res
     // the union of its members' boxes. A member reads its FLAIR rows inside (its row box n the
     // query's) and its T1Gd rows inside (its T1Gd box n the query's): outside either pair of
     // boxes one of the two masks is empty.
-    // This wave's candidates: positions first + c0 .. + kRC - 1 of the query's list, count of
-    // them (qcount: the query's own count). With order, position i is slot order[i] and entry
-    // ents[i] (the candidates in bound order); else slot = position.
-    const int c0 = SPLIT == 1 ? qb * kRerankPerBlock + wave * kRC : qb * kRC;
+    // With order, position i is slot order[i] and entry ents[i] (the candidates in bound order);
+    // else slot = position.
     const int64_t qo = (int64_t)q * nc;
-    const int cnt = qcount ? qcount[q] : count;
     int cs[kRC];
     int32_t ent[kRC];
-    bool act[kRC], any = false;
+    bool act[kRC];
 #pragma unroll
     for (int j = 0; j < kRC; ++j) {
-        const int i = first + c0 + j;
-        act[j] = c0 + j < cnt && i < nc;
-        const int ii = act[j] ? i : 0;
+        act[j] = c0 + j < cnt;
+        const int ii = first + c0 + (act[j] ? j : 0);
         cs[j] = order ? order[qo + ii] : ii;
         ent[j] = ents ? ents[qo + ii] : cand[qo + cs[j]];
-        any |= act[j];
     }
-    if (!any) return;       // a whole wave leaves; no block barrier below
     // Each member's per-slice y-ranges of its FLAIR and T1Gd rows over the query's slices (every
-    // slice swept lies in them), in this wave's part of LDS, their loads issued together and
-    // before the members' boxes are known (a query deeper than kZStage slices goes by the
-    // boxes alone).
-    __shared__ uint2 s_zr[4][kRC][kZStage];
+    // slice swept lies in them), in this wave's (SPLIT > 1: the block's) part of LDS, their loads
+    // issued together and before the members' boxes are known (a query deeper than kZStage slices
+    // goes by the boxes alone).
+    constexpr int kStagers = SPLIT == 1 ? 64 : 64 * SPLIT;
+    __shared__ uint2 s_zr[SPLIT == 1 ? 4 : 1][kRC][kZStage];
+    uint2(&zrs)[kRC][kZStage] = s_zr[SPLIT == 1 ? wave : 0];
     const int nzs = qz1 - qz0;
     const bool zr_ok = nzs > 0 && nzs <= kZStage;
     if (zr_ok) {
-        constexpr int kStageMax = kRC * kZStage / 64;
+        constexpr int kStageMax = (kRC * kZStage + kStagers - 1) / kStagers;
+        const int sl = SPLIT == 1 ? lane : threadIdx.x;
         uint2 t[kStageMax];
 #pragma unroll
         for (int u = 0; u < kStageMax; ++u) {
-            const int i = lane + 64 * u, j = i / nzs, zz = i - j * nzs;
+            const int i = sl + kStagers * u, j = i / nzs, zz = i - j * nzs;
             const int32_t e = j == 0 ? ent[0] : j == 1 ? ent[1] : j == 2 ? ent[2] : ent[3];
             t[u] = i < kRC * nzs ? *reinterpret_cast<const uint2 *>(zrange + ((int64_t)e * nz + qz0 + zz) * 2)
                                  : (uint2){0u, 0u};
         }
 #pragma unroll
         for (int u = 0; u < kStageMax; ++u) {
-            const int i = lane + 64 * u, j = i / nzs, zz = i - j * nzs;
-            if (i < kRC * nzs) s_zr[wave][j][zz] = t[u];
+            const int i = sl + kStagers * u, j = i / nzs, zz = i - j * nzs;
+            if (i < kRC * nzs) zrs[j][zz] = t[u];
         }
-        __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
-        __builtin_amdgcn_wave_barrier();
-        __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+        if (SPLIT == 1) {
+            __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+            __builtin_amdgcn_wave_barrier();
+            __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+        }
     }
+    if (SPLIT > 1) __syncthreads();
     const uint32_t *D0[kRC], *D1[kRC];
     int z0[kRC], z1[kRC], y0[kRC], y1[kRC], tz0[kRC], tz1[kRC], ty0[kRC], ty1[kRC];
     int uz0 = INT_MAX, uz1 = INT_MIN, uy0 = INT_MAX, uy1 = INT_MIN;
@@ -622,75 +634,89 @@ __global__ void __launch_bounds__(256) rerank_score_kernel(const uint32_t *__res
     }
     const int nyr = uy1 > uy0 ? uy1 - uy0 : 0;
     const int nr = uz1 > uz0 ? (uz1 - uz0) * nyr : 0;
-    // Row (z, y) of member j holds FLAIR bits only if y is in its FLAIR range of slice z.
-    auto in_range = [&](int j, int z, int y, bool t1gd) {
+    // Rows [y, y + G) of slice z hold FLAIR (T1Gd) bits of member j only if they meet its range.
+    auto in_range = [&](int j, int z, int y, int G, bool t1gd) {
         if (!zr_ok) return true;
-        const uint2 rg = s_zr[wave][j][z - qz0];
+        const uint2 rg = zrs[j][z - qz0];
         const uint32_t v = t1gd ? rg.y : rg.x;
-        return y >= (int)(v & 0xffffu) && y < (int)(v >> 16);
+        return y + G > (int)(v & 0xffffu) && y < (int)(v >> 16);
     };
     uint32_t i0[kRC], i1[kRC];
 #pragma unroll
     for (int j = 0; j < kRC; ++j) i0[j] = i1[j] = 0;
-    if (nxw == 4) {
-        // Rows of 128 voxels: one 16-byte load per plane; two rows per lane per pass, all
-        // loads of the pass issued before any is used.
-        constexpr int U = SPLIT == 1 ? 2 : 1;
-        const int rw = SPLIT == 1 ? 0 : wave;
-        for (int r0 = lane + 64 * U * rw; r0 < nr; r0 += 64 * U * SPLIT) {
+    const int rw = SPLIT == 1 ? 0 : wave;
+    if constexpr (NXW > 0) {
+        constexpr int U = 2, G = NXW == 1 ? 4 : NXW == 2 ? 2 : 1;
+        const int ngr = (nyr + G - 1) / G, ng = uz1 > uz0 ? (uz1 - uz0) * ngr : 0;
+        const uint32_t rec = 8u * (uint32_t)Wp, plane = 4u * (uint32_t)Wp;
+        const __amdgpu_buffer_rsrc_t qr = buffer_of(Q0, rec);
+        __amdgpu_buffer_rsrc_t dr[kRC];
+#pragma unroll
+        for (int j = 0; j < kRC; ++j) dr[j] = buffer_of(D0[j], rec);
+        for (int r0 = lane + 64 * U * rw; r0 < ng; r0 += 64 * U * SPLIT) {
             u32x4 qa[U], qb[U], da[U][kRC], db[U][kRC];
+            uint32_t w0[U], w1[U], base[U];             // the group's words and the first one read
 #pragma unroll
             for (int u = 0; u < U; ++u) {
                 const int r = r0 + 64 * u;
-                const int zr = r / nyr;
-                const int z = uz0 + zr, y = uy0 + r - zr * nyr;
-                const int base = (z * ny + y) * 4;
-                const bool live = r < nr;
+                const int zr = r / ngr;
+                const int z = min(uz0 + zr, uz1 - 1), y = uy0 + (r - zr * ngr) * G;
+                w0[u] = (uint32_t)((z * ny + y) * NXW);
+                w1[u] = (uint32_t)((z * ny + min(y + G, uy1)) * NXW);
+                base[u] = min(w0[u], (uint32_t)Wp - 4u);
+                const bool live = r < ng;
                 bool any0 = false, any1 = false;
                 // With the slice ranges staged, a member's range of a slice lies in its own row
                 // boxes and the sweep in the query's row box: the range decides for FLAIR, the
                 // range and the query's T1Gd box for T1Gd.
-                const bool tin = z >= tqz0 && z < tqz1 && y >= tqy0 && y < tqy1;
+                const bool tin = live && z >= tqz0 && z < tqz1 && y + G > tqy0 && y < tqy1;
 #pragma unroll
                 for (int j = 0; j < kRC; ++j) {
                     bool in0, in1;
                     if constexpr (ALLZR) {
-                        in0 = live && act[j] && in_range(j, z, y, false);
-                        in1 = live && act[j] && tin && in_range(j, z, y, true);
+                        in0 = live & act[j] & in_range(j, z, y, G, false);
+                        in1 = tin & act[j] & in_range(j, z, y, G, true);
                     } else {
-                        in0 = live && z >= z0[j] && z < z1[j] && y >= y0[j] && y < y1[j] &&
-                              in_range(j, z, y, false);
-                        in1 = live && z >= tz0[j] && z < tz1[j] && y >= ty0[j] && y < ty1[j] &&
-                              in_range(j, z, y, true);
+                        in0 = live && z >= z0[j] && z < z1[j] && y + G > y0[j] && y < y1[j] &&
+                              in_range(j, z, y, G, false);
+                        in1 = live && z >= tz0[j] && z < tz1[j] && y + G > ty0[j] && y < ty1[j] &&
+                              in_range(j, z, y, G, true);
                     }
                     any0 |= in0;
                     any1 |= in1;
-                    da[u][j] = db[u][j] = (u32x4){0u, 0u, 0u, 0u};
-                    if (in0) da[u][j] = load_stream(reinterpret_cast<const u32x4 *>(D0[j] + base));
-                    if (in1) db[u][j] = load_stream(reinterpret_cast<const u32x4 *>(D1[j] + base));
+                    da[u][j] = buffer_b128<2>(dr[j], in0 ? 4u * base[u] : kBufferOut, 0);
+                    db[u][j] = buffer_b128<2>(dr[j], in1 ? 4u * base[u] : kBufferOut, plane);
                 }
-                qa[u] = qb[u] = (u32x4){0u, 0u, 0u, 0u};
-                if (any0) qa[u] = *reinterpret_cast<const u32x4 *>(Q0 + base);
-                if (any1) qb[u] = *reinterpret_cast<const u32x4 *>(Q1 + base);
+                qa[u] = buffer_b128<0>(qr, any0 ? 4u * base[u] : kBufferOut, 0);
+                qb[u] = buffer_b128<0>(qr, any1 ? 4u * base[u] : kBufferOut, plane);
             }
 #pragma unroll
-            for (int u = 0; u < U; ++u)
+            for (int u = 0; u < U; ++u) {
+                if (NXW < 4) {
+#pragma unroll
+                    for (int w = 0; w < 4; ++w) {
+                        const bool in = base[u] + w >= w0[u] && base[u] + w < w1[u];
+                        qa[u][w] = in ? qa[u][w] : 0u;
+                        qb[u][w] = in ? qb[u][w] : 0u;
+                    }
+                }
 #pragma unroll
                 for (int j = 0; j < kRC; ++j) {
                     i0[j] += popc_and4(qa[u], da[u][j]);
                     i1[j] += popc_and4(qb[u], db[u][j]);
                 }
+            }
         }
     } else {
-        for (int r = lane + (SPLIT == 1 ? 0 : 64 * wave); r < nr; r += 64 * SPLIT) {
+        for (int r = lane + 64 * rw; r < nr; r += 64 * SPLIT) {
             const int zr = r / nyr;
             const int z = uz0 + zr, y = uy0 + r - zr * nyr;
             const int base = (z * ny + y) * nxw;
             bool in0[kRC], in1[kRC];
 #pragma unroll
             for (int j = 0; j < kRC; ++j) {
-                in0[j] = z >= z0[j] && z < z1[j] && y >= y0[j] && y < y1[j] && in_range(j, z, y, false);
-                in1[j] = z >= tz0[j] && z < tz1[j] && y >= ty0[j] && y < ty1[j] && in_range(j, z, y, true);
+                in0[j] = z >= z0[j] && z < z1[j] && y >= y0[j] && y < y1[j] && in_range(j, z, y, 1, false);
+                in1[j] = z >= tz0[j] && z < tz1[j] && y >= ty0[j] && y < ty1[j] && in_range(j, z, y, 1, true);
             }
             for (int w = 0; w < nxw; ++w) {
                 const uint32_t qa = Q0[base + w], qb = Q1[base + w];
@@ -702,8 +728,8 @@ __global__ void __launch_bounds__(256) rerank_score_kernel(const uint32_t *__res
             }
         }
     }
-    if constexpr (SPLIT > 1) {                // the four waves' overlaps, added in wave 0
-        __shared__ uint32_t s_red[4][kRC][2];
+    if constexpr (SPLIT > 1) {                // the waves' overlaps, added in wave 0
+        __shared__ uint32_t s_red[SPLIT][kRC][2];
 #pragma unroll
         for (int j = 0; j < kRC; ++j) {
             const uint32_t a0 = wave_sum(i0[j]), a1 = wave_sum(i1[j]);
@@ -716,8 +742,8 @@ __global__ void __launch_bounds__(256) rerank_score_kernel(const uint32_t *__res
         if (wave) return;
 #pragma unroll
         for (int j = 0; j < kRC; ++j) {
-            i0[j] = lane == 0 ? s_red[0][j][0] + s_red[1][j][0] + s_red[2][j][0] + s_red[3][j][0] : 0u;
-            i1[j] = lane == 0 ? s_red[0][j][1] + s_red[1][j][1] + s_red[2][j][1] + s_red[3][j][1] : 0u;
+            i0[j] = lane < SPLIT ? s_red[lane][j][0] : 0u;
+            i1[j] = lane < SPLIT ? s_red[lane][j][1] : 0u;
         }
     }
 #pragma unroll
@@ -1837,22 +1863,38 @@ hipError_t launch_rerank_score(const db_t *db, int nq, const uint32_t *qpack, co
     int32_t *qcount = reinterpret_cast<int32_t *>(tail);
     uint32_t *qbc = reinterpret_cast<uint32_t *>(tail + ((size_t)nq * 4 + 255) / 256 * 256);
     // split: kRC candidates per block with the waves splitting the rows (the bound-ordered
-    // rounds, few candidates per query), else 4 kRC per block.
+    // rounds, few candidates per query), else 4 kRC per block. Sixteen waves while every block has
+    // a CU to itself (embedding search of one query, 16 + 84 candidates: 285 us against 299 with
+    // four); with more blocks the waves of several fill a CU, and blocks that find no candidate
+    // left cost more the larger they are (50 queries, 1,000 candidates: 341 against 222 us).
     auto score = [&](int first, int count, const int32_t *ord, const int32_t *en,
                      const int32_t *qc, bool split) {
         const int per = split ? kRC : kRerankPerBlock;
         const int nbq = (count + per - 1) / per;
         const int64_t blocks = (int64_t)nbq * 8 * ((nq + 7) / 8);
-#define TDB_RERANK_SCORE(SPLIT_, ALLZR_)                                                            \
-    hipLaunchKernelGGL((rerank_score_kernel<SPLIT_, ALLZR_>), dim3((unsigned)blocks), dim3(256), 0, \
-                       s, db->planes, db->popcnt, db->box, db->tbox, db->zrange, g.nz, g.Wp,      \
-                       g.nxw, g.ny, qpack, acnt, box, tbox, cand, nc, ws_s, ws_i, ws_I, nq, nbq,  \
-                       ord, en, qc, first, count)
-        const bool allzr = g.nz <= kZStage;
-        if (split && allzr) TDB_RERANK_SCORE(4, true);
-        else if (split) TDB_RERANK_SCORE(4, false);
-        else if (allzr) TDB_RERANK_SCORE(1, true);
-        else TDB_RERANK_SCORE(1, false);
+#define TDB_RERANK_SCORE(SPLIT_, ALLZR_, NXW_)                                                      \
+    hipLaunchKernelGGL((rerank_score_kernel<SPLIT_, ALLZR_, NXW_>), dim3((unsigned)blocks),       \
+                       dim3(SPLIT_ > 4 ? 64 * SPLIT_ : 256), 0, s, db->planes, db->popcnt, db->box, \
+                       db->tbox, db->zrange, g.nz, g.Wp, g.nxw, g.ny, qpack, acnt, box, tbox, cand, \
+                       nc, ws_s, ws_i, ws_I, nq, nbq, ord, en, qc, first, count)
+#define TDB_RERANK_NXW(SPLIT_)                                                                      \
+    do {                                                                                          \
+        if (g.nz <= kZStage) {                                                                    \
+            if (g.nxw == 4) TDB_RERANK_SCORE(SPLIT_, true, 4);                                    \
+            else if (g.nxw == 3) TDB_RERANK_SCORE(SPLIT_, true, 3);                               \
+            else if (g.nxw == 2) TDB_RERANK_SCORE(SPLIT_, true, 2);                               \
+            else if (g.nxw == 1) TDB_RERANK_SCORE(SPLIT_, true, 1);                               \
+            else TDB_RERANK_SCORE(SPLIT_, true, 0);                                               \
+        } else if (g.nxw == 4) {                                                                  \
+            TDB_RERANK_SCORE(SPLIT_, false, 4);                                                   \
+        } else {                                                                                  \
+            TDB_RERANK_SCORE(SPLIT_, false, 0);                                                   \
+        }                                                                                         \
+    } while (0)
+        if (!split) TDB_RERANK_NXW(1);
+        else if ((int64_t)nq * nbq <= db->cus) TDB_RERANK_NXW(16);
+        else TDB_RERANK_NXW(4);
+#undef TDB_RERANK_NXW
 #undef TDB_RERANK_SCORE
     };
     int nbx = 0, nby = 0;

@@ -96,3 +96,43 @@ def test_bound_rerank_equals_scoring_every_candidate(name, n, nc):
             assert bi[q].cpu().tolist() == [int(cand[q][j]) for j in order], (k, q)
             assert np.array_equal(bs[q].cpu().numpy().view(np.uint64),
                                   sc[cand[q][order]].view(np.uint64)), (k, q)
+
+
+@pytest.mark.parametrize("dims,nq", [((32, 37, 29), 3), ((32, 3, 50), 90), ((64, 33, 41), 3),
+                                     ((64, 5, 200), 70), ((96, 21, 17), 70), ((96, 22, 131), 2),
+                                     ((128, 19, 23), 70), ((128, 6, 140), 3), ((160, 9, 31), 5)])
+def test_rerank_row_widths(dims, nq):
+    """Rows of one to five words, slices whose rows end inside a 16-byte group, masks that reach the
+    last row of the grid, few and many queries (16, 4 and 1 waves' share of a candidate's rows):
+    scores and counts against the oracle's, bit for bit, with and without the bound."""
+    need_gpu()
+    nx, ny, nz = dims
+    n, nc, k = 70, 41, 16
+    say(f"rerank row widths {dims}, {nq} queries")
+    rng = np.random.default_rng(nx + ny + nz)
+    # Noise over a random box of each entry, every third one the whole grid.
+    conc = np.zeros((n, nz, ny, nx), dtype=np.float32)
+    for e in range(n):
+        lo = [int(rng.integers(0, d)) if e % 3 else 0 for d in (nz, ny, nx)]
+        hi = [int(rng.integers(a, d)) + 1 if e % 3 else d for a, d in zip(lo, (nz, ny, nx))]
+        s = tuple(slice(a, b) for a, b in zip(lo, hi))
+        conc[(e,) + s] = rng.random(conc[(e,) + s].shape, dtype=np.float32)
+    db, conc = build_db_from_host(synth.GenConfig(nx, ny, nz, 1.0, 2.0, 0.5, 3.0, 1), n, synth.T_LO,
+                                  synth.T_HI, conc=conc)
+    labels = rng.integers(0, 4, (nq, nz, ny, nx)).astype(np.uint8)
+    labels[1::3, :nz // 3] = 0                                     # row boxes that start inside
+    cand = np.stack([rng.choice(n, nc, replace=False) for _ in range(nq)]).astype(np.int32)
+    lab_d, cand_d = torch.from_numpy(labels).cuda(), torch.from_numpy(cand).cuda()
+    out = []
+    for bound in (False, True):
+        db.set_rerank_bound(bound)
+        out.append([t.cpu().numpy() for t in db.rerank(lab_d, cand_d, k)])
+    db.sync()
+    for q in range(nq):
+        cnt, sc = oracle.scan_block(conc, labels[q], synth.T_LO, synth.T_HI)
+        order = sorted(range(nc), key=lambda j: (-sc[cand[q][j]], cand[q][j]))[:k]
+        best = cand[q][order]
+        for i, s, c in out:
+            assert np.array_equal(i[q], best), q
+            assert np.array_equal(s[q].view(np.uint64), sc[best].view(np.uint64)), q
+            assert np.array_equal(c[q].view(np.uint32).astype(np.uint64), cnt[best]), q
