@@ -33,6 +33,8 @@
 // for the written distances.
 #include <limits.h>
 
+#include <algorithm>
+
 #include "common.hpp"
 #include "embed_core.hpp"
 #include "internal.hpp"
@@ -81,13 +83,14 @@ __device__ __forceinline__ float knn_alpha(float qn, float tau)
 }
 
 // Tighten the bound of one row and drop the entries above it (one wave, every lane
-// active; L is the row's list of n <= kKnnCap entries, *cnt, *bound and *tauf its LDS
-// state). The whole list is loaded once, 16 entries per lane.
+// active; L is the row's list of n <= CAP entries, *cnt, *bound and *tauf its LDS
+// state). The whole list is loaded once, CAP / 64 entries per lane. Keeps at most KEEP >= k.
+template <int CAP, int KEEP>
 __device__ __forceinline__ void knn_compact(uint64_t *__restrict__ L, uint32_t *cnt,
                                             uint64_t *bound, float *tauf, float *alpha, float qn,
                                             int k, int lane)
 {
-    constexpr int R = kKnnCap / 64;
+    constexpr int R = CAP / 64;
     const int n = (int)*cnt;
     uint64_t B = *bound;
     // Opaque lane index: keeps the compiler from hoisting the 16 entry offsets of the
@@ -136,7 +139,7 @@ __device__ __forceinline__ void knn_compact(uint64_t *__restrict__ L, uint32_t *
         if (keep) L[kept + __popcll(m & lt)] = e[u];
         kept += __popcll(m);
     }
-    if (kept > kKnnKeepMax) {
+    if (kept > KEEP) {
         // Many entries share the bound's key: B = the exact k-th smallest packed value.
         uint64_t lo64 = 0, hi64 = B;
         while (lo64 < hi64) {
@@ -471,15 +474,15 @@ __global__ void __launch_bounds__(kDThreads, 4) knn_kernel(
         // A list that outgrows the trigger is tightened.
         for (int rl = wave; rl < kDM; rl += kDThreads / 64)
             if (s_cnt[rl] > (uint32_t)kKnnTrigger)
-                knn_compact(Lb + (size_t)rl * kKnnCap, &s_cnt[rl], &s_bound[rl], &s_tauf[rl],
-                            &s_alpha[rl], s_qn[rl], k, lane);
+                knn_compact<kKnnCap, kKnnKeepMax>(Lb + (size_t)rl * kKnnCap, &s_cnt[rl], &s_bound[rl],
+                                                  &s_tauf[rl], &s_alpha[rl], s_qn[rl], k, lane);
         __syncthreads();
     }
     // Long lists are tightened once more (fewer entries for the merge); then the results.
     for (int rl = wave; rl < kDM; rl += kDThreads / 64)
         if (s_cnt[rl] > (uint32_t)kKnnFinal)
-            knn_compact(Lb + (size_t)rl * kKnnCap, &s_cnt[rl], &s_bound[rl], &s_tauf[rl],
-                        &s_alpha[rl], s_qn[rl], k, lane);
+            knn_compact<kKnnCap, kKnnKeepMax>(Lb + (size_t)rl * kKnnCap, &s_cnt[rl], &s_bound[rl],
+                                              &s_tauf[rl], &s_alpha[rl], s_qn[rl], k, lane);
     __syncthreads();
     if (tid < kDM) {
         cnt_out[(size_t)b * kDM + tid] = s_cnt[tid];
@@ -487,36 +490,239 @@ __global__ void __launch_bounds__(kDThreads, 4) knn_kernel(
     }
 }
 
+// ---- few queries -------------------------------------------------------------------------------
+//
+// Up to 128 query rows are bound by the database's bytes, not by products: the tiled kernel above
+// holds 128 rows whatever M is, has at most 64 blocks for them and waits for memory once per slice
+// (18 us per tile of 256 entries and 512 values). Here the query rows, 32 TM of them, are laid in
+// LDS whole as BF16 (swizzled by row, so that the 32 rows of a fragment lie on different banks) and
+// a wave takes 32 database rows at a time straight from memory in fragment layout: eight 16-byte
+// loads per lane in flight, the next eight issued before the products of the current ones (not as
+// streaming loads: a row's 128 bytes are four of them, which the first one's line must outlive). FP8
+// rows come 16 codes per lane, two steps of 16 at once, and the halves of the wave trade 8 bytes
+// each so that every product has the k order of the tiled kernel. The same instructions in the same
+// order per distance: the same bits. Blocks (one per CU at most) take contiguous ranges of tiles of
+// 256 entries and keep lists and bounds as above, with kRowsCap entries per list, so that more
+// blocks fit in the same workspace.
+// The whole search, dimension 512, k = 100, before / now: 1 query x 50,000 BF16 115 / 52 us,
+// x 500,000 BF16 (512 MB) 505 / 162, x 500,000 FP8 555 / 105; 64 queries x 500,000 BF16 615 / 209,
+// FP8 660 / 162; 128 queries x 500,000 FP8 697 / 321; 1 query x 2,000 106 / 52.
+// GMIN: no lists; the smallest key of every group of 16 entries goes to gmin [M][ng] (the sample).
+constexpr int kRowsMax = 128;                 // query rows taken here
+constexpr int kRowsLds = 131072;              // bytes of LDS for them
+constexpr int kRowsCap = 512;                 // list entries per (block, row)
+constexpr int kRowsTrigger = kRowsCap - kDN;
+constexpr int kRowsThreads = 512;
+static_assert(kRowsTrigger >= kKnnMaxKPublic && 8 * 32 == kDN, "list and tile sizes");
+
+template <bool FP8, int TM, bool GMIN>
+__global__ void __launch_bounds__(kRowsThreads, 2) knn_rows_kernel(
+    int M, int N, int K, int k, int nsplit, int nt, const uint8_t *__restrict__ Q,
+    const float *__restrict__ qs, const float *__restrict__ qn, const uint8_t *__restrict__ X,
+    const float *__restrict__ xs, const float *__restrict__ xn, const uint64_t *__restrict__ seed,
+    uint64_t *__restrict__ lists, uint32_t *__restrict__ cnt_out, uint64_t *__restrict__ bound_out,
+    uint32_t *__restrict__ gmin, int ng)
+{
+    constexpr int R = 32 * TM;
+    __shared__ __attribute__((aligned(16))) uint8_t lq[kRowsLds];
+    __shared__ uint64_t s_bound[R];
+    __shared__ uint32_t s_cnt[R];
+    __shared__ float s_tauf[R];
+    __shared__ __attribute__((aligned(16))) float s_alpha[R], s_qn[R], s_qs[R];
+    const int s = blockIdx.x, tid = threadIdx.x, lane = tid & 63;
+    const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const int half = lane >> 5, r32 = lane & 31;
+    const int t0 = (int)((int64_t)s * nt / nsplit), T = (int)((int64_t)(s + 1) * nt / nsplit) - t0;
+    uint64_t *const Lb = lists + (size_t)s * R * kRowsCap;
+    const uint32_t Kb = FP8 ? K : 2 * K;                   // bytes per row in Q and X
+    const int nch = K / 8;                                 // 16-byte chunks of a row in LDS
+    const int sw = min(15, (nch & -nch) - 1);              // chunk c of row r lies at c ^ (r & sw)
+    if (tid < R) {
+        // A row past M takes no entry: its bound is below every packed value.
+        const uint64_t B = tid >= M ? 0ull : !GMIN && seed ? seed[tid] : ~0ull;
+        s_bound[tid] = B;
+        s_cnt[tid] = 0;
+        s_tauf[tid] = bound_float(B);
+        s_qn[tid] = qn[min(tid, M - 1)];
+        s_qs[tid] = FP8 ? qs[min(tid, M - 1)] : 1.0f;
+        s_alpha[tid] = tid < M ? knn_alpha(s_qn[tid], s_tauf[tid]) : __int_as_float(0x7f800000);
+    }
+    for (int i = tid; i < R * nch; i += kRowsThreads) {
+        const int row = i / nch, c = i - row * nch;
+        const uint8_t *src = Q + (uint32_t)min(row, M - 1) * Kb + (uint32_t)c * (FP8 ? 8 : 16);
+        const u32x4 v = FP8 ? e4m3x8_to_bf16(*reinterpret_cast<const u32x2 *>(src))
+                            : *reinterpret_cast<const u32x4 *>(src);
+        *reinterpret_cast<u32x4 *>(&lq[2 * row * K + 16 * (c ^ (row & sw))]) = v;
+    }
+    // The wave's stream: tiles of 32 of its rows, K in chunks of L loads (L or 2 L steps of 16).
+    constexpr int L = 8, SL = FP8 ? 2 : 1;                 // steps per load
+    const int nl = K / (16 * SL), nck = (nl + L - 1) / L;  // loads and chunks per row
+    int fi = 0, fc = 0;                                    // tile and chunk of the next fetch
+    u32x4 b0[L], b1[L];
+    auto fetch = [&](u32x4 (&b)[L]) {
+        if (fi >= T) return;
+        const int row = min((t0 + fi) * kDN + wave * 32 + r32, N - 1);
+        const uint8_t *src = X + (uint32_t)row * Kb + (uint32_t)(32 * L * fc + 16 * half);
+        const int n = min(L, nl - fc * L);
+#pragma unroll
+        for (int l = 0; l < L; ++l)
+            if (l < n) b[l] = *reinterpret_cast<const u32x4 *>(src + 32 * l);
+        if (++fc == nck) {
+            fc = 0;
+            ++fi;
+        }
+    };
+    f32x16 acc[TM];
+    auto step = [&](int st, const bf16x8 &bb) {
+#pragma unroll
+        for (int t = 0; t < TM; ++t) {
+            const int row = 32 * t + r32;
+            const bf16x8 a = *reinterpret_cast<const bf16x8 *>(
+                &lq[2 * row * K + 16 * ((2 * st + half) ^ (row & sw))]);
+            acc[t] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a, bb, acc[t], 0, 0, 0);
+        }
+    };
+    auto compute = [&](int c, const u32x4 (&b)[L]) {
+        const int n = min(L, nl - c * L);
+#pragma unroll
+        for (int l = 0; l < L; ++l) {
+            if (l >= n) continue;                          // uniform
+            if (FP8) {
+                // Lower lanes hold step 2 j's 16 codes, upper lanes step 2 j + 1's: trade the lower
+                // lanes' second eight for the upper lanes' first.
+                const auto x = __builtin_amdgcn_permlane32_swap(b[l][0], b[l][2], false, false);
+                const auto y = __builtin_amdgcn_permlane32_swap(b[l][1], b[l][3], false, false);
+                step(2 * (c * L + l), __builtin_bit_cast(bf16x8, e4m3x8_to_bf16((u32x2){x[0], y[0]})));
+                step(2 * (c * L + l) + 1, __builtin_bit_cast(bf16x8, e4m3x8_to_bf16((u32x2){x[1], y[1]})));
+            } else {
+                step(c * L + l, __builtin_bit_cast(bf16x8, b[l]));
+            }
+        }
+    };
+    float xc = 0.f, scol = 1.f;                            // of the lane's column
+    auto begin = [&](int i) {
+        const int col = min((t0 + i) * kDN + wave * 32 + r32, N - 1);
+        xc = xn[col];
+        if (FP8) scol = xs[col];
+#pragma unroll
+        for (int t = 0; t < TM; ++t) acc[t] = (f32x16){};
+    };
+    auto epilogue = [&](int i) {
+        const int col = (t0 + i) * kDN + wave * 32 + r32;
+        if constexpr (GMIN) {
+#pragma unroll
+            for (int t = 0; t < TM; ++t)
+#pragma unroll
+                for (int r = 0; r < 16; ++r) {
+                    const int rr = 32 * t + 8 * (r >> 2) + (r & 3);
+                    if (rr >= M) continue;                 // uniform: neither half has a query here
+                    const int row = rr + 4 * half;
+                    const float dot = FP8 ? (s_qs[row] * scol) * acc[t][r] : acc[t][r];
+                    uint32_t key = col < N ? fkey((s_qn[row] + xc) - 2.0f * dot) : ~0u;
+#pragma unroll
+                    for (int o = 8; o > 0; o >>= 1) key = min(key, (uint32_t)__shfl_xor((int)key, o, 64));
+                    const int grp = ((t0 + i) * kDN + wave * 32 + (lane & 16)) >> 4;
+                    if ((lane & 15) == 0 && row < M && grp < ng) gmin[(size_t)row * ng + grp] = key;
+                }
+        } else {
+            const float beta = xc * 0.5f - 4e-7f * xc;
+#pragma unroll
+            for (int t = 0; t < TM; ++t)
+#pragma unroll
+                for (int a = 0; a < 4; ++a) {
+                    const int rl0 = 32 * t + 8 * a + 4 * half;
+                    const f32x4 al = *reinterpret_cast<const f32x4 *>(&s_alpha[rl0]);
+                    f32x4 sr = {1.0f, 1.0f, 1.0f, 1.0f};
+                    if (FP8) sr = *reinterpret_cast<const f32x4 *>(&s_qs[rl0]);
+#pragma unroll
+                    for (int c = 0; c < 4; ++c) {
+                        const float dt = FP8 ? (sr[c] * scol) * acc[t][4 * a + c] : acc[t][4 * a + c];
+                        // Without a bound yet every distance counts, an infinite one too.
+                        const bool ok = dt >= al[c] + beta || al[c] == __int_as_float(0xff800000);
+                        if (ok && col < N) {
+                            const float dv = (s_qn[rl0 + c] + xc) - 2.0f * dt;
+                            const uint64_t p = ((uint64_t)fkey(dv) << 32) | (uint32_t)col;
+                            if (dv == dv && p <= s_bound[rl0 + c]) {
+                                const uint32_t pos = atomicAdd(&s_cnt[rl0 + c], 1u);
+                                Lb[(uint32_t)(rl0 + c) * (uint32_t)kRowsCap + pos] = p;
+                            }
+                        }
+                    }
+                }
+        }
+    };
+    auto tighten = [&](uint32_t above) {
+        for (int rl = wave; rl < min(R, M); rl += kRowsThreads / 64)
+            if (s_cnt[rl] > above)
+                knn_compact<kRowsCap, kRowsTrigger>(Lb + (size_t)rl * kRowsCap, &s_cnt[rl], &s_bound[rl],
+                                                    &s_tauf[rl], &s_alpha[rl], s_qn[rl], k, lane);
+    };
+    fetch(b0);
+    __syncthreads();
+    int c = 0, i = 0;
+    auto advance = [&](const u32x4 (&b)[L]) {
+        if (c == 0) begin(i);
+        compute(c, b);
+        if (++c < nck) return;
+        c = 0;
+        epilogue(i);
+        ++i;
+        if constexpr (!GMIN) {
+            __syncthreads();                               // every append of the tile is done
+            tighten(kRowsTrigger);
+            __syncthreads();
+        }
+    };
+    while (i < T) {                                        // the same count of barriers in every wave
+        fetch(b1);
+        advance(b0);
+        if (i >= T) break;
+        fetch(b0);
+        advance(b1);
+    }
+    if constexpr (!GMIN) {
+        // Lists of more than k entries are tightened once more (fewer for the merge).
+        tighten((uint32_t)k);
+        __syncthreads();
+        if (tid < R) {
+            cnt_out[(size_t)s * R + tid] = s_cnt[tid];
+            bound_out[(size_t)s * R + tid] = s_bound[tid];
+        }
+    }
+}
+
 constexpr int kMergeThreads = 256;
 constexpr int kDirectPairs = 4;      // (query, candidate) pairs per wave of knn_direct_kernel
 constexpr int kMergeCap = 8192;     // gathered candidates held in LDS
 
-// One block per query row: the k smallest packed values over the row's split lists.
+// One block per query row: the k smallest packed values over the row's split lists of `cap` entries,
+// `rows` lists per block of the pass.
 __global__ void __launch_bounds__(kMergeThreads) knn_merge_kernel(
-    int k, int mt, int nsplit, const uint64_t *__restrict__ lists,
+    int k, int mt, int nsplit, int rows, int cap, const uint64_t *__restrict__ lists,
     const uint32_t *__restrict__ cnt, const uint64_t *__restrict__ bound, int32_t *__restrict__ idx,
     float *__restrict__ dout)
 {
     __shared__ uint64_t buf[kMergeCap];
     __shared__ uint64_t win[kKnnMaxK];
     __shared__ uint32_t hist[256];
-    __shared__ uint32_t s_blk[kKnnMaxSplit], s_n[kKnnMaxSplit], s_off[kKnnMaxSplit + 1];
+    __shared__ uint32_t s_blk[kMergeThreads], s_off[kMergeThreads + 1], s_wn[kMergeThreads / 64];
+    __shared__ uint64_t s_wB[kMergeThreads / 64];
     __shared__ uint64_t s_B;
     __shared__ uint32_t s_gather, s_win, s_sel[3];
     __shared__ unsigned long long s_lo, s_hi;
     const int q = blockIdx.x, tid = threadIdx.x, lane = tid & 63;
-    const int m = q / kDM, r = q % kDM;
-    // The first wave: lane s reads split s's list length and bound; B* is their smallest bound
-    // and the lists are laid end to end at the exclusive prefix sums of the lengths.
-    if (tid < 64) {
+    const int m = q / rows, r = q % rows;
+    // Thread s reads split s's list length and bound; B* is their smallest bound and the lists are
+    // laid end to end at the exclusive prefix sums of the lengths.
+    {
         const int s = tid;
         uint32_t n_s = 0;
         uint64_t B = ~0ull;
         if (s < nsplit) {
             const uint32_t blk = (uint32_t)(kXcds * (m + mt * (s / kXcds)) + s % kXcds);
             s_blk[s] = blk;
-            n_s = cnt[(size_t)blk * kDM + r];
-            B = bound[(size_t)blk * kDM + r];
+            n_s = cnt[(size_t)blk * rows + r];
+            B = bound[(size_t)blk * rows + r];
         }
         uint32_t incl = n_s;
 #pragma unroll
@@ -526,10 +732,14 @@ __global__ void __launch_bounds__(kMergeThreads) knn_merge_kernel(
             const uint64_t b2 = __shfl_xor(B, o, 64);
             B = b2 < B ? b2 : B;
         }
-        if (s < nsplit) {
-            s_n[s] = n_s;
-            s_off[s] = incl - n_s;
+        if (lane == 63) s_wn[tid >> 6] = incl;
+        if (lane == 0) s_wB[tid >> 6] = B;
+        __syncthreads();
+        for (int w = 0; w < kMergeThreads / 64; ++w) {
+            if (w < tid >> 6) incl += s_wn[w];
+            B = s_wB[w] < B ? s_wB[w] : B;
         }
+        if (s < nsplit) s_off[s] = incl - n_s;
         if (s == nsplit - 1) s_off[nsplit] = incl;
         if (s == 0) {
             s_B = B;
@@ -550,23 +760,17 @@ __global__ void __launch_bounds__(kMergeThreads) knn_merge_kernel(
             if (s_off[mid] <= f) lo = mid;
             else hi = mid - 1;
         }
-        return lists[((size_t)s_blk[lo] * kDM + r) * kKnnCap + (f - s_off[lo])];
+        return lists[((size_t)s_blk[lo] * rows + r) * cap + (f - s_off[lo])];
     };
     // Gather the entries <= B* into LDS while they fit; four loads in flight per thread.
-    // Their smallest and largest values fix the bits all of them share. A thread's entries
-    // only move forward through the lists, so it keeps the split of its last one.
+    // Their smallest and largest values fix the bits all of them share.
     uint64_t lo_t = ~0ull, hi_t = 0;
-    int sp = 0;
     for (uint32_t f0 = 0; f0 < n_all; f0 += 4 * kMergeThreads) {
         uint64_t e[4];
 #pragma unroll
         for (int u = 0; u < 4; ++u) {
             const uint32_t f = f0 + u * kMergeThreads + tid;
-            e[u] = ~0ull;
-            if (f < n_all) {
-                while (s_off[sp + 1] <= f) ++sp;      // s_off[nsplit] = n_all > f stops it
-                e[u] = lists[((size_t)s_blk[sp] * kDM + r) * kKnnCap + (f - s_off[sp])];
-            }
+            e[u] = f < n_all ? entry(f) : ~0ull;
         }
 #pragma unroll
         for (int u = 0; u < 4; ++u) {
@@ -820,20 +1024,33 @@ __global__ void __launch_bounds__(256) knn_seed_kernel(int M, int ng, int k,
     uint32_t v[R];
 #pragma unroll
     for (int u = 0; u < R; ++u) {
-        const int g = u * 64 + lane;
-        v[u] = g < ng ? gmin[(size_t)row * ng + g] : ~0u;
+        const int g = u * 64 + lane;                  // all loads in flight at once
+        const uint32_t x = gmin[(size_t)row * ng + min(g, ng - 1)];
+        v[u] = g < ng ? x : ~0u;
     }
-    // The smallest key with at least k minima <= it (bisection; ballot counts).
-    uint32_t lo = 0, hi = ~0u;
+    // A key with at least k minima <= it, and not many more (any such key is a bound: the search
+    // stops early), between the smallest and the largest of them: bisection, ballot counts.
+    uint32_t lo = ~0u, hi = 0u;
+#pragma unroll
+    for (int u = 0; u < R; ++u) {
+        lo = min(lo, v[u]);
+        hi = max(hi, u * 64 + lane < ng ? v[u] : 0u);
+    }
+#pragma unroll
+    for (int o = 32; o > 0; o >>= 1) {
+        lo = min(lo, (uint32_t)__shfl_xor((int)lo, o, 64));
+        hi = max(hi, (uint32_t)__shfl_xor((int)hi, o, 64));
+    }
     while (lo < hi) {
         const uint32_t mid = lo + ((hi - lo) >> 1);
         int c = 0;
 #pragma unroll
-        for (int u = 0; u < R; ++u)
-            if (u * 64 < ng) c += __popcll(__ballot(v[u] <= mid));
+        for (int u = 0; u < R; ++u) c += __popcll(__ballot(v[u] <= mid));
         if (c >= k) hi = mid;
         else lo = mid + 1;
+        if (c >= k && c <= k + k / 16) break;
     }
+    lo = hi;
     if (lane == 0) seed[row] = lo == ~0u ? ~0ull : (((uint64_t)lo << 32) | 0xffffffffull);
 }
 
@@ -846,13 +1063,46 @@ static int knn_sample_cols(int N)
     return N >= 2 * kSample ? kSample : 0;
 }
 
+// Shape of the pass over the database.
+struct KnnPlan {
+    int tm, mt, nsplit, rows, cap;     // tm: 32-row tiles of knn_rows_kernel, 0: knn_kernel
+    // Per (block, row) a list, its length and its bound: three arrays end to end.
+    size_t lists() const { return (size_t)mt * nsplit * rows; }
+    size_t o_cnt() const { return align_up(lists() * cap * 8, kAlign); }
+    size_t o_bound() const { return o_cnt() + align_up(lists() * 4, kAlign); }
+    size_t bytes() const { return o_bound() + align_up(lists() * 8, kAlign); }
+};
+// Bytes kept for them: what the tiled kernel needs.
+static size_t knn_list_bytes(int M, int N)
+{
+    return KnnPlan{0, (M + kDM - 1) / kDM, knn_splits(M, N), kDM, kKnnCap}.bytes();
+}
+static KnnPlan knn_plan(int M, int N, int K, int cus)
+{
+    const int nt = (N + kDN - 1) / kDN, splits = knn_splits(M, N);
+    KnnPlan p{0, (M + kDM - 1) / kDM, splits, kDM, kKnnCap};
+    // knn_rows_kernel where all queries' rows fit its LDS (a multiple of 16 values in BF16, of 64 in
+    // FP8: whole loads). With 128 rows the workspace's lists still allow 127 blocks: 128 queries x
+    // 50,000 92 us against 131, x 500,000 FP8 321 against 697. More rows would be read by several
+    // blocks each, as the tiled kernel's are, without its sharing of them in LDS.
+    const int tm = M <= 32 ? 1 : M <= 64 ? 2 : 4;
+    if (M <= kRowsMax && 64 * tm * K <= kRowsLds) {
+        p.tm = tm;
+        p.mt = 1;
+        p.rows = 32 * tm;
+        p.cap = kRowsCap;
+        // A block per CU, in the workspace of the tiled kernel's lists; without a sample's bound
+        // three tiles per block, so that the merge gets fewer than its LDS holds.
+        p.nsplit = std::min({kMergeThreads, cus, knn_sample_cols(N) ? nt : (nt + 2) / 3});
+        while (p.nsplit > 1 && p.bytes() > knn_list_bytes(M, N)) --p.nsplit;
+    }
+    return p;
+}
+
 size_t knn_ws_bytes(int M, int N)
 {
-    const size_t G = (size_t)((M + kDM - 1) / kDM) * knn_splits(M, N);
     const size_t S = (size_t)knn_sample_cols(N);
-    return align_up(G * kDM * kKnnCap * 8, kAlign) + align_up(G * kDM * 4, kAlign) +
-           align_up(G * kDM * 8, kAlign) + align_up((size_t)M * 8, kAlign) +
-           align_up((size_t)M * (S / 16) * 4, kAlign);
+    return knn_list_bytes(M, N) + align_up((size_t)M * 8, kAlign) + align_up((size_t)M * (S / 16) * 4, kAlign);
 }
 
 template <bool FP8, bool TAIL, bool SEEDB>
@@ -867,29 +1117,51 @@ static hipError_t knn_pass(int M, int N, int K, int k, int nsplit, const uint8_t
     return hipGetLastError();
 }
 
+template <bool FP8, bool GMIN>
+static hipError_t knn_rows(const KnnPlan &p, int M, int N, int K, int k, const uint8_t *q, const float *qs,
+                           const float *qn, const uint8_t *x, const float *xs, const float *xn,
+                           const uint64_t *seed, uint64_t *lists, uint32_t *cnt, uint64_t *bound,
+                           uint32_t *gmin, hipStream_t s)
+{
+    const int nt = (N + kDN - 1) / kDN, blocks = GMIN ? nt : p.nsplit;
+    const auto kernel = p.tm == 1           ? knn_rows_kernel<FP8, 1, GMIN>
+                        : p.tm == 2 || GMIN ? knn_rows_kernel<FP8, 2, GMIN>
+                                            : knn_rows_kernel<FP8, 4, false>;
+    hipLaunchKernelGGL(kernel, dim3((unsigned)blocks), dim3(kRowsThreads), 0, s, M, N, K, k, blocks, nt,
+                       q, qs, qn, x, xs, xn, seed, lists, cnt, bound, gmin, N / 16);
+    return hipGetLastError();
+}
+
 hipError_t launch_knn(bool fp8, int M, int N, int K, const void *Q, const float *qs,
                       const float *qn, const void *X, const float *xs, const float *xn, int k,
                       bool direct, int32_t *idx, float *d, void *ws, hipStream_t s)
 {
-    const int mt = (M + kDM - 1) / kDM, nsplit = knn_splits(M, N);
-    const size_t G = (size_t)mt * nsplit;
-    uint64_t *lists = static_cast<uint64_t *>(ws);
-    char *p = static_cast<char *>(ws) + align_up(G * kDM * kKnnCap * 8, kAlign);
-    uint32_t *cnt = reinterpret_cast<uint32_t *>(p);
-    p += align_up(G * kDM * 4, kAlign);
-    uint64_t *bound = reinterpret_cast<uint64_t *>(p);
-    p += align_up(G * kDM * 8, kAlign);
+    int dev = 0, cus = 0;
+    hipError_t e = hipGetDevice(&dev);
+    if (e == hipSuccess) e = hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev);
+    if (e != hipSuccess) return e;
+    const KnnPlan plan = knn_plan(M, N, K, cus);
+    const int mt = plan.mt, nsplit = plan.nsplit;
+    char *p = static_cast<char *>(ws);
+    uint64_t *lists = reinterpret_cast<uint64_t *>(p);
+    uint32_t *cnt = reinterpret_cast<uint32_t *>(p + plan.o_cnt());
+    uint64_t *bound = reinterpret_cast<uint64_t *>(p + plan.o_bound());
+    p += knn_list_bytes(M, N);
     uint64_t *seed = reinterpret_cast<uint64_t *>(p);
     p += align_up((size_t)M * 8, kAlign);
     uint32_t *gmin = reinterpret_cast<uint32_t *>(p);
     const auto *q = static_cast<const uint8_t *>(Q);
     const auto *x = static_cast<const uint8_t *>(X);
     const bool tail = !fp8 && (2 * K) % kDSlice;
-    hipError_t e = hipSuccess;
     const int S = knn_sample_cols(N);
     if (S) {
         // Group minima of the first S entries (no distances written), then the seeds.
-        if (fp8)
+        if (plan.tm == 1 || plan.tm == 2)         // four row tiles' keys would spill
+            e = fp8 ? knn_rows<true, true>(plan, M, S, K, k, q, qs, qn, x, xs, xn, nullptr, nullptr, nullptr,
+                                           nullptr, gmin, s)
+                    : knn_rows<false, true>(plan, M, S, K, k, q, nullptr, qn, x, nullptr, xn, nullptr,
+                                            nullptr, nullptr, nullptr, gmin, s);
+        else if (fp8)
             e = launch_dist_fp8(M, S, K, q, qs, qn, x, xs, xn, nullptr, 0, gmin, s);
         else
             e = launch_dist_bf16(M, S, K, static_cast<const uint16_t *>(Q), qn,
@@ -899,6 +1171,14 @@ hipError_t launch_knn(bool fp8, int M, int N, int K, const void *Q, const float 
                            S / 16, k, gmin, seed);
         e = hipGetLastError();
         if (e != hipSuccess) return e;
+    }
+    if (plan.tm) {
+        const uint64_t *sd = S ? seed : nullptr;
+        e = fp8 ? knn_rows<true, false>(plan, M, N, K, k, q, qs, qn, x, xs, xn, sd, lists, cnt, bound,
+                                        nullptr, s)
+                : knn_rows<false, false>(plan, M, N, K, k, q, nullptr, qn, x, nullptr, xn, sd, lists, cnt,
+                                         bound, nullptr, s);
+    } else if (S) {
         if (fp8)
             e = knn_pass<true, false, false>(M, N, K, k, nsplit, q, qs, qn, x, xs, xn, seed,
                                              lists, cnt, bound, s);
@@ -921,7 +1201,7 @@ hipError_t launch_knn(bool fp8, int M, int N, int K, const void *Q, const float 
     }
     if (e != hipSuccess) return e;
     hipLaunchKernelGGL(knn_merge_kernel, dim3((unsigned)M), dim3(kMergeThreads), 0, s, k, mt,
-                       nsplit, lists, cnt, bound, idx, d);
+                       nsplit, plan.rows, plan.cap, lists, cnt, bound, idx, d);
     e = hipGetLastError();
     if (e != hipSuccess || !direct) return e;
     const int64_t pairs = (int64_t)M * k;

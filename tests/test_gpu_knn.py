@@ -118,3 +118,29 @@ def test_knn_workload_shapes(fmt, N):
     del Xf
     say(f"knn workload fmt {fmt}: 1024 x {N}")
     _check_equal(Q, X, 100)
+
+
+@pytest.mark.parametrize("fmt,M,N,dim,ks", [
+    (0, 1, 1, 16, (1,)), (1, 1, 256, 64, (1, 256)), (0, 32, 257, 16, (1, 200)),    # one tile and one row more
+    (0, 33, 2_000, 512, (1, 256)), (1, 64, 3_333, 1024, (100,)),                   # 64-row tile, its widest rows
+    (0, 65, 3_000, 64, (10,)), (1, 128, 33_000, 512, (256,)), (0, 100, 90_000, 16, (100,)),  # 128-row tile
+    (0, 129, 3_000, 64, (10,)), (0, 33, 1_500, 1040, (10,)),                       # back to the tiled kernel
+    (0, 32, 2_100, 2048, (256,)), (1, 31, 40_001, 1024, (1, 256)),                 # 32-row tile, its widest rows
+    (0, 2, 32_769, 144, (256,)), (1, 64, 140_000, 64, (256,)), (0, 1, 70_000, 80, (1, 100)),
+])
+def test_knn_few_queries(fmt, M, N, dim, ks):
+    """The kernel for up to 128 queries at the edges of its row tiles, its LDS (32 rows of 2,048
+    values, 64 of 1,024, 128 of 512), chunks of loads with a rest and lists that are tightened, with and without
+    the sampled bound, on rows with exact ties and an infinite and a NaN distance."""
+    need_gpu()
+    from paper_2205_04550_amd import binding as b
+    g = torch.Generator(device="cuda").manual_seed(M + N + dim)
+    base = torch.randn(min(N, 997), dim, generator=g, device="cuda")
+    Xf = base.repeat(N // len(base) + 1, 1)[:N].contiguous()
+    Qf = torch.randn(M, dim, generator=g, device="cuda")
+    Q, X = b.Latents(Qf, fmt), b.Latents(Xf, fmt)
+    if N > 300:
+        X.sq[299], X.sq[123] = float("inf"), float("nan")
+    for k in ks:
+        say(f"knn few queries fmt {fmt} {M} x {N} x {dim} k = {k}")
+        _check_equal(Q, X, k)
