@@ -173,6 +173,10 @@ __device__ __forceinline__ void knn_compact(uint64_t *__restrict__ L, uint32_t *
 // database tiles. Split s takes database tiles [s nt / nsplit, (s + 1) nt / nsplit).
 // Outputs per (block, row): the list lists[b][row][0 .. cnt), cnt, and the bound.
 // SEEDB: no bound is given; the block's first tile provides one (small databases).
+// Bound by LDS and vector instructions, not by the products: 1,024 queries x 500,000 FP8 latents of
+// 512 values are 300 us of products at the rate the matrix cores sustain. FP8 as codes in LDS, 64
+// values per slice: 750 us; converted to BF16 before they are staged, 32 values per slice (LDS busy
+// 72 % of the time): 880; query rows as codes too (four conversions more per product): 815.
 template <bool FP8, bool TAIL, bool SEEDB>
 __global__ void __launch_bounds__(kDThreads, 4) knn_kernel(
     int M, int N, int K, int k, int mt, int nsplit, int nt, const uint8_t *__restrict__ Q,
@@ -180,7 +184,7 @@ __global__ void __launch_bounds__(kDThreads, 4) knn_kernel(
     const float *__restrict__ xs, const float *__restrict__ xn, const uint64_t *__restrict__ seed,
     uint64_t *__restrict__ lists, uint32_t *__restrict__ cnt_out, uint64_t *__restrict__ bound_out)
 {
-    __shared__ __attribute__((aligned(16))) uint8_t lds[2][(kDM + kDN) * kDRow];
+    __shared__ __attribute__((aligned(16))) uint8_t lds[2][FP8 ? kDM * 128 + kDN * 72 : (kDM + kDN) * kDRow];
     __shared__ __attribute__((aligned(16))) float tv[2][2][kDM + kDN];
     __shared__ uint64_t s_bound[kDM];
     __shared__ uint32_t s_cnt[kDM];
@@ -208,7 +212,12 @@ __global__ void __launch_bounds__(kDThreads, 4) knn_kernel(
         s_seed[tid] = 0;
     }
     const int Kb = FP8 ? K : 2 * K;                        // bytes per row in Q and X
-    const int nslices = (2 * K + kDSlice - 1) / kDSlice;   // 32 values per slice
+    // Slices of 64 bytes per row: 32 BF16 or 64 FP8 values. FP8 database rows stay codes in LDS (half
+    // the bytes to write and read) and are converted as fragments are read, the fewer query rows
+    // before they are written; database rows of 72 bytes and query
+    // rows with their 16-byte chunks turned by the row put the reads of 32 rows on all 64 banks.
+    constexpr int QS = FP8 ? 128 : kDRow, RS = FP8 ? 72 : kDRow;
+    const int nslices = (Kb + kDSlice - 1) / kDSlice;
     const int wm = wave >> 2, wn = wave & 3;
     const int half = lane >> 5, r32 = lane & 31;
     const int frow = tid >> 2, fpart = (tid & 3) * 16;
@@ -225,18 +234,11 @@ __global__ void __launch_bounds__(kDThreads, 4) knn_kernel(
             ox[0] = (uint32_t)min(n0 + frow, N - 1) * (uint32_t)Kb;
             ox[1] = (uint32_t)min(n0 + kDM + frow, N - 1) * (uint32_t)Kb;
         }
-        const uint32_t kb = FP8 ? (uint32_t)(sl * (kDSlice / 2) + (fpart >> 1))
-                                : (uint32_t)(sl * kDSlice + fpart);
+        const uint32_t kb = (uint32_t)(sl * kDSlice + fpart);
         if (!TAIL || (int)kb < Kb) {
-            if (FP8) {
-                dst[0] = e4m3x8_to_bf16(*reinterpret_cast<const u32x2 *>(Q + oq + kb));
-                dst[1] = e4m3x8_to_bf16(*reinterpret_cast<const u32x2 *>(X + ox[0] + kb));
-                dst[2] = e4m3x8_to_bf16(*reinterpret_cast<const u32x2 *>(X + ox[1] + kb));
-            } else {
-                dst[0] = *reinterpret_cast<const u32x4 *>(Q + oq + kb);
-                dst[1] = *reinterpret_cast<const u32x4 *>(X + ox[0] + kb);
-                dst[2] = *reinterpret_cast<const u32x4 *>(X + ox[1] + kb);
-            }
+            dst[0] = *reinterpret_cast<const u32x4 *>(Q + oq + kb);
+            dst[1] = *reinterpret_cast<const u32x4 *>(X + ox[0] + kb);
+            dst[2] = *reinterpret_cast<const u32x4 *>(X + ox[1] + kb);
         } else {
             dst[0] = dst[1] = dst[2] = (u32x4){0u, 0u, 0u, 0u};
         }
@@ -254,9 +256,24 @@ __global__ void __launch_bounds__(kDThreads, 4) knn_kernel(
     };
     auto stash = [&](int i, int sl, int buf, const u32x4 (&src)[3], const float (&sv)[2]) {
         uint8_t *Ls = &lds[buf][0];
+        if (FP8) {
+            uint8_t *d = &Ls[frow * QS];
+            const int c = (2 * (tid & 3)) ^ (frow >> 1 & 7);
+            *reinterpret_cast<u32x4 *>(d + 16 * c) = e4m3x8_to_bf16((u32x2){src[0][0], src[0][1]});
+            *reinterpret_cast<u32x4 *>(d + 16 * (c ^ 1)) = e4m3x8_to_bf16((u32x2){src[0][2], src[0][3]});
+        } else {
+            *reinterpret_cast<u32x4 *>(&Ls[frow * QS + fpart]) = src[0];
+        }
 #pragma unroll
-        for (int j = 0; j < 3; ++j)
-            *reinterpret_cast<u32x4 *>(&Ls[(j * kDM + frow) * kDRow + fpart]) = src[j];
+        for (int j = 1; j < 3; ++j) {
+            uint8_t *d = &Ls[kDM * QS + ((j - 1) * kDM + frow) * RS + fpart];
+            if (FP8) {
+                *reinterpret_cast<u32x2 *>(d) = (u32x2){src[j][0], src[j][1]};
+                *reinterpret_cast<u32x2 *>(d + 8) = (u32x2){src[j][2], src[j][3]};
+            } else {
+                *reinterpret_cast<u32x4 *>(d) = src[j];
+            }
+        }
         if (sl == 0 && tid < kDM + kDN) {
             tv[i & 1][0][tid] = sv[0];
             if (FP8) tv[i & 1][1][tid] = sv[1];
@@ -266,16 +283,21 @@ __global__ void __launch_bounds__(kDThreads, 4) knn_kernel(
     // The first slice of a tile starts its products from zero (not from the accumulators),
     // so the accumulators are free between a tile's epilogue and its successor's first slice.
     auto compute = [&](int buf, bool first) {
-        const uint8_t *A = &lds[buf][0], *Bm = &lds[buf][kDM * kDRow];
+        const uint8_t *A = &lds[buf][0], *Bm = &lds[buf][kDM * QS];
+        auto fragment = [&](const uint8_t *row, int st) {
+            return FP8 ? __builtin_bit_cast(bf16x8, e4m3x8_to_bf16(*reinterpret_cast<const u32x2 *>(
+                                                        row + st * 16 + half * 8)))
+                       : *reinterpret_cast<const bf16x8 *>(row + st * 32 + half * 16);
+        };
 #pragma unroll
-        for (int st = 0; st < 2; ++st) {
+        for (int st = 0; st < (FP8 ? 4 : 2); ++st) {
             bf16x8 a[2], bb[2];
 #pragma unroll
             for (int i = 0; i < 2; ++i) {
                 a[i] = *reinterpret_cast<const bf16x8 *>(
-                    A + (wm * 64 + i * 32 + r32) * kDRow + st * 32 + half * 16);
-                bb[i] = *reinterpret_cast<const bf16x8 *>(
-                    Bm + (wn * 64 + i * 32 + r32) * kDRow + st * 32 + half * 16);
+                    A + (wm * 64 + i * 32 + r32) * QS +
+                    (FP8 ? 16 * ((2 * st + half) ^ (r32 >> 1 & 7)) : st * 32 + half * 16));
+                bb[i] = fragment(Bm + (wn * 64 + i * 32 + r32) * RS, st);
             }
 #pragma unroll
             for (int i = 0; i < 2; ++i)
@@ -763,14 +785,26 @@ __global__ void __launch_bounds__(kMergeThreads) knn_merge_kernel(
         return lists[((size_t)s_blk[lo] * rows + r) * cap + (f - s_off[lo])];
     };
     // Gather the entries <= B* into LDS while they fit; four loads in flight per thread.
-    // Their smallest and largest values fix the bits all of them share.
+    // Their smallest and largest values fix the bits all of them share. A thread's entries
+    // only move forward through the lists: up to 64 lists it walks on from its last one, through
+    // more (most of them short) it searches (1,024 queries, 64 lists: 83 us against 88; one query,
+    // 196 lists: 17 us; by lists, a wave to four of them, 32 us).
     uint64_t lo_t = ~0ull, hi_t = 0;
+    int sp = 0;
     for (uint32_t f0 = 0; f0 < n_all; f0 += 4 * kMergeThreads) {
         uint64_t e[4];
 #pragma unroll
         for (int u = 0; u < 4; ++u) {
             const uint32_t f = f0 + u * kMergeThreads + tid;
-            e[u] = f < n_all ? entry(f) : ~0ull;
+            e[u] = ~0ull;
+            if (f < n_all) {
+                if (nsplit <= kKnnMaxSplit) {
+                    while (s_off[sp + 1] <= f) ++sp;      // s_off[nsplit] = n_all > f stops it
+                    e[u] = lists[((size_t)s_blk[sp] * rows + r) * cap + (f - s_off[sp])];
+                } else {
+                    e[u] = entry(f);
+                }
+            }
         }
 #pragma unroll
         for (int u = 0; u < 4; ++u) {
