@@ -157,11 +157,16 @@ __device__ __forceinline__ int row_div(int r, int nyr, float inv)
 }
 
 // One wave per entry, four entries per 256-thread block. Lanes sweep the
-// flattened rows of (entry box n query box); x-rows of 128 voxels (nxw == 4)
-// are single 16-byte loads, other widths go word by word.
+// flattened rows of (entry box n query box). NXW = 1 .. 4: rows of so many words are read as
+// 16 bytes per lane and plane (4, 2, 1, 1 rows of a slice; words past the slice's last row are
+// taken out of the query's side), U groups per pass, by buffer loads that a lane without a row
+// turns off with its offset, so that all 4 U loads of a pass are in flight at once. NXW = 0: any
+// width, a word at a time. Whole query, 20,000 entries, a word at a time / now: 96 x 112 x 77
+// 103 / 63 us, 64 x 100 x 90 64 / 50, 32 x 60 x 120 51 / 46. 50,000 entries of 128^3 are bound by
+// the rows' bytes: 247 us, with loads under conditions too.
 constexpr int kZStageScan = 128;   // z-slices of the entry's row ranges a wave stages in LDS
 
-template <bool V4, int U>
+template <int NXW, int U>
 __global__ void __launch_bounds__(256) box_scan_kernel(const uint32_t *__restrict__ planes, int Wp,
                                                        int nxw, int ny, int nz,
                                                        const int32_t *__restrict__ box,
@@ -173,7 +178,8 @@ __global__ void __launch_bounds__(256) box_scan_kernel(const uint32_t *__restric
                                                        uint32_t *__restrict__ inter)
 {
     const int lane = threadIdx.x & 63;
-    const int64_t e = (int64_t)blockIdx.x * 4 + (threadIdx.x >> 6);
+    const int wv = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    const int64_t e = (int64_t)blockIdx.x * 4 + wv;
     if (e >= n) return;   // a whole wave leaves; the kernel has no block barrier
     const int32_t *b = box + 4 * e, *tb = tbox + 4 * e;
     const int z0 = max(b[0], qbox[0]), z1 = min(b[1], qbox[1]);
@@ -188,7 +194,6 @@ __global__ void __launch_bounds__(256) box_scan_kernel(const uint32_t *__restric
     // The entry's per-slice y-ranges of its FLAIR and T1Gd rows over the slices swept, in this
     // wave's part of LDS (a box deeper than kZStageScan slices goes by the boxes alone).
     __shared__ uint2 s_zr[4][kZStageScan];
-    const int wv = threadIdx.x >> 6;
     const bool zr_ok = nr > 0 && z1 - z0 <= kZStageScan;
     if (zr_ok) {
         for (int i = lane; i < z1 - z0; i += 64)
@@ -197,38 +202,53 @@ __global__ void __launch_bounds__(256) box_scan_kernel(const uint32_t *__restric
         __builtin_amdgcn_wave_barrier();
         __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
     }
-    auto in_range = [&](int z, int y, bool t1gd) {
+    // Rows [y, y + G) of slice z meet the slice's FLAIR (T1Gd) rows.
+    auto in_range = [&](int z, int y, int G, bool t1gd) {
         if (!zr_ok) return true;
         const uint2 rg = s_zr[wv][z - z0];
         const uint32_t v = t1gd ? rg.y : rg.x;
-        return y >= (int)(v & 0xffffu) && y < (int)(v >> 16);
+        return y + G > (int)(v & 0xffffu) && y < (int)(v >> 16);
     };
     const uint32_t *D0 = planes + e * 2 * (int64_t)Wp, *D1 = D0 + Wp;
     const uint32_t *Q0 = qpack, *Q1 = qpack + Wp;
     uint32_t c0 = 0, c1 = 0;
-    if (V4) {
-        for (int r0 = 0; r0 < nr; r0 += 64 * U) {
+    if constexpr (NXW > 0) {
+        constexpr int G = NXW == 1 ? 4 : NXW == 2 ? 2 : 1;
+        const int ngr = nr > 0 ? (nyr + G - 1) / G : 0, ng = nr > 0 ? (z1 - z0) * ngr : 0;
+        const float ginv = G == 1 ? inv : ngr > 0 ? 1.0f / (float)ngr : 0.0f;
+        const uint32_t rec = 8u * (uint32_t)Wp, plane = 4u * (uint32_t)Wp;
+        const __amdgpu_buffer_rsrc_t dr = buffer_of(D0, rec), qr = buffer_of(Q0, rec);
+        for (int r0 = 0; r0 < ng; r0 += 64 * U) {
             u32x4 d0[U], d1[U], q0[U], q1[U];
+            uint32_t w0[U], w1[U], base[U];             // the group's words and the first one read
 #pragma unroll
             for (int u = 0; u < U; ++u) {
-                const int r = r0 + u * 64 + lane;
-                d0[u] = d1[u] = q0[u] = q1[u] = (u32x4){0u, 0u, 0u, 0u};
-                if (r < nr) {
-                    const int zr = row_div(r, nyr, inv);
-                    const int z = z0 + zr, y = y0 + r - zr * nyr;
-                    const int64_t base = ((int64_t)z * ny + y) * 4;
-                    if (in_range(z, y, false)) {
-                        d0[u] = load_stream(reinterpret_cast<const u32x4 *>(D0 + base));
-                        q0[u] = *reinterpret_cast<const u32x4 *>(Q0 + base);
-                    }
-                    if (z >= tz0 && z < tz1 && y >= ty0 && y < ty1 && in_range(z, y, true)) {
-                        d1[u] = load_stream(reinterpret_cast<const u32x4 *>(D1 + base));
-                        q1[u] = *reinterpret_cast<const u32x4 *>(Q1 + base);
-                    }
-                }
+                const int r = min(r0 + u * 64 + lane, ng - 1);
+                const int zr = row_div(r, ngr, ginv);
+                const int z = z0 + zr, y = y0 + (r - zr * ngr) * G;
+                w0[u] = (uint32_t)((z * ny + y) * NXW);
+                w1[u] = (uint32_t)((z * ny + min(y + G, y1)) * NXW);
+                base[u] = min(w0[u], (uint32_t)Wp - 4u);
+                const bool live = r0 + u * 64 + lane < ng;
+                const bool in0 = live & in_range(z, y, G, false);
+                const bool in1 = live & (z >= tz0) & (z < tz1) & (y + G > ty0) & (y < ty1) &
+                                 in_range(z, y, G, true);
+                const uint32_t o0 = in0 ? 4u * base[u] : kBufferOut, o1 = in1 ? 4u * base[u] : kBufferOut;
+                d0[u] = buffer_b128<2>(dr, o0, 0);
+                d1[u] = buffer_b128<2>(dr, o1, plane);
+                q0[u] = buffer_b128<0>(qr, o0, 0);
+                q1[u] = buffer_b128<0>(qr, o1, plane);
             }
 #pragma unroll
             for (int u = 0; u < U; ++u) {
+                if (NXW < 4) {
+#pragma unroll
+                    for (int w = 0; w < 4; ++w) {
+                        const bool in = base[u] + w >= w0[u] && base[u] + w < w1[u];
+                        q0[u][w] = in ? q0[u][w] : 0u;
+                        q1[u][w] = in ? q1[u][w] : 0u;
+                    }
+                }
                 c0 += popc_and4(q0[u], d0[u]);
                 c1 += popc_and4(q1[u], d1[u]);
             }
@@ -240,8 +260,8 @@ __global__ void __launch_bounds__(256) box_scan_kernel(const uint32_t *__restric
             const int zr = row_div(r, nyr, inv);
             const int z = z0 + zr, y = y0 + r - zr * nyr;
             const int64_t base = ((int64_t)z * ny + y) * nxw + w;
-            if (in_range(z, y, false)) c0 += popc(Q0[base] & D0[base]);
-            if (z >= tz0 && z < tz1 && y >= ty0 && y < ty1 && in_range(z, y, true))
+            if (in_range(z, y, 1, false)) c0 += popc(Q0[base] & D0[base]);
+            if (z >= tz0 && z < tz1 && y >= ty0 && y < ty1 && in_range(z, y, 1, true))
                 c1 += popc(Q1[base] & D1[base]);
         }
     }
@@ -258,14 +278,13 @@ hipError_t launch_box_scan(const db_t *db, int64_t n, const uint32_t *qpack, con
 {
     const Geometry &g = db->g;
     const int64_t blocks = (n + 3) / 4;
-    if (g.nxw == 4)
-        hipLaunchKernelGGL((box_scan_kernel<true, 4>), dim3((unsigned)blocks), dim3(256), 0, s,
-                           db->planes, g.Wp, g.nxw, g.ny, g.nz, db->box, db->tbox, db->zrange,
-                           qpack, qbox, qtbox, n, inter);
-    else
-        hipLaunchKernelGGL((box_scan_kernel<false, 1>), dim3((unsigned)blocks), dim3(256), 0, s,
-                           db->planes, g.Wp, g.nxw, g.ny, g.nz, db->box, db->tbox, db->zrange,
-                           qpack, qbox, qtbox, n, inter);
+    const auto kernel = g.nxw == 4   ? box_scan_kernel<4, 4>
+                        : g.nxw == 3 ? box_scan_kernel<3, 4>
+                        : g.nxw == 2 ? box_scan_kernel<2, 4>
+                        : g.nxw == 1 ? box_scan_kernel<1, 4>
+                                     : box_scan_kernel<0, 1>;
+    hipLaunchKernelGGL(kernel, dim3((unsigned)blocks), dim3(256), 0, s, db->planes, g.Wp, g.nxw, g.ny,
+                       g.nz, db->box, db->tbox, db->zrange, qpack, qbox, qtbox, n, inter);
     return hipGetLastError();
 }
 

@@ -124,3 +124,34 @@ def test_full_size_sparse_equals_dense_and_oracle():
         assert np.array_equal(_host(b[2]).view(np.uint32).astype(np.uint64), o_cnt)
         assert np.array_equal(_host(b[1]).view(np.uint64), o_sc.view(np.uint64))
         say(f"full config: query {j} (source {srcs[j]}) -> {top[:3]}")
+
+
+@pytest.mark.parametrize("dims", [(32, 37, 29), (32, 3, 50), (64, 33, 41), (64, 5, 200), (96, 21, 17),
+                                  (96, 4, 300), (128, 19, 23), (160, 9, 31)])
+def test_sparse_query_row_widths(dims):
+    """Rows of one to five words, slices whose rows end inside a 16-byte group, masks that reach the
+    last row of the grid, boxes that start inside it and boxes deeper than the staged ranges."""
+    need_gpu()
+    nx, ny, nz = dims
+    n, k = 45, 9
+    say(f"sparse row widths {dims}")
+    rng = np.random.default_rng(nx + ny + nz)
+    conc = np.zeros((n, nz, ny, nx), np.float32)
+    for e in range(n):                                  # noise in a box, every third the whole grid
+        lo = [int(rng.integers(0, d)) if e % 3 else 0 for d in (nz, ny, nx)]
+        hi = [int(rng.integers(a, d)) + 1 if e % 3 else d for a, d in zip(lo, (nz, ny, nx))]
+        s = (e,) + tuple(slice(a, b) for a, b in zip(lo, hi))
+        conc[s] = rng.random(conc[s].shape, dtype=np.float32)
+    db, conc = build_db_from_host(synth.GenConfig(nx, ny, nz, 1.0, 2.0, 0.5, 3.0, 1), n, T_LO, T_HI,
+                                  conc=conc)
+    for cut in (0, nz // 3):
+        q = rng.integers(0, 4, (nz, ny, nx)).astype(np.uint8)
+        q[:cut] = 0
+        q[:, :min(cut, ny - 1)] &= 1
+        cnt, sc = oracle.scan_block(conc, q, T_LO, T_HI)
+        top = oracle.rank(sc, k)
+        idx, score, counts = db.query_sparse(torch.from_numpy(q).cuda(), k)
+        db.sync()
+        assert _host(idx).tolist() == list(top)
+        assert np.array_equal(_host(score).view(np.uint64), sc[top].view(np.uint64))
+        assert np.array_equal(_host(counts).view(np.uint32).astype(np.uint64), cnt[top])
