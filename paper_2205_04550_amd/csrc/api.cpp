@@ -508,11 +508,11 @@ int db_scan(const db_t *db, const uint8_t *q_labels, uint32_t *inter, uint32_t *
     hipStream_t s = static_cast<hipStream_t>(stream);
     QueryPart *qpart = at<QueryPart>(ws, L.qpart);
     hipError_t e = launch_pack_queries(db, q_labels, 1, nullptr, at<uint32_t>(ws, L.qpack), qpart, s);
-    if (e == hipSuccess)
-        e = launch_sum_parts(qpart, 1, qcount ? qcount : at<uint32_t>(ws, L.acnt),
-                             at<int32_t>(ws, L.qbox), at<uint64_t>(ws, L.qmom), s);
     if (e == hipSuccess) e = prof_mark(db, s);
-    if (e == hipSuccess) e = launch_scan(db, db->count, at<uint32_t>(ws, L.qpack), inter, s);
+    if (e == hipSuccess)
+        e = launch_scan(db, db->count, at<uint32_t>(ws, L.qpack), inter, qpart,
+                        qcount ? qcount : at<uint32_t>(ws, L.acnt), at<int32_t>(ws, L.qbox),
+                        at<uint64_t>(ws, L.qmom), s);
     if (e == hipSuccess) e = prof_mark(db, s);
     if (e != hipSuccess) return hip_fail(e, "db_scan: launch");
     return DB_OK;
@@ -531,10 +531,10 @@ hipError_t enqueue_query(const db_t *db, const uint8_t *q_labels, int k, int32_t
     uint32_t *acnt = at<uint32_t>(ws, L.acnt);
     QueryPart *qpart = at<QueryPart>(ws, L.qpart);
     hipError_t e = launch_pack_queries(db, q_labels, 1, nullptr, at<uint32_t>(ws, L.qpack), qpart, s);
-    if (e == hipSuccess)
-        e = launch_sum_parts(qpart, 1, acnt, at<int32_t>(ws, L.qbox), at<uint64_t>(ws, L.qmom), s);
     if (e == hipSuccess) e = prof_mark(db, s);
-    if (e == hipSuccess) e = launch_scan(db, db->count, at<uint32_t>(ws, L.qpack), inter, s);
+    if (e == hipSuccess)
+        e = launch_scan(db, db->count, at<uint32_t>(ws, L.qpack), inter, qpart, acnt,
+                        at<int32_t>(ws, L.qbox), at<uint64_t>(ws, L.qmom), s);
     if (e == hipSuccess) e = prof_mark(db, s);
     if (e == hipSuccess) {
         TopkArgs a{};

@@ -134,7 +134,9 @@ hipError_t launch_pack_pool_queries(const db_t *db, const uint8_t *labels, int n
 // the row box of the T1Gd bits alone qtbox [nq][4].
 hipError_t launch_sum_parts(const QueryPart *qpart, int nq, uint32_t *acnt, int32_t *qbox,
                             uint64_t *qmom, hipStream_t s, int32_t *qtbox = nullptr);
+// The exact scan; its launch also sums the query's partials (launch_sum_parts' outputs of one query).
 hipError_t launch_scan(const db_t *db, int64_t n, const uint32_t *qpack, uint32_t *inter,
+                       const QueryPart *qpart, uint32_t *acnt, int32_t *qbox, uint64_t *qmom,
                        hipStream_t s);
 // Shape of a batched launch: the matrix-core kernel (te > 0: its entry tiles per wave), LDS
 // slabs of Z planes (use_lds) or the L2 fallback.
