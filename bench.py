@@ -292,7 +292,7 @@ def bench_batch(args, db, gen, n, build_s) -> int:
     log("autotuning the launch shape (z-planes per LDS slab x block size x entries per tile x "
         "queries per chunk)")
     best, table = autotune.tune_batch(db, lab_d, rois, k, reps=3, log=log)
-    log(f"picked {best[0] or 'max'} planes x {best[1]} threads, tile {best[2] or 4}, chunk "
+    log(f"picked {best[0] or 'max'} planes x {best[1] or 'default'} threads, tile {best[2] or 4}, chunk "
         f"{best[3] or 256} ({best[4]:.2f} ms)")
     for _ in range(args.warmup):
         db.query_batch(lab_d, rois, k, out=out, ws=ws)
@@ -422,8 +422,8 @@ def bench_train(args, db, gen, n, build_s) -> int:
         "roofline": {"bound": "alu", "achieved": flop / (ms * 1e-3) / 1e12,
                      "peak": FP32_VECTOR_PEAK / 1e12, "unit": "TFLOP/s",
                      "frac": flop / (ms * 1e-3) / FP32_VECTOR_PEAK, "traffic": None,
-                     "kernel": "whole step (forward convolutions and linear layers on the FP32 "
-                               "matrix cores, backward kernels on the vector ALUs)",
+                     "kernel": "whole step (convolutions, input gradients and linear layers on the FP32 "
+                               "matrix cores, convolution weight gradients on the vector ALUs)",
                      "note": "peak = the vector FP32 rate without packed instructions",
                      "algorithmic_flop_per_step": flop},
         "loss_first_last": [losses[0], losses[-1]],

@@ -6,7 +6,10 @@
 // counted on the fly (it depends on the box). The query words were ROI-masked
 // when packed, so only the database side needs x-edge masks.
 //
-// Main kernel (batch_lds_kernel): one block per work item (tile, query chunk).
+// Many queries with large boxes on rows of 128 voxels: batch_mfma_kernel (below, with its rule in
+// batch_plan).
+//
+// Otherwise (batch_lds_kernel): one block per work item (tile, query chunk).
 // Tiles are groups of TILE entries (4 or 8) ordered by their cost, largest first,
 // and blocks are dispatched in item order, so the long items start early and the
 // short ones fill in at the end (a persistent grid taking the items from an atomic

@@ -8,9 +8,10 @@
 // are exact in BF16) on BF16 16x16x32 products, the later convolutions with
 // Ci % 4 == 0 and the linear layers on FP32 16x16x4 / 32x32x2 products (each
 // product exact in FP32, only the summation order differs from a direct sum).
-// The backward kernels and the FP64 instantiation used by finite-difference
-// checks are direct convolutions on the vector ALUs: one thread per output (or
-// input, for the adjoint) voxel with block-uniform channel and batch indices.
+// The FP32 training kernels of the usual shapes are in train.hip; the general ones here, for other
+// shapes and for the FP64 instantiation used by finite-difference checks, are direct convolutions
+// on the vector ALUs: one thread per output (or input, for the adjoint) voxel with block-uniform
+// channel and batch indices. Both sum in the same order.
 // Weight gradients reduce in two deterministic stages. Kernels are templates
 // over the activation type T (float, or double) and the weight storage type
 // (bfloat16 bits, float or double); accumulation is in T.
