@@ -895,8 +895,10 @@ struct AdamCoef {
 };
 __device__ __forceinline__ void adam_one(float &w, float &m, float &v, float g, const AdamCoef &k)
 {
-    const float mi = k.b1 * m + (1.0f - k.b1) * g;
-    const float vi = k.b2 * v + (1.0f - k.b2) * g * g;
+    // Written as the FMAs they are, so that no compilation picks the other product of a sum: a last
+    // bit here is another trajectory some steps later.
+    const float mi = __builtin_fmaf(1.0f - k.b1, g, k.b1 * m);
+    const float vi = __builtin_fmaf(g, (1.0f - k.b2) * g, k.b2 * v);
     m = mi;
     v = vi;
     w = w - k.lr * (mi / k.c1) / (sqrtf(vi / k.c2) + k.eps);

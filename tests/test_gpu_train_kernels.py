@@ -1,6 +1,7 @@
 """Training kernels against float64 sums, at the sizes where a tile, a channel block or a row
 ends: every element within the bound of its own FP32 sum,
 (K + 2) 2^-24 times the sum of its terms' magnitudes."""
+import numpy as np
 import pytest
 import torch
 
@@ -226,3 +227,28 @@ def test_first_layer_gradient_masked_as_it_is_read(shape):
     xr = x.clone().requires_grad_()
     c = torch.autograd.grad(nn.Conv3dS2.apply(xr, w, b, w.detach(), True), (w, b, xr), gy)
     assert torch.equal(a[0], c[0]) and torch.equal(a[1], c[1])
+
+
+def test_adam_moments_bits():
+    """The moments after each of four steps, bit for bit: m = fma(1 - b1, g, b1 m) and
+    v = fma(g, (1 - b2) g, b2 v) in float32 (products exact in float64, one rounding of the sum)."""
+    need_gpu()
+    from paper_2205_04550_amd.binding import LIB
+    f = np.float32
+    n, b1, b2 = 1027, f(0.9), f(0.999)
+    rng = np.random.default_rng(5)
+    w = torch.randn(n, device="cuda")
+    m, v = torch.zeros(n, device="cuda"), torch.zeros(n, device="cuda")
+    mh, vh = np.zeros(n, f), np.zeros(n, f)
+    for t in range(1, 5):
+        g = rng.standard_normal(n).astype(f)
+        gd = torch.from_numpy(g).cuda()
+        say(f"adam step {t}")
+        rc = LIB.nn_adam_step(n, w.data_ptr(), m.data_ptr(), v.data_ptr(), gd.data_ptr(), None, 1e-3, 0.9,
+                              0.999, 1e-8, t, torch.cuda.current_stream().cuda_stream)
+        assert rc == 0
+        torch.cuda.synchronize()
+        mh = ((f(1) - b1).astype(np.float64) * g + (b1 * mh).astype(np.float64)).astype(f)
+        vh = (g.astype(np.float64) * ((f(1) - b2) * g).astype(np.float64) + (b2 * vh)).astype(f)
+        assert np.array_equal(m.cpu().numpy().view(np.uint32), mh.view(np.uint32)), t
+        assert np.array_equal(v.cpu().numpy().view(np.uint32), vh.view(np.uint32)), t
