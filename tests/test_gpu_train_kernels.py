@@ -148,6 +148,32 @@ def test_conv_forward(shape):
                 assert ok, (shape, wc.dtype, relu, worst)
 
 
+@pytest.mark.parametrize("shape", [(3, 3, 9, 6, 8, 10), (3, 5, 16, 4, 6, 12), (2, 6, 20, 8, 4, 6), (3, 7, 8, 4, 4, 10),
+                                   (2, 9, 16, 6, 6, 6), (3, 13, 5, 2, 4, 6), (3, 8, 16, 8, 8, 8), (3, 2, 8, 8, 8, 16)])
+def test_conv_forward_keeps_infinities_and_nans_in_their_sample(shape):
+    """Fine channels that do not fill a product or a batch: an infinity or a NaN of one sample
+    reaches only the outputs whose taps hold it (the float64 kernel's), and the other samples'
+    bits are those of a batch without it."""
+    need_gpu()
+    from paper_2205_04550_amd import nn
+    B, Ci, Co, D, H, W = shape
+    say(f"forward, special values in sample 1 {shape}")
+    g = torch.Generator().manual_seed(7)
+    fine = torch.randn(B, Ci, D, H, W, generator=g)
+    w = torch.randn(Co, Ci, 3, 3, 3, generator=g) * 0.2
+    clean = nn.Conv3dS2.apply(fine.cuda(), w.cuda(), None, w.cuda(), False).cpu()
+    fine[1, :, ::3, ::2, ::4] = float("inf")
+    fine[1, :, 1::3, 1::2, ::5] = float("nan")
+    got = nn.Conv3dS2.apply(fine.cuda(), w.cuda(), None, w.cuda(), False).cpu()
+    want = nn.Conv3dS2.apply(fine.cuda().double(), w.cuda().double(), None, w.cuda().double(), False).cpu()
+    assert torch.equal(torch.isnan(got), torch.isnan(want))
+    assert torch.equal(torch.isposinf(got), torch.isposinf(want))
+    assert torch.equal(torch.isneginf(got), torch.isneginf(want))
+    for b in range(B):
+        assert b == 1 or torch.equal(got[b], clean[b]), b
+    assert not torch.isfinite(got[1]).all()
+
+
 # (B, In, Out): tiles of 16 rows and 16 or 64 columns with a rest, terms that end inside a chunk of
 # 64, one chunk, several chunks in flight and past them; In not a multiple of 4 (the direct loop).
 LINEAR = [(32, 512, 640), (7, 68, 36), (17, 1028, 20), (1, 4, 4), (33, 64, 2116), (5, 4096, 16), (3, 30, 8)]
