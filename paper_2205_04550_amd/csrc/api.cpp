@@ -108,8 +108,11 @@ struct BatchGraph {
     hipGraphExec_t exec = nullptr;
     int32_t *staging = nullptr;  // pinned upload buffer: rois [nq][6] + order [nq]
     size_t staging_elems = 0;
-    int32_t *order = nullptr;    // device: entry order of the matrix-core kernel's tiles
-    int64_t order_n = 0, order_cap = 0;
+    struct Order {               // entries in the order of tiles of `tile`, for count = n
+        int tile = 0;
+        int64_t n = 0;
+        std::vector<int32_t> entries;
+    } orders[2];                 // host: of the vector kernel's tiles, the matrix-core kernel's
     hipEvent_t uploaded = nullptr;
     bool upload_pending = false;
 
@@ -126,7 +129,6 @@ struct BatchGraph {
             (void)hipEventDestroy(uploaded);
         }
         if (staging) (void)hipHostFree(staging);
-        if (order) (void)hipFree(order);
         if (cap) (void)hipStreamDestroy(cap);
     }
 };
@@ -305,8 +307,8 @@ static void neighbour_order(const int32_t *box, int32_t *order, int n)
 // entries) hold overlapping boxes; then order the tiles by the size of the union
 // of their members' row boxes, largest first (blocks are dispatched in this
 // order, so the longest items start first). Reads the boxes back after a
-// device synchronisation; host sort; one upload.
-static int build_tile_order(db_t *db, int tile, int32_t *dst)
+// device synchronisation; host sort.
+static int build_tile_order(const db_t *db, int tile, std::vector<int32_t> &sorted)
 {
     const int64_t n = db->count;
     std::vector<int32_t> box((size_t)n * 4);
@@ -352,13 +354,35 @@ static int build_tile_order(db_t *db, int tile, int32_t *dst)
     const int64_t nfull = n / tile;
     std::stable_sort(tperm.begin(), tperm.begin() + nfull,
                      [&](int64_t a, int64_t b) { return tcost[a] > tcost[b]; });
-    std::vector<int32_t> sorted;
+    sorted.clear();
     sorted.reserve(n);
     for (int64_t t : tperm)
         for (int64_t j = t * tile; j < std::min<int64_t>(n, (t + 1) * tile); ++j)
             sorted.push_back(order[j]);
-    e = hipMemcpy(dst, sorted.data(), (size_t)n * 4, hipMemcpyHostToDevice);
+    return DB_OK;
+}
+
+// The handle's tile order (in its storage) for tiles of `tile` entries: sorted anew after appends;
+// where calls of both kernels alternate, the host's copy of the order is uploaded again once the
+// launches that read the other one are done.
+static int use_tile_order(db_t *db, int tile, BatchGraph::Order &o)
+{
+    if (db->tile_order_n == db->count && db->tile_order_tile == tile) return DB_OK;
+    db->tile_order_n = 0;
+    if (o.n != db->count || o.tile != tile) {
+        o.n = 0;
+        const int rc = build_tile_order(db, tile, o.entries);
+        if (rc) return rc;
+        o.n = db->count;
+        o.tile = tile;
+    } else {
+        const hipError_t e = hipDeviceSynchronize();
+        if (e != hipSuccess) return hip_fail(e, "db_query_batch: tile order");
+    }
+    const hipError_t e = hipMemcpy(db->tile_order, o.entries.data(), (size_t)o.n * 4, hipMemcpyHostToDevice);
     if (e != hipSuccess) return hip_fail(e, "db_query_batch: upload tile order");
+    db->tile_order_n = o.n;
+    db->tile_order_tile = tile;
     return DB_OK;
 }
 
@@ -709,39 +733,11 @@ int db_query_batch(const db_t *db_c, int nq, const uint8_t *q_labels, const db_r
         if (e == hipSuccess) e = hipEventCreateWithFlags(&G.uploaded, hipEventDisableTiming);
         if (e != hipSuccess) return hip_fail(e, "db_query_batch: stream/event create");
     }
-    // Entries grouped by row-box centre for the tiles (rebuilt after appends); the matrix-core
-    // kernel's have an order of their own, so that calls of both kinds may alternate.
-    if (P.use_lds) {
-        if (db->tile_order_n != db->count || db->tile_order_tile != P.tile) {
-            db->tile_order_n = 0;
-            rc = build_tile_order(db, P.tile, db->tile_order);
-            if (rc) return rc;
-            db->tile_order_n = db->count;
-            db->tile_order_tile = P.tile;
-        }
+    // Entries grouped by row-box centre for the tiles.
+    if (P.use_lds || P.te) {
+        rc = use_tile_order(db, P.tile, G.orders[P.te ? 1 : 0]);
+        if (rc) return rc;
         P.tile_order = db->tile_order;
-    } else if (P.te) {
-        if (G.order_cap < db->count) {
-            G.drop_exec();                               // recorded with the old buffer
-            e = hipDeviceSynchronize();
-            if (e != hipSuccess) return hip_fail(e, "db_query_batch: tile order");
-            if (G.order) (void)hipFree(G.order);
-            G.order = nullptr;
-            G.order_n = G.order_cap = 0;
-            if (hipMalloc((void **)&G.order, (size_t)db->capacity * 4) == hipSuccess) {
-                G.order_cap = db->capacity;
-            } else {                                     // no memory left: entries as they stand
-                (void)hipGetLastError();
-                G.order = nullptr;
-            }
-        }
-        if (G.order && G.order_n != db->count) {
-            G.order_n = 0;
-            rc = build_tile_order(db, P.tile, G.order);
-            if (rc) return rc;
-            G.order_n = db->count;
-        }
-        P.tile_order = G.order;
     }
     // Pinned staging buffer; wait for the previous upload before reusing it.
     const size_t elems = (size_t)nq * 7 + list_off.size() + list_q.size();

@@ -34,6 +34,19 @@ def test_library_exports_every_declared_symbol():
     assert set(declared_functions()) == set(binding.SYMBOLS) | set(nn.NN_SYMBOLS)
 
 
+def test_library_never_allocates_device_memory():
+    """No device allocation among the functions that the library calls (the header's promise:
+    every device buffer is the caller's)."""
+    import subprocess
+    from paper_2205_04550_amd import binding
+    names = subprocess.run(["nm", "-D", "--undefined-only", binding.LIB_PATH], capture_output=True,
+                           text=True, check=True).stdout.split()
+    called = {n.split("@")[0] for n in names if n.startswith("hip")}
+    assert "hipMemcpyAsync" in called
+    assert not {n for n in called if n.startswith(("hipMalloc", "hipExtMalloc", "hipMemPool")) or
+                n in ("hipFree", "hipFreeAsync")}
+
+
 def test_storage_bytes():
     from paper_2205_04550_amd import binding
     # 128^3: 65,536 words per mask plane, 2 planes, 4 bytes; popcounts 8 bytes per entry;

@@ -188,3 +188,28 @@ def test_batch_matrix_core_kernel(nq, n, dims):
     res = db.query_batch(lab_d, rois, k)
     db.sync()
     _compare(res, ref, k)
+
+
+def test_batch_kinds_alternate_on_one_handle():
+    """Calls that take the matrix-core kernel (many whole-grid queries) and the vector kernel (a few)
+    in turn, and after an append: the oracle's results, and the handle's tile order is one of all
+    its entries after each."""
+    need_gpu()
+    dims = (128, 80, 80)
+    gen = synth.GenConfig(*dims, 2.0, 20.0, 0.5, 3.0, 41)
+    n, k = 70, 5
+    db, conc = build_db_from_host(gen, 61, T_LO, T_HI, capacity=n)
+    conc = np.concatenate([conc, gen.conc_cpu(61, n - 61)])
+    labels, _ = synth.make_queries(gen, n, 96, synth.BATCH_QUERY_SEED)
+    whole = np.tile((0, 0, 0) + dims, (96, 1)).astype(np.int32)
+    lab_d = torch.from_numpy(labels).cuda()
+    for have in (61, n):
+        db.append(torch.from_numpy(conc[len(db):have]).cuda())
+        cnt, sc = oracle.scan_block_multi(conc[:have], labels, T_LO, T_HI, whole)
+        ref = [(cnt[q], sc[q], oracle.rank(sc[q], k)) for q in range(96)]
+        for nq in (96, 7, 96, 7, 7, 96):
+            say(f"batch kinds in turn: {have} entries, {nq} queries")
+            res = db.query_batch(lab_d[:nq], whole[:nq], k)
+            db.sync()
+            _compare(res, ref[:nq], k)
+            assert sorted(_host(db.tile_order[:have])) == list(range(have))
