@@ -2211,9 +2211,9 @@ int dtype_pair(int dtype, int wdtype)
     return -1;
 }
 
-int launched(const char *what)
+// e: what a launcher returned (launchers end in hipGetLastError, which clears the error).
+int launched(const char *what, hipError_t e = hipGetLastError())
 {
-    hipError_t e = hipGetLastError();
     if (e != hipSuccess) return tdb_set_error(DB_EHIP, "%s: %s", what, hipGetErrorString(e));
     return DB_OK;
 }
@@ -2575,9 +2575,9 @@ int nn_conv3d_s2_fwd(int dtype, int B, int Ci, int Co, int D, int H, int W, cons
     const bool staged = Ci % 4 == 0 && W % 4 == 0 && (uintptr_t)X % 16 == 0 && Co <= 64 &&
                         B <= 65535 && (int64_t)D * H * W * 4 < ((int64_t)1 << 31);
     if (pair <= 1 && conv_fwd_direct_ok(B, Ci, Co, D, H, W, staged)) {
-        (void)launch_conv_fwd_direct(pair == 0, staged, B, Ci, Co, D, H, W, (const float *)X, Wt,
-                                     (const float *)bias, relu, (float *)Y, s);
-        return launched("nn_conv3d_s2_fwd");
+        return launched("nn_conv3d_s2_fwd",
+                        launch_conv_fwd_direct(pair == 0, staged, B, Ci, Co, D, H, W, (const float *)X, Wt,
+                                               (const float *)bias, relu, (float *)Y, s));
     }
     if (pair <= 1 && staged) {
         const int e = conv_fwd_mfma(pair == 0, B, Ci, Co, D, H, W, X, Wt, bias, relu, Y, s);
@@ -2624,9 +2624,9 @@ int nn_conv3d_s2_bwd_data(int dtype, int B, int Ci, int Co, int D, int H, int W,
         return tdb_set_error(DB_EINVAL, "nn_conv3d_s2_bwd_data: bad arguments");
     const hipStream_t s = static_cast<hipStream_t>(stream);
     if (pair <= 1 && conv_adjoint_ok(B, Ci, Co, D, H, W)) {
-        (void)launch_conv_adjoint(pair == 0, B, Ci, Co, D, H, W, (const float *)dY, Wt,
-                                  (const float *)bias, relu, (float *)dX, s);
-        return launched("nn_conv3d_s2_bwd_data");
+        return launched("nn_conv3d_s2_bwd_data",
+                        launch_conv_adjoint(pair == 0, B, Ci, Co, D, H, W, (const float *)dY, Wt,
+                                            (const float *)bias, relu, (float *)dX, s));
     }
     const int64_t isp = (int64_t)D * H * W;
     const dim3 grid((unsigned)((B * isp + 255) / 256), (Ci + kCB - 1) / kCB);
@@ -2671,8 +2671,9 @@ int nn_conv3d_s2_bwd_weight(int dtype, int B, int Ci, int Co, int D, int H, int 
     const dim3 g1f(chunks, Ci, (Co + kWgCB - 1) / kWgCB);
     const unsigned g2 = (unsigned)((Co * Ci * 28 + 255) / 256);
     if (dtype == NN_F32 && conv_wgrad_ok(Ci, Co, D, H, W)) {
-        (void)launch_conv_wgrad(B, Ci, Co, D, H, W, (const float *)X, (const float *)dY, nullptr,
-                                (float *)dWt, (float *)dbias, (float *)ws, s);
+        return launched("nn_conv3d_s2_bwd_weight",
+                        launch_conv_wgrad(B, Ci, Co, D, H, W, (const float *)X, (const float *)dY, nullptr,
+                                          (float *)dWt, (float *)dbias, (float *)ws, s));
     } else if (dtype == NN_F32) {   // samples of 2 GiB and more
         hipLaunchKernelGGL((conv_bwd_weight_partial<float, kWgCB>), g1f, dim3(256), 0, s, B, Ci, Co,
                            D, H, W, (const float *)X, (const float *)dY, (float *)ws);
@@ -2722,8 +2723,8 @@ int nn_linear_fwd(int dtype, int B, int In, int Out, const void *X, const void *
     const size_t wal = pair == 0 ? 8 : 16;
     const bool vec = In % 4 == 0 && (uintptr_t)X % 16 == 0 && (uintptr_t)Wt % wal == 0;
     if (pair <= 1 && vec && linear_small_ok(B, Out, In))
-        (void)launch_linear_small(pair == 0, false, B, Out, In, (const float *)X, Wt,
-                                  (const float *)bias, relu, (float *)Y, s);
+        return launched("nn_linear_fwd", launch_linear_small(pair == 0, false, B, Out, In, (const float *)X, Wt,
+                                                             (const float *)bias, relu, (float *)Y, s));
     else if (pair == 0 && vec)
         hipLaunchKernelGGL((linear_mfma_kernel<uint16_t, false>), mgrid, dim3(512), 0, s, B, Out, In,
                            (const float *)X, (const uint16_t *)Wt, (const float *)bias, relu,
@@ -2761,8 +2762,9 @@ int nn_linear_bwd_data(int dtype, int B, int In, int Out, const void *dY, const 
     const bool vec = In % 4 == 0 && Out % 4 == 0 && (uintptr_t)dY % 16 == 0 &&
                      (uintptr_t)Wt % wal == 0;
     if (pair <= 1 && vec && linear_small_ok(B, In, Out))
-        (void)launch_linear_small(pair == 0, true, B, In, Out, (const float *)dY, Wt, nullptr, 0,
-                                  (float *)dX, s);
+        return launched("nn_linear_bwd_data",
+                        launch_linear_small(pair == 0, true, B, In, Out, (const float *)dY, Wt, nullptr, 0,
+                                            (float *)dX, s));
     else if (pair == 0 && vec)
         hipLaunchKernelGGL((linear_mfma_kernel<uint16_t, true>), mgrid, dim3(512), 0, s, B, In, Out,
                            (const float *)dY, (const uint16_t *)Wt, (const float *)nullptr, 0,
@@ -2795,8 +2797,9 @@ int nn_linear_bwd_weight(int dtype, int B, int In, int Out, const void *X, const
     const hipStream_t s = static_cast<hipStream_t>(stream);
     const dim3 grid((In + 255) / 256, Out);
     if (dtype == NN_F32 && linear_wgrad_ok(B, In, Out))
-        (void)launch_linear_wgrad(B, In, Out, (const float *)X, (const float *)dY, (float *)dWt,
-                                  (float *)dbias, s);
+        return launched("nn_linear_bwd_weight",
+                        launch_linear_wgrad(B, In, Out, (const float *)X, (const float *)dY, (float *)dWt,
+                                            (float *)dbias, s));
     else if (dtype == NN_F32)
         hipLaunchKernelGGL(linear_bwd_weight_kernel<float>, grid, dim3(256), 0, s, B, In, Out,
                            (const float *)X, (const float *)dY, (float *)dWt, (float *)dbias);
@@ -2875,10 +2878,10 @@ int nn_conv3d_s2_backward(int dtype, int B, int Ci, int Co, int D, int H, int W,
         return tdb_set_error(DB_ENOSPC, "nn_conv3d_s2_backward: workspace %zu < %zu", ws_bytes, need);
     if (Y && !dX && dtype == NN_F32 && conv_wgrad_ok(Ci, Co, D, H, W)) {
         // Only the weight gradient reads the gradient before the ReLU: masked as it is read.
-        (void)launch_conv_wgrad(B, Ci, Co, D, H, W, (const float *)X, (const float *)dY,
-                                (const float *)Y, (float *)dWt, (float *)dbias, (float *)ws,
-                                static_cast<hipStream_t>(stream));
-        return launched("nn_conv3d_s2_backward");
+        return launched("nn_conv3d_s2_backward",
+                        launch_conv_wgrad(B, Ci, Co, D, H, W, (const float *)X, (const float *)dY,
+                                          (const float *)Y, (float *)dWt, (float *)dbias, (float *)ws,
+                                          static_cast<hipStream_t>(stream)));
     }
     const size_t wg = up256(nn_conv3d_s2_bwd_weight_ws_bytes(dtype, B, Ci, Co, D, H, W));
     const void *g = dY;

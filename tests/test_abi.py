@@ -116,3 +116,50 @@ def test_group_path_sizes_and_argument_errors_before_any_gpu_call():
     # Query codes of 2 GiB or more are refused (32-bit row offsets in the distance kernel).
     assert b.LIB.emb_distances(b.EMB_BF16, 1 << 20, 100, 1024, fake, None, sq, fake, None, sq,
                                fake, None) == b.DB_EINVAL
+
+
+# A HIP runtime whose launches fail: the error is reported once and cleared, as the real one does.
+FAILING_RUNTIME = r"""
+static int last;
+int __hipPushCallConfiguration() { return 0; }
+int __hipPopCallConfiguration() { return 0; }
+int hipLaunchKernel() { last = 9; return 9; }
+int hipGetLastError(void) { int e = last; last = 0; return e; }
+int hipGetDevice(int *d) { *d = 0; return 0; }
+int hipDeviceGetAttribute(int *v, int a, int d) { *v = 256; return 0; }
+"""
+FAILING_CALLS = r"""
+import ctypes, sys
+ctypes.CDLL(sys.argv[1], mode=ctypes.RTLD_GLOBAL)
+from paper_2205_04550_amd import binding as b, nn
+L, p, n, f32 = b.LIB, 1 << 20, 1 << 40, nn.NN_F32
+conv, lin = (f32, 2, 8, 16, 8, 8, 8), (f32, 32, 512, 256)
+adam = (1e-3, 0.9, 0.999, 1e-8, 1, None)
+for name, args in (("nn_conv3d_s2_fwd", (*conv, p, p, f32, p, 0, p, None)),
+                   ("nn_conv3d_s2_bwd_data", (*conv, p, p, f32, None, 0, p, None)),
+                   ("nn_conv3d_s2_bwd_weight", (*conv, p, p, p, p, p, n, None)),
+                   ("nn_conv3d_s2_backward", (*conv, p, p, f32, p, p, None, p, p, p, n, None)),
+                   ("nn_conv3d_s2_backward", (*conv, p, p, f32, p, p, p, p, p, p, n, None)),
+                   ("nn_conv3d_t_s2_backward", (*conv, p, p, f32, p, p, p, p, p, p, n, None)),
+                   ("nn_linear_fwd", (*lin, p, p, f32, p, 0, p, None)),
+                   ("nn_linear_bwd_data", (*lin, p, p, f32, p, None)),
+                   ("nn_linear_bwd_weight", (*lin, p, p, p, p, None)),
+                   ("nn_linear_backward", (*lin, p, p, f32, p, p, p, p, p, p, n, None)),
+                   ("nn_adam_step", (100, p, p, p, p, None, *adam)),
+                   ("emb_knn", (b.EMB_BF16, 4, 40000, 64, p, None, p, p, None, p, 10, 0, p, p, p, n, None))):
+    print(name, getattr(L, name)(*args) == b.DB_EHIP)
+"""
+
+
+def test_calls_report_a_launch_that_failed(tmp_path):
+    """Each call whose launch fails returns DB_EHIP, not DB_OK (over a runtime that launches
+    nothing, so the aligned, non-null pointers are never dereferenced)."""
+    import subprocess
+    import sys
+    src, lib = tmp_path / "hip.c", tmp_path / "libfailing.so"
+    src.write_text(FAILING_RUNTIME)
+    subprocess.run(["gcc", "-w", "-shared", "-fPIC", str(src), "-o", str(lib)], check=True)
+    out = subprocess.run([sys.executable, "-c", FAILING_CALLS, str(lib)], cwd=ROOT, check=True,
+                         capture_output=True, text=True).stdout.split()
+    assert len(out) == 24
+    assert [n for n, ok in zip(out[::2], out[1::2]) if ok != "True"] == []
