@@ -7,6 +7,8 @@
 // is all a Dice overlap needs and is 32x smaller than float32.
 #include <limits.h>
 
+#include <algorithm>
+
 #include "common.hpp"
 #include "internal.hpp"
 #include "query_parts.hpp"
@@ -277,10 +279,14 @@ hipError_t launch_append(const db_t *db, const float *conc, int64_t n, uint32_t 
     const int nbp = bcnt ? bound_blocks(g, &nbx, &nby) : 0;
     // Eight waves per block, four blocks per CU; 16 waves where there are fewer entries than that.
     const int threads = n >= 1024 ? 512 : 1024;
-    hipLaunchKernelGGL(append_kernel, dim3((unsigned)n), dim3(threads),
-                       (size_t)(4 * g.nz + 2 * nbp) * sizeof(int), s, conc, g.V, g.W, g.Wp, g.nxw, g.ny,
-                       g.nz, db->t_lo, db->t_hi, nbx, nby, nbp, planes, popcnt, box, tbox, mom, zrange,
-                       bcnt);
+    // A launch takes fewer than 2^32 threads.
+    constexpr int64_t kMax = (int64_t)1 << 22;
+    for (int64_t e = 0; e < n; e += kMax)
+        hipLaunchKernelGGL(append_kernel, dim3((unsigned)std::min(n - e, kMax)), dim3(threads),
+                           (size_t)(4 * g.nz + 2 * nbp) * sizeof(int), s, conc + e * g.V, g.V, g.W, g.Wp,
+                           g.nxw, g.ny, g.nz, db->t_lo, db->t_hi, nbx, nby, nbp, planes + e * 2 * g.Wp,
+                           popcnt + e * 2, box + e * 4, tbox + e * 4, mom + e * 4, zrange + e * g.nz * 2,
+                           bcnt ? bcnt + e * 2 * nbp : nullptr);
     return hipGetLastError();
 }
 

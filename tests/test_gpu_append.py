@@ -69,3 +69,23 @@ def test_append_one_pass(dims, n, t_lo):
         want = np.zeros((n, 2, nbp), dtype=np.int64)
         want[:, :, :b.shape[2]] = b
         assert np.array_equal(db.block_counts[:n].cpu().numpy().astype(np.uint16), want)
+
+
+def test_append_of_millions_of_tiny_entries():
+    """More entries than one launch takes threads for, in one call."""
+    need_gpu()
+    from paper_2205_04550_amd import TumorDB
+    n = 8_400_000
+    g = torch.Generator(device="cuda").manual_seed(1)
+    c = torch.rand((n, 1, 1, 32), generator=g, device="cuda")
+    db = TumorDB(32, 1, 1, n, 0.25, 0.675)
+    db.storage.fill_(0xa5)
+    db.append(c)
+    torch.cuda.synchronize()
+    bit = 2 ** torch.arange(32, device="cuda", dtype=torch.int64)
+    for m, t in enumerate((0.25, 0.675)):
+        on = c.view(n, 32) >= t
+        word = (on.long() * bit).sum(1)
+        assert torch.equal(db.planes[:, m, 0].long() & 0xffffffff, word)
+        assert torch.equal(db.popcounts[:, m].long(), on.sum(1))
+    assert torch.equal(db.moments[:, 3], (c.view(n, 32) >= 0.25).sum(1))
