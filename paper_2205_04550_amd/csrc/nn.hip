@@ -3028,20 +3028,30 @@ int nn_adam_step_multi(int count, const int64_t *n, float *const *w, float *cons
         ok = n[i] > 0 && n[i] < ((int64_t)1 << 40) && w[i] && m[i] && v[i] && g[i];
     if (!ok) return tdb_set_error(DB_EINVAL, "nn_adam_step: bad arguments");
     const AdamCoef k = {lr, b1, b2, eps, 1.0f - powf(b1, (float)t), 1.0f - powf(b2, (float)t)};
+    // A launch takes fewer than 2^32 threads: pieces of tensors of at most kMax blocks in all.
+    constexpr int64_t kMax = (int64_t)1 << 23;
+    int64_t at = 0;                                      // elements of tensor i already in a launch
     for (int i = 0; i < count;) {
         AdamTable tab = {};
         int64_t blocks = 0;
-        for (; i < count && tab.count < kAdamMax; ++i) {
-            const int64_t nb = (n[i] + 1023) / 1024;
-            if (tab.count && blocks + nb > 0x7fffffff) break;
+        while (i < count && tab.count < kAdamMax && blocks < kMax) {
+            const int64_t nb = std::min((n[i] - at + 1023) / 1024, kMax - blocks);
+            const int64_t ne = std::min(n[i] - at, nb * 1024);
             tab.first[tab.count] = (unsigned)blocks;
-            tab.t[tab.count++] = {n[i], w[i], m[i], v[i], g[i], w_bf16[i]};
+            tab.t[tab.count++] = {ne, w[i] + at, m[i] + at, v[i] + at, g[i] + at, w_bf16[i] ? w_bf16[i] + at : nullptr};
             blocks += nb;
+            at += ne;
+            if (at == n[i]) {
+                ++i;
+                at = 0;
+            }
         }
         hipLaunchKernelGGL(adam_kernel, dim3((unsigned)blocks), dim3(256), 0,
                            static_cast<hipStream_t>(stream), tab, k);
+        const hipError_t e = hipGetLastError();
+        if (e != hipSuccess) return launched("nn_adam_step", e);
     }
-    return launched("nn_adam_step");
+    return DB_OK;
 }
 
 int nn_to_bf16(int64_t n, const float *x, uint16_t *y, void *stream)

@@ -163,3 +163,69 @@ def test_calls_report_a_launch_that_failed(tmp_path):
                          capture_output=True, text=True).stdout.split()
     assert len(out) == 24
     assert [n for n, ok in zip(out[::2], out[1::2]) if ok != "True"] == []
+
+
+RECORDING_RUNTIME = r"""
+#include <stdio.h>
+struct d3 { unsigned x, y, z; };
+struct tensor { long long n; char *w, *m, *v, *g, *wb; };
+struct table { int count; unsigned first[33]; struct tensor t[32]; };
+int __hipPushCallConfiguration() { return 0; }
+int __hipPopCallConfiguration(struct d3 *g, struct d3 *b, unsigned long *l, void **s)
+{
+    static const struct d3 one = {1, 1, 1};
+    *g = *b = one;
+    *l = 0;
+    *s = 0;
+    return 0;
+}
+int hipLaunchKernel(const void *f, struct d3 grid, struct d3 block, void **args, unsigned long l, void *s)
+{
+    const struct table *t = args[0];
+    printf("launch %d\n", t->count);
+    for (int i = 0; i < t->count; ++i)
+        printf("%u %lld %llu %llu\n", t->first[i], t->t[i].n, (unsigned long long)t->t[i].w,
+               (unsigned long long)t->t[i].wb);
+    fflush(stdout);
+    return 0;
+}
+int hipGetLastError(void) { return 0; }
+"""
+ADAM_OF_LARGE_TENSORS = r"""
+import ctypes, sys
+ctypes.CDLL(sys.argv[1], mode=ctypes.RTLD_GLOBAL)
+from paper_2205_04550_amd.nn import LIB
+n = [int(a) for a in sys.argv[2:]]
+k = len(n)
+col = lambda c: (ctypes.c_void_p * k)(*(((i + 1) << 44) + (c << 40) for i in range(k)))
+sys.exit(LIB.nn_adam_step_multi(k, (ctypes.c_int64 * k)(*n), col(0), col(1), col(2), col(3), col(4),
+                                1e-3, 0.9, 0.999, 1e-8, 1, None))
+"""
+
+
+@pytest.mark.parametrize("sizes", [(5, 1024, 1025), (2 ** 34 + 5, 3, 2 ** 33, 1025), (7,) * 70,
+                                   (2 ** 33 - 1024, 2048, 2 ** 35)])
+def test_adam_launches_take_fewer_threads_than_a_grid_holds(tmp_path, sizes):
+    """Every element of every tensor in exactly one launch, in order, in launches of at most 2^31
+    threads (blocks of 256 for 1,024 elements; nothing runs)."""
+    import subprocess
+    import sys
+    src, lib = tmp_path / "hip.c", tmp_path / "librecording.so"
+    src.write_text(RECORDING_RUNTIME)
+    subprocess.run(["gcc", "-w", "-shared", "-fPIC", str(src), "-o", str(lib)], check=True)
+    out = subprocess.run([sys.executable, "-c", ADAM_OF_LARGE_TENSORS, str(lib), *map(str, sizes)], cwd=ROOT,
+                         check=True, capture_output=True, text=True).stdout.splitlines()
+    done, i = 0, 0
+    while out:
+        count = int(out.pop(0).split()[1])
+        blocks = 0
+        for _ in range(count):
+            first, n, w, wb = map(int, out.pop(0).split())
+            assert first == blocks and n > 0
+            assert w == ((i + 1) << 44) + 4 * done and wb == ((i + 1) << 44) + (4 << 40) + 2 * done
+            blocks += -(-n // 1024)
+            done += n
+            if done == sizes[i]:
+                i, done = i + 1, 0
+        assert blocks * 256 <= 2 ** 31
+    assert i == len(sizes) and done == 0
