@@ -545,6 +545,7 @@ __global__ void __launch_bounds__(256) channel_sum_partial(int B, int C, int64_t
     const int64_t p0 = (int64_t)blockIdx.x * kCsChunk;
     const int n = (int)(P - p0 < kCsChunk ? P - p0 : kCsChunk);
     int64_t b = (p0 + threadIdx.x) / S, sidx = p0 + threadIdx.x - b * S;
+    const int64_t db = 256 / S, ds = 256 - db * S;       // 256 positions on
     T acc = T(0);
     constexpr int U = 8;
     for (int i = threadIdx.x; i < n; i += 256 * U) {
@@ -555,8 +556,9 @@ __global__ void __launch_bounds__(256) channel_sum_partial(int B, int C, int64_t
             at[u] = i + 256 * u < n ? (b * C + c) * S + sidx : (int64_t)c * S;
             v[u] = X[at[u]];
             if (RELU) m[u] = Y[at[u]];
-            sidx += 256;
-            while (sidx >= S) {
+            b += db;
+            sidx += ds;
+            if (sidx >= S) {
                 sidx -= S;
                 ++b;
             }

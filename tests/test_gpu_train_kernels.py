@@ -278,3 +278,47 @@ def test_adam_moments_bits():
         vh = (g.astype(np.float64) * ((f(1) - b2) * g).astype(np.float64) + (b2 * vh)).astype(f)
         assert np.array_equal(m.cpu().numpy().view(np.uint32), mh.view(np.uint32)), t
         assert np.array_equal(v.cpu().numpy().view(np.uint32), vh.view(np.uint32)), t
+
+
+@pytest.mark.parametrize("B,C,S", [(70000, 3, 1), (20000, 2, 3), (5000, 4, 27), (3, 2, 255), (40, 3, 256), (9, 2, 4097)])
+def test_channel_sum(B, C, S):
+    """Sums over samples and positions, in float and (with its input's ReLU, as a transposed
+    convolution's backward) from rows shorter and longer than the 256 positions of a step."""
+    need_gpu()
+    from paper_2205_04550_amd.nn import LIB, _check
+    say(f"channel sum {B} x {C} x {S}")
+    g = torch.Generator().manual_seed(B + C + S)
+    x = torch.randn(B, C, S, generator=g, dtype=torch.float64)
+    st = torch.cuda.current_stream().cuda_stream
+    for dtype, xd in ((0, x.float().cuda()), (1, x.cuda())):
+        out = torch.empty(C, dtype=xd.dtype, device="cuda")
+        nb = LIB.nn_channel_sum_ws_bytes(dtype, B, C, S)
+        ws = torch.empty(nb, dtype=torch.uint8, device="cuda")
+        _check(LIB.nn_channel_sum(dtype, B, C, S, xd.data_ptr(), out.data_ptr(), ws.data_ptr(), nb, st))
+        h = xd.double().cpu()
+        err = (out.double().cpu() - h.sum((0, 2))).abs()
+        assert bool((err <= (B * S + 2) * (U if dtype == 0 else 2.0 ** -53) * h.abs().sum((0, 2))).all())
+
+
+def test_channel_sum_of_single_positions_takes_no_longer():
+    """65,536 samples of one position take about as long as 256 samples of 256 (the same values)."""
+    need_gpu()
+    from paper_2205_04550_amd.nn import LIB, _check
+    x = torch.randn(65536 * 64, device="cuda")
+    st = torch.cuda.current_stream().cuda_stream
+    best = {}
+    for B, S in ((65536, 1), (256, 256)):
+        out = torch.empty(64, device="cuda")
+        nb = LIB.nn_channel_sum_ws_bytes(0, B, 64, S)
+        ws = torch.empty(nb, dtype=torch.uint8, device="cuda")
+        times = []
+        for _ in range(6):
+            a, b = torch.cuda.Event(enable_timing=True), torch.cuda.Event(enable_timing=True)
+            a.record()
+            for _ in range(10):
+                _check(LIB.nn_channel_sum(0, B, 64, S, x.data_ptr(), out.data_ptr(), ws.data_ptr(), nb, st))
+            b.record()
+            b.synchronize()
+            times.append(a.elapsed_time(b))
+        best[S] = min(times[1:])
+    assert best[1] < 6 * best[256], best
