@@ -1060,7 +1060,8 @@ __global__ void __launch_bounds__(256) knn_seed_kernel(int M, int ng, int k,
     for (int u = 0; u < R; ++u) {
         const int g = u * 64 + lane;                  // all loads in flight at once
         const uint32_t x = gmin[(size_t)row * ng + min(g, ng - 1)];
-        v[u] = g < ng ? x : ~0u;
+        // Below the key of -infinity: a NaN hides the group's smallest distance, so it counts for none.
+        v[u] = g < ng && x >= 0x007fffffu ? x : ~0u;
     }
     // A key with at least k minima <= it, and not many more (any such key is a bound: the search
     // stops early), between the smallest and the largest of them: bisection, ballot counts.

@@ -144,3 +144,32 @@ def test_knn_few_queries(fmt, M, N, dim, ks):
     for k in ks:
         say(f"knn few queries fmt {fmt} {M} x {N} x {dim} k = {k}")
         _check_equal(Q, X, k)
+
+
+@pytest.mark.parametrize("fmt,M", [(0, 5), (0, 40), (0, 70), (1, 5)])
+@pytest.mark.parametrize("N", [5000, 40_000])
+def test_knn_of_few_queries_leaves_nans_out(fmt, M, N):
+    """Queries and entries with infinities and NaNs: the nearest by the distances that are numbers,
+    infinite ones too, below and above the size of the sampled bound."""
+    need_gpu()
+    from paper_2205_04550_amd import binding as b
+    g = torch.Generator(device="cuda").manual_seed(43)
+    Xf, Qf = (torch.randn(n, 64, generator=g, device="cuda") for n in (N, M))
+    if fmt == 0:
+        Qf[3, 1] = float("inf")                    # half the distances infinite, half NaN
+    Qf[4, 2] = float("nan")
+    Xf[7::9, 5] = float("nan")
+    Q, X = b.Latents(Qf, fmt), b.Latents(Xf, fmt)
+    k = 6
+    say(f"knn with special values fmt {fmt} {M} x {N}")
+    D = b.emb_distances(Q, X).cpu()
+    idx, d = b.emb_knn(Q, X, k, direct=False)
+    idx, d = idx.cpu(), d.cpu()
+    for q in range(M):
+        ok = torch.nonzero(~torch.isnan(D[q]))[:, 0]
+        order = ok[torch.sort(D[q][ok], stable=True).indices][:k]
+        if len(order) < k:
+            assert len(order) == 0 and (idx[q] == -1).all()
+            continue
+        assert torch.equal(idx[q].long(), order), q
+        assert torch.equal(d[q], D[q][order]), q
