@@ -1112,7 +1112,7 @@ static size_t knn_list_bytes(int M, int N)
 {
     return KnnPlan{0, (M + kDM - 1) / kDM, knn_splits(M, N), kDM, kKnnCap}.bytes();
 }
-static KnnPlan knn_plan(int M, int N, int K, int cus)
+static KnnPlan knn_plan(int M, int N, int K, int k, int cus)
 {
     const int nt = (N + kDN - 1) / kDN, splits = knn_splits(M, N);
     KnnPlan p{0, (M + kDM - 1) / kDM, splits, kDM, kKnnCap};
@@ -1121,7 +1121,18 @@ static KnnPlan knn_plan(int M, int N, int K, int cus)
     // 50,000 92 us against 131, x 500,000 FP8 321 against 697. More rows would be read by several
     // blocks each, as the tiled kernel's are, without its sharing of them in LDS.
     const int tm = M <= 32 ? 1 : M <= 64 ? 2 : 4;
-    if (M <= kRowsMax && 64 * tm * K <= kRowsLds) {
+    // Without a sample's bound (fewer than 32,768 entries) every distance of a block's first tile
+    // enters the lists, and those of more than 128 are cut by exact values: a time that grows with M
+    // and little with N, where the tiled kernel's grows with N. Dimension 64, BF16, tiled / rows:
+    // 33 x 600, k = 100: 96 / 71 us; 64 x 2,000 106 / 116, x 4,000 123 / 118; 100 x 12,000 267 / 185;
+    // 128 x 16,000, k = 10: 152 / 207. k = 256: 32 x 4,000 139 / 199, x 8,000 291 / 203;
+    // 128 x 2,000 129 / 701.
+    const int64_t n = N;
+    const bool few = knn_sample_cols(N) ? true
+                     : k > 128          ? n >= 192 * M
+                                        : M <= 40 || (M <= 64 && n >= 48 * M) ||
+                                              (n >= 96 * M && (M <= 80 || k >= 100));
+    if (M <= kRowsMax && few && 64 * tm * K <= kRowsLds) {
         p.tm = tm;
         p.mt = 1;
         p.rows = 32 * tm;
@@ -1175,7 +1186,7 @@ hipError_t launch_knn(bool fp8, int M, int N, int K, const void *Q, const float 
     hipError_t e = hipGetDevice(&dev);
     if (e == hipSuccess) e = hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev);
     if (e != hipSuccess) return e;
-    const KnnPlan plan = knn_plan(M, N, K, cus);
+    const KnnPlan plan = knn_plan(M, N, K, k, cus);
     const int mt = plan.mt, nsplit = plan.nsplit;
     char *p = static_cast<char *>(ws);
     uint64_t *lists = reinterpret_cast<uint64_t *>(p);

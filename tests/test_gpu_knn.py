@@ -173,3 +173,44 @@ def test_knn_of_few_queries_leaves_nans_out(fmt, M, N):
             continue
         assert torch.equal(idx[q].long(), order), q
         assert torch.equal(d[q], D[q][order]), q
+
+
+@pytest.mark.parametrize("M,N,k", [(40, 300, 100), (41, 1967, 20), (41, 1968, 20), (64, 3071, 128), (64, 3072, 128),
+                                   (80, 7680, 64), (81, 7776, 64), (81, 7776, 100), (128, 12_288, 100), (4, 767, 256),
+                                   (4, 768, 129), (100, 19_200, 200)])
+def test_knn_either_side_of_the_small_database_rule(M, N, k):
+    """Databases below the sampled size, where M, N and k decide between the kernel of few queries
+    and the tiled one: equal to the distances' smallest on both sides."""
+    need_gpu()
+    from paper_2205_04550_amd import binding as b
+    g = torch.Generator(device="cuda").manual_seed(47)
+    Xf = torch.randn(N, 64, generator=g, device="cuda")
+    Xf[N // 2:] = Xf[:N - N // 2].clone()                   # ties
+    Qf = torch.randn(M, 64, generator=g, device="cuda")
+    for fmt in (0, 1):
+        say(f"knn rule fmt {fmt} {M} x {N} k = {k}")
+        _check_equal(b.Latents(Qf, fmt), b.Latents(Xf, fmt), k)
+
+
+@pytest.mark.parametrize("M,N,k", [(128, 2000, 256), (64, 600, 200), (128, 2000, 100)])
+def test_knn_of_few_queries_takes_no_longer_than_of_more(M, N, k):
+    """A search of up to 128 queries takes at most one and a half times as long as of 192."""
+    need_gpu()
+    from paper_2205_04550_amd import binding as b
+    g = torch.Generator(device="cuda").manual_seed(48)
+    X = b.Latents(torch.randn(N, 64, generator=g, device="cuda"), 0)
+    best = {}
+    for m in (M, 192):
+        Q = b.Latents(torch.randn(m, 64, generator=g, device="cuda"), 0)
+        ws = b.knn_workspace(m, N, k)
+        times = []
+        for _ in range(6):
+            e0, e1 = torch.cuda.Event(enable_timing=True), torch.cuda.Event(enable_timing=True)
+            e0.record()
+            for _ in range(5):
+                b.emb_knn(Q, X, k, direct=False, ws=ws)
+            e1.record()
+            e1.synchronize()
+            times.append(e0.elapsed_time(e1))
+        best[m] = min(times[1:])
+    assert best[M] < 1.5 * best[192], best
