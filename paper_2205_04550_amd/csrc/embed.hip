@@ -1866,7 +1866,11 @@ hipError_t launch_rerank_score(const db_t *db, int nq, const uint32_t *qpack, co
     // rounds, few candidates per query), else 4 kRC per block. Sixteen waves while every block has
     // a CU to itself (embedding search of one query, 16 + 84 candidates: 285 us against 299 with
     // four); with more blocks the waves of several fill a CU, and blocks that find no candidate
-    // left cost more the larger they are (50 queries, 1,000 candidates: 341 against 222 us).
+    // left cost more the larger they are (50 queries, 1,000 candidates: 341 against 222 us). Not on
+    // grids whose rows four waves cover in one pass: the others would only wait (two queries and
+    // 16 candidates of 32^3: 38 against 22 us).
+    const int pass_rows = g.nxw == 1 ? 512 : g.nxw == 2 ? 256 : g.nxw <= 4 ? 128 : 64;   // of a wave
+    const bool wide = (int64_t)g.ny * g.nz > 4 * pass_rows;
     auto score = [&](int first, int count, const int32_t *ord, const int32_t *en,
                      const int32_t *qc, bool split) {
         const int per = split ? kRC : kRerankPerBlock;
@@ -1892,7 +1896,7 @@ hipError_t launch_rerank_score(const db_t *db, int nq, const uint32_t *qpack, co
         }                                                                                         \
     } while (0)
         if (!split) TDB_RERANK_NXW(1);
-        else if ((int64_t)nq * nbq <= db->cus) TDB_RERANK_NXW(16);
+        else if (wide && (int64_t)nq * nbq <= db->cus) TDB_RERANK_NXW(16);
         else TDB_RERANK_NXW(4);
 #undef TDB_RERANK_NXW
 #undef TDB_RERANK_SCORE

@@ -136,3 +136,26 @@ def test_rerank_row_widths(dims, nq):
             assert np.array_equal(i[q], best), q
             assert np.array_equal(s[q].view(np.uint64), sc[best].view(np.uint64)), q
             assert np.array_equal(c[q].view(np.uint32).astype(np.uint64), cnt[best]), q
+
+
+@pytest.mark.parametrize("dims", [(32, 32, 64), (32, 32, 65), (64, 32, 32), (64, 33, 32), (96, 16, 32), (128, 27, 19),
+                                  (160, 16, 16), (160, 16, 17)])
+def test_rerank_either_side_of_four_waves_rows(dims):
+    """Grids whose rows four waves cover in one pass and the next larger ones (16 waves for few
+    queries): a rerank of every entry is the exact query."""
+    need_gpu()
+    from paper_2205_04550_amd import TumorDB
+    nx, ny, nz = dims
+    n, k = 64, 9
+    say(f"rerank of every entry {dims}")
+    g = torch.Generator(device="cuda").manual_seed(sum(dims))
+    conc = torch.rand((n, nz, ny, nx), generator=g, device="cuda")
+    conc[:, nz // 2 :, : ny // 3] *= 0.3
+    db = TumorDB(nx, ny, nz, n, synth.T_LO, synth.T_HI)
+    db.append(conc)
+    labels = torch.randint(0, 5, (2, nz, ny, nx), generator=g, device="cuda", dtype=torch.uint8)
+    cand = torch.stack([torch.randperm(n, generator=g, device="cuda") for _ in range(2)]).to(torch.int32)
+    got = db.rerank(labels, cand, k)
+    for q in range(2):
+        for a, b in zip(got, db.query(labels[q], k)):
+            assert torch.equal(a[q], b), q
