@@ -71,6 +71,13 @@ def test_append_one_pass(dims, n, t_lo):
         assert np.array_equal(db.block_counts[:n].cpu().numpy().astype(np.uint16), want)
 
 
+@pytest.mark.parametrize("dims,n", [((32, 4, 8), 7), ((32, 8, 9), 1030), ((64, 8, 13), 6), ((32, 2, 100), 5),
+                                    ((32, 33, 8), 1025)])
+def test_append_with_few_waves(dims, n):
+    """Grids of fewer word groups than a block has waves elsewhere: one wave to all of them."""
+    test_append_one_pass(dims, n, 0.25)
+
+
 def test_append_of_millions_of_tiny_entries():
     """More entries than one launch takes threads for, in one call."""
     need_gpu()
