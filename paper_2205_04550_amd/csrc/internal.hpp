@@ -229,7 +229,7 @@ hipError_t launch_conv_fwd_direct(bool bf16w, bool chunk4, int B, int Ci, int Co
                                   float *Y, hipStream_t s);
 // C[m][n] = act(bias[n] + sum_k A[m][k] W(k, n)) of a small batch, W [N][K] or (kn) [K][N]; K and
 // (kn) N multiples of 4, sizes for which linear_small_ok holds. The bits of linear_mfma_kernel.
-bool linear_small_ok(int M, int N, int K);
+bool linear_small_ok(bool kn, int M, int N, int K);
 hipError_t launch_linear_small(bool bf16w, bool kn, int M, int N, int K, const float *A, const void *Wt,
                                const float *bias, int relu, float *C, hipStream_t s);
 bool linear_wgrad_ok(int B, int In, int Out);

@@ -2724,7 +2724,7 @@ int nn_linear_fwd(int dtype, int B, int In, int Out, const void *X, const void *
     // The matrix-core path loads four k at a time: rows and bases must be aligned to that.
     const size_t wal = pair == 0 ? 8 : 16;
     const bool vec = In % 4 == 0 && (uintptr_t)X % 16 == 0 && (uintptr_t)Wt % wal == 0;
-    if (pair <= 1 && vec && linear_small_ok(B, Out, In))
+    if (pair <= 1 && vec && linear_small_ok(false, B, Out, In))
         return launched("nn_linear_fwd", launch_linear_small(pair == 0, false, B, Out, In, (const float *)X, Wt,
                                                              (const float *)bias, relu, (float *)Y, s));
     else if (pair == 0 && vec)
@@ -2763,7 +2763,7 @@ int nn_linear_bwd_data(int dtype, int B, int In, int Out, const void *dY, const 
     const size_t wal = pair == 0 ? 8 : 16;
     const bool vec = In % 4 == 0 && Out % 4 == 0 && (uintptr_t)dY % 16 == 0 &&
                      (uintptr_t)Wt % wal == 0;
-    if (pair <= 1 && vec && linear_small_ok(B, In, Out))
+    if (pair <= 1 && vec && linear_small_ok(true, B, In, Out))
         return launched("nn_linear_bwd_data",
                         launch_linear_small(pair == 0, true, B, In, Out, (const float *)dY, Wt, nullptr, 0,
                                             (float *)dX, s));

@@ -1128,11 +1128,23 @@ hipError_t linear_small_launch(const LinArgs &a, const WT *Wt, hipStream_t s)
 
 }  // namespace
 
-bool linear_small_ok(int M, int N, int K)
+bool linear_small_ok(bool kn, int M, int N, int K)
 {
-    // 31-bit byte offsets; up to 1,024 pairs of waves, beyond which the 64 x 64 tiles' reuse wins.
-    return (int64_t)((M + 15) / 16) * ((N + 15) / 16) <= 1024 && (int64_t)M * K * 4 < ((int64_t)1 << 31) &&
-           (int64_t)N * K * 4 < ((int64_t)1 << 31);
+    if ((int64_t)M * K * 4 >= ((int64_t)1 << 31) || (int64_t)N * K * 4 >= ((int64_t)1 << 31)) return false;   // 31-bit byte offsets
+    // While the pairs of waves run side by side (256 CUs, a second round hidden by long chains) a
+    // launch takes as long as one chain, which the 64 x 64 tiles walk at a third of the pace; with
+    // more of them the tiles' reuse wins. 64 x 64 tiles / pairs, forward: 256 pairs, K = 68: 5.8 / 4.8
+    // us, K = 4,096: 88 / 33; 512 pairs, K = 256: 8.4 / 8.8, K = 320: 9.7 / 9.6, K = 4,096: 87 / 62; 1,024
+    // pairs, K = 4,096: 89 / 120. A chain of one chunk of 64 pays only for rows past the first tile:
+    // 4 rows 4.2 / 4.7, 32 rows 5.3 / 4.8.
+    const int64_t my = (M + 15) / 16;
+    if (!kn) return (K > 64 || M >= 32) && my * ((N + 15) / 16) <= (K > 256 ? 512 : 256);
+    // Input gradient, in groups of 64 columns (BF16 weights, the tiles' better type): 256 groups, K = 256:
+    // 10.9 / 9.7; 512, K = 256: 11.2 / 12.9, K = 1,024: 35 / 31, K = 4,096: 150 / 104; 1,024, K = 1,024 (float)
+    // 34 / 46. Two chunks of 64: 4 rows 5.9 / 5.9, 32 rows in pairs of one column tile 7.1 / 6.2, of four (128
+    // groups and more) 6.7 / 8.0.
+    const int64_t groups = my * ((N + 63) / 64);
+    return K > 128 ? groups <= (K > 256 ? 512 : 256) : K > 64 && M >= 32 && groups < 128;
 }
 
 hipError_t launch_linear_small(bool bf16w, bool kn, int M, int N, int K, const float *A, const void *Wt,

@@ -205,6 +205,15 @@ def test_linear_small_batch(shape):
             assert ok, (shape, name, worst)
 
 
+@pytest.mark.parametrize("shape", [(16, 68, 4096), (16, 68, 4112), (31, 64, 64), (32, 64, 64), (32, 256, 4096),
+                                   (32, 260, 4096), (32, 260, 4112), (4, 256, 128), (4, 256, 132), (31, 64, 68),
+                                   (32, 64, 128), (32, 4032, 68), (32, 4096, 68), (64, 4096, 256), (64, 4160, 256),
+                                   (32, 16384, 260), (48, 16384, 260)])
+def test_linear_either_side_of_the_small_batch_rule(shape):
+    """Rows, columns and terms where the kernels of a small batch give way to the 64 x 64 tiles."""
+    test_linear_small_batch(shape)
+
+
 def test_adam_of_several_tensors_equals_one_by_one():
     """One launch for 37 tensors (more than a table holds, sizes around a block of 1,024 and
     pointers off 16 bytes) leaves the bits of a launch per tensor."""
