@@ -223,7 +223,7 @@ hipError_t launch_conv_adjoint(bool bf16w, int B, int Ci, int Co, int D, int H, 
                                float *dX, hipStream_t s);
 // Forward Y = conv(X) + bias; chunk4: the order of sums of the staged matrix-core kernel (Ci in
 // chunks of four, bias last), else of the vector kernel. Sizes for which conv_fwd_direct_ok holds.
-bool conv_fwd_direct_ok(int B, int Ci, int Co, int D, int H, int W, bool chunk4);
+bool conv_fwd_direct_ok(bool bf16w, int B, int Ci, int Co, int D, int H, int W, bool chunk4);
 hipError_t launch_conv_fwd_direct(bool bf16w, bool chunk4, int B, int Ci, int Co, int D, int H,
                                   int W, const float *X, const void *Wt, const float *bias, int relu,
                                   float *Y, hipStream_t s);

@@ -2576,7 +2576,7 @@ int nn_conv3d_s2_fwd(int dtype, int B, int Ci, int Co, int D, int H, int W, cons
     const hipStream_t s = static_cast<hipStream_t>(stream);
     const bool staged = Ci % 4 == 0 && W % 4 == 0 && (uintptr_t)X % 16 == 0 && Co <= 64 &&
                         B <= 65535 && (int64_t)D * H * W * 4 < ((int64_t)1 << 31);
-    if (pair <= 1 && conv_fwd_direct_ok(B, Ci, Co, D, H, W, staged)) {
+    if (pair <= 1 && conv_fwd_direct_ok(pair == 0, B, Ci, Co, D, H, W, staged)) {
         return launched("nn_conv3d_s2_fwd",
                         launch_conv_fwd_direct(pair == 0, staged, B, Ci, Co, D, H, W, (const float *)X, Wt,
                                                (const float *)bias, relu, (float *)Y, s));

@@ -14,6 +14,7 @@
 #include <hip/hip_runtime.h>
 
 #include <algorithm>
+#include <cmath>
 #include <type_traits>
 
 #include "../../include/tumornn.h"
@@ -877,16 +878,61 @@ int fwd_products(int Ci, bool chunk4)
 
 }  // namespace
 
-bool conv_fwd_direct_ok(int B, int Ci, int Co, int D, int H, int W, bool chunk4)
+// Times of the forward kernels in us, fitted to 1,400 shapes and more of each weight type with inputs not
+// in the L2 (within 5 to 13 %): the rule below compares them. A chain of dependent steps while the waves
+// fit the chip side by side, else the rate of its products. groups: groups of 16 voxels; nt, nb: tiles
+// of 16 (blocks of 8 or 16) coarse channels.
+static double direct_us(double groups, int nt, int NK, int Ci, int64_t isp, int OW, bool chunk4)
 {
-    const int64_t osp = (int64_t)(D / 2) * (H / 2) * (W / 2), P = (int64_t)B * osp;
-    // By chunk with rows of 16 and more voxels the staged kernel is as fast (24 us against 26 for
-    // 8 -> 16 at batch 32); by channel, two fine channels leave the lanes half idle (72 us
-    // against 49 for the vector kernel, 2 -> 8 at 64^3) unless the first layer's kernel takes them.
-    if (chunk4 ? (W / 2) % 16 == 0 : Ci <= 2 && W % 8 != 0) return false;
-    if (fwd_products(Ci, chunk4) > kFwdMaxNK || Co > 1024 || P >= ((int64_t)1 << 31) - 65536) return false;
+    const bool big = groups * nt >= 8192;                // two groups per wave
+    if (!chunk4) return 5.3 + .125 * Ci + NK * std::max(Ci % 4 ? .03 : .021, groups * nt * 53e-6);
+    // Channels a multiple of 2 KB apart lie on the same few L2 channels.
+    const bool same = isp % 512 == 0;
+    const double chain = NK * (OW < 4 ? .054 : same ? .048 : .036) + .17 * Ci;
+    const double rate = groups * nt * NK * (big ? 44e-6 : 54e-6) * (same ? 1.22 : 1);
+    return 7.5 + .07 * nt + std::cbrt(chain * chain * chain + rate * rate * rate);
+}
+// conv_mfma_kernel: its boxes of voxels, npb of a sample in turn per block, a stage per four fine
+// channels, most of it the wait for its loads; BF16 weights are widened on their way into LDS.
+static double staged_us(bool bf16w, int B, int Ci, int OD, int OH, int OW, int nt)
+{
+    static const double stage[2][3][4] = {
+        {{1.1, 1.7, 2.4, 3.15}, {1.8, 3.25, 4.5, 5.7}, {2.0, 3.4, 4.75, 6.2}},     // float weights
+        {{1.7, 3.3, 4.7, 6.0}, {2.4, 4.6, 6.45, 8.25}, {2.4, 4.5, 6.4, 8.3}}};
+    const int box = OW >= 16 ? 2 : OW >= 8 ? 1 : 0, td = box == 2 ? 2 : 4, tw = 4 << box, stages = Ci / 4;
+    const int64_t T = (int64_t)((OD + td - 1) / td) * ((OH + 3) / 4) * ((OW + tw - 1) / tw);
+    const int npb = T >= 64 ? 4 : T >= 16 ? 2 : 1;
+    const double boxes = (double)B * T * td * 4 * tw / 16384, chain = npb * stages * stage[bf16w][box][std::min(nt, 4) - 1];
+    const double start = bf16w ? 5.8 + 1.2 * nt : 6.1 + .65 * nt;
+    return start + std::max(chain + (bf16w ? .75 : 1.5) * npb, boxes * stages * nt);
+}
+// conv_fwd_kernel.
+static double vector_us(double P, int Ci, int Co, bool wide)
+{
+    const int cb = wide ? 16 : 8, nb = (Co + cb - 1) / cb;
+    return 3.5 + std::hypot(Ci * (.98 + .12 * cb), Ci * P * nb * (8 + cb) * 1e-6);
+}
+
+bool conv_fwd_direct_ok(bool bf16w, int B, int Ci, int Co, int D, int H, int W, bool chunk4)
+{
+    const int OD = D / 2, OH = H / 2, OW = W / 2;
+    const int64_t osp = (int64_t)OD * OH * OW, P = (int64_t)B * osp;
+    const int NK = fwd_products(Ci, chunk4);
+    if (P >= ((int64_t)1 << 31) - 65536) return false;
     // A block's voxels (at most 1,024) lie in these samples, addressed with 31-bit byte offsets.
-    return ((1023 / osp + 2) * Ci + 4) * (8 * osp) * 4 < ((int64_t)1 << 31);
+    if (((1023 / osp + 2) * Ci + 4) * (8 * osp) * 4 >= ((int64_t)1 << 31)) return false;
+    // The first layer's kernel takes rows of whole fours. Other rows of two channels leave the lanes of
+    // the matrix products half idle (72 us against 49 for the vector kernel, 2 -> 8 at 64^3).
+    if (Ci <= 2) return W % 8 == 0;
+    if (NK > kFwdMaxNK || Co > 1024) return false;
+    // By chunk, rows of 16 and more voxels fill the staged kernel's boxes (24 us against 26, 8 -> 16 at
+    // batch 32). Otherwise the estimates decide, with a margin for their errors: short sums of few
+    // channels and many samples whose boxes are full go to the other kernels (float weights, 12 -> 16 on
+    // 4^3, batch 100: staged 8 / direct 12; 28 -> 8 on 8^3, batch 100: 29 / 54; 3 -> 24 on 10 x 10 x 11:
+    // vector 25 / 36), batch 32, BF16 weights, 16 -> 32 on 8^3 and 32 -> 64 on 4^3 stay (28 / 20 and 67 / 21).
+    const double direct = direct_us((double)((P + 15) / 16), (Co + 15) / 16, NK, Ci, 8 * osp, OW, chunk4);
+    if (chunk4) return OW % 16 != 0 && 1.05 * direct < staged_us(bf16w, B, Ci, OD, OH, OW, (Co + 15) / 16);
+    return 1.15 * direct < vector_us((double)P, Ci, Co, Co >= 16 && (int64_t)D * H * W <= 4096);
 }
 
 hipError_t launch_conv_fwd_direct(bool bf16w, bool chunk4, int B, int Ci, int Co, int D, int H,

@@ -331,3 +331,16 @@ def test_channel_sum_of_single_positions_takes_no_longer():
             times.append(a.elapsed_time(b))
         best[S] = min(times[1:])
     assert best[1] < 6 * best[256], best
+
+
+# (B, Ci, Co, D, H, W) either side of the estimates' lines: short and long sums, few and many samples,
+# full and empty boxes, one to four tiles of coarse channels; by chunk, then by channel.
+FORWARD_RULE = [(16, 12, 16, 4, 4, 4), (100, 12, 16, 8, 8, 8), (2, 12, 33, 20, 20, 20), (100, 28, 8, 16, 16, 16),
+                (2, 28, 8, 16, 16, 16), (3, 32, 64, 6, 14, 8), (1, 4, 24, 40, 40, 40), (64, 4, 17, 24, 24, 24),
+                (200, 32, 64, 8, 8, 8), (7, 16, 32, 12, 12, 12), (100, 3, 24, 20, 20, 22), (2, 3, 24, 20, 20, 22),
+                (16, 5, 100, 20, 20, 22), (1, 9, 100, 6, 6, 6)]
+
+
+@pytest.mark.parametrize("shape", FORWARD_RULE)
+def test_conv_forward_either_side_of_the_rule(shape):
+    test_conv_forward(shape)
