@@ -544,8 +544,10 @@ __global__ void __launch_bounds__(256) channel_sum_partial(int B, int C, int64_t
     const int64_t P = (int64_t)B * S;
     const int64_t p0 = (int64_t)blockIdx.x * kCsChunk;
     const int n = (int)(P - p0 < kCsChunk ? P - p0 : kCsChunk);
-    int64_t b = (p0 + threadIdx.x) / S, sidx = p0 + threadIdx.x - b * S;
-    const int64_t db = 256 / S, ds = 256 - db * S;       // 256 positions on
+    const int64_t b = (p0 + threadIdx.x) / S;
+    int64_t sidx = p0 + threadIdx.x - b * S, pos = (b * C + c) * S + sidx;
+    // 256 positions on: whole rows and a rest, which may end in the row after.
+    const int64_t db = 256 / S, ds = 256 - db * S, step = db * C * S + ds, wrap = (int64_t)(C - 1) * S;
     T acc = T(0);
     constexpr int U = 8;
     for (int i = threadIdx.x; i < n; i += 256 * U) {
@@ -553,14 +555,14 @@ __global__ void __launch_bounds__(256) channel_sum_partial(int B, int C, int64_t
         int64_t at[U];
 #pragma unroll
         for (int u = 0; u < U; ++u) {
-            at[u] = i + 256 * u < n ? (b * C + c) * S + sidx : (int64_t)c * S;
+            at[u] = i + 256 * u < n ? pos : (int64_t)c * S;
             v[u] = X[at[u]];
             if (RELU) m[u] = Y[at[u]];
-            b += db;
+            pos += step;
             sidx += ds;
             if (sidx >= S) {
                 sidx -= S;
-                ++b;
+                pos += wrap;
             }
         }
 #pragma unroll
