@@ -565,6 +565,7 @@ __global__ void __launch_bounds__(256) channel_sum_partial(int B, int C, int64_t
                 pos += wrap;
             }
         }
+        __builtin_amdgcn_sched_barrier(0);               // no use before the last load is issued
 #pragma unroll
         for (int u = 0; u < U; ++u) {
             const bool in = i + 256 * u < n;
