@@ -351,3 +351,149 @@ def test_conv_forward_either_side_of_the_rule(shape):
 def test_conv_adjoint_of_few_coarse_channels(shape):
     """Two and four coarse channels, where the general kernel takes over."""
     test_conv_adjoint(shape)
+
+
+# The training kernels' sums run in the order of the general kernels, bit for bit. Each is compared with
+# the general kernel on a call that holds the same sums among others: a wider volume, more channels or
+# columns, a channel of zeros.
+
+def _cases(w):
+    return (w.cuda(), w.cuda()), (w.to(torch.bfloat16).float().cuda(), w.to(torch.bfloat16).cuda())
+
+
+@pytest.mark.parametrize("shape", [(2, 8, 16, 10, 12, 24), (3, 16, 33, 6, 6, 8), (2, 32, 64, 8, 8, 4), (1, 20, 40, 4, 6, 20)])
+def test_conv_forward_by_chunk_has_the_staged_kernels_bits(shape):
+    """Rows of 16 voxels and more go to the staged kernel: the same columns of a volume of 64."""
+    need_gpu()
+    from paper_2205_04550_amd import nn
+    B, Ci, Co, D, H, W = shape
+    g = torch.Generator().manual_seed(sum(shape) + 11)
+    wide = torch.randn(B, Ci, D, H, 64, generator=g)
+    w, b = torch.randn(Co, Ci, 3, 3, 3, generator=g), torch.randn(Co, generator=g).cuda()
+    for wf, wc in _cases(w):
+        say(f"bits forward by chunk {shape} {wc.dtype}")
+        y = nn.Conv3dS2.apply(wide[..., :W].contiguous().cuda(), wf, b, wc, True)
+        ref = nn.Conv3dS2.apply(wide.cuda(), wf, b, wc, True)
+        assert torch.equal(y, ref[..., :W // 2])
+
+
+@pytest.mark.parametrize("shape", [(2, 3, 9, 6, 8, 10), (2, 8, 16, 6, 6, 6), (1, 9, 20, 10, 6, 14), (3, 31, 33, 4, 4, 6),
+                                   (2, 32, 64, 6, 6, 6)])
+def test_conv_forward_by_channel_has_the_vector_kernels_bits(shape):
+    """More than 1,024 coarse channels go to the vector kernel: the first of them."""
+    need_gpu()
+    from paper_2205_04550_amd import nn
+    B, Ci, Co, D, H, W = shape
+    g = torch.Generator().manual_seed(sum(shape) + 12)
+    x = torch.randn(B, Ci, D, H, W, generator=g).cuda()
+    w, b = torch.randn(1032, Ci, 3, 3, 3, generator=g), torch.randn(1032, generator=g).cuda()
+    for wf, wc in _cases(w):
+        say(f"bits forward by channel {shape} {wc.dtype}")
+        y = nn.Conv3dS2.apply(x, wf[:Co].contiguous(), b[:Co].contiguous(), wc[:Co].contiguous(), False)
+        ref = nn.Conv3dS2.apply(x, wf, b, wc, False)
+        assert torch.equal(y, ref[:, :Co])
+
+
+@pytest.mark.parametrize("shape", [(2, 2, 8, 8, 6, 64), (3, 1, 11, 6, 10, 24), (40, 2, 5, 4, 4, 8)])
+def test_first_layer_forward_has_the_vector_kernels_bits(shape):
+    """Rows that are not whole fours of outputs go to the vector kernel: a volume one pair wider."""
+    need_gpu()
+    from paper_2205_04550_amd import nn
+    B, Ci, Co, D, H, W = shape
+    g = torch.Generator().manual_seed(sum(shape) + 13)
+    wide = torch.randn(B, Ci, D, H, W + 2, generator=g)
+    w, b = torch.randn(Co, Ci, 3, 3, 3, generator=g), torch.randn(Co, generator=g).cuda()
+    for wf, wc in _cases(w):
+        say(f"bits first layer {shape} {wc.dtype}")
+        y = nn.Conv3dS2.apply(wide[..., :W].contiguous().cuda(), wf, b, wc, False)
+        ref = nn.Conv3dS2.apply(wide.cuda(), wf, b, wc, False)
+        assert torch.equal(y, ref[..., :W // 2])
+
+
+@pytest.mark.parametrize("shape", [(2, 2, 8, 10, 12, 32), (3, 1, 4, 6, 10, 6), (2, 2, 40, 4, 6, 8), (2, 8, 16, 6, 8, 32),
+                                   (3, 3, 10, 6, 10, 14), (2, 16, 32, 10, 6, 18), (3, 32, 64, 8, 8, 8)])
+def test_conv_adjoint_has_the_general_kernels_bits(shape):
+    """An odd count of coarse channels goes to the general kernel: one of zero weights more."""
+    need_gpu()
+    from paper_2205_04550_amd import nn
+    B, Ci, Co, D, H, W = shape
+    g = torch.Generator().manual_seed(sum(shape) + 14)
+    x = torch.randn(B, Co + 1, D // 2, H // 2, W // 2, generator=g).cuda()
+    w, b = torch.randn(Co + 1, Ci, 3, 3, 3, generator=g), torch.randn(Ci, generator=g).cuda()
+    w[Co] = 0.0
+    for wf, wc in _cases(w):
+        say(f"bits adjoint {shape} {wc.dtype}")
+        y = nn.ConvT3dS2.apply(x[:, :Co].contiguous(), wf[:Co].contiguous(), b, wc[:Co].contiguous(), False)
+        assert torch.equal(y, nn.ConvT3dS2.apply(x, wf, b, wc, False))
+
+
+@pytest.mark.parametrize("shape", [(32, 512, 64), (7, 132, 36), (17, 1028, 16), (33, 320, 200), (5, 4096, 16)])
+def test_linear_of_a_small_batch_has_the_tiles_bits(shape):
+    """The outputs (and input gradients) of a layer with thousands of columns, which goes to the
+    64 x 64 tiles, and the weight gradient of one more input, which goes to the general kernel."""
+    need_gpu()
+    from paper_2205_04550_amd import nn
+    from paper_2205_04550_amd.nn import LIB, _check
+    B, K, N = shape
+    g = torch.Generator().manual_seed(sum(shape) + 15)
+    a, w, b = torch.randn(B, K, generator=g).cuda(), torch.randn(16640, K, generator=g), torch.randn(16640, generator=g).cuda()
+    st = torch.cuda.current_stream().cuda_stream
+    for wf, wc in _cases(w):
+        say(f"bits linear {shape} {wc.dtype}")
+        assert torch.equal(nn.Linear.apply(a, wf[:N].contiguous(), b[:N].contiguous(), wc[:N].contiguous(), True),
+                           nn.Linear.apply(a, wf, b, wc, True)[:, :N])
+        out = []
+        for n in (N, 16640):                                   # dX [B][n] from dY [B][K], W [K][n]
+            wt, dx = wc[:n].t().contiguous(), torch.empty(B, n, device="cuda")
+            _check(LIB.nn_linear_bwd_data(0, B, n, K, a.data_ptr(), wt.data_ptr(), nn._wdt(wt), dx.data_ptr(), st))
+            out.append(dx)
+        assert torch.equal(out[0], out[1][:, :N])
+    x, grads = torch.randn(B, K + 1, generator=g).cuda(), []
+    dy = torch.randn(B, N, generator=g).cuda()
+    for i in (K, K + 1):
+        xi, dw, db = x[:, :i].contiguous(), torch.empty(N, i, device="cuda"), torch.empty(N, device="cuda")
+        _check(LIB.nn_linear_bwd_weight(0, B, i, N, xi.data_ptr(), dy.data_ptr(), dw.data_ptr(), db.data_ptr(), st))
+        grads.append((dw, db))
+    assert torch.equal(grads[0][0], grads[1][0][:, :K]) and torch.equal(grads[0][1], grads[1][1])
+
+
+@pytest.mark.parametrize("shape", [(2, 2, 8, 8, 6, 64), (3, 3, 5, 6, 10, 6), (5, 4, 9, 24, 24, 24)])
+def test_conv_weight_gradient_bits(shape):
+    """The order of conv_bwd_weight_partial and _final: a thread every 256th position of a chunk of
+    4,096 as fused multiply-adds, lanes by halves, four waves, chunks. Inputs of 12 bits near one, so
+    that float64 holds every sum before its rounding exactly."""
+    need_gpu()
+    from paper_2205_04550_amd import nn
+    B, Ci, Co, D, H, W = shape
+    rng = np.random.default_rng(sum(shape))
+    f = np.float32
+    draw = lambda *s: (rng.integers(512, 2048, s) * rng.choice((-1, 1), s) / 1024).astype(f)
+    x, gy = draw(B, Ci, D, H, W), draw(B, Co, D // 2, H // 2, W // 2)
+    say(f"bits weight gradient {shape}")
+    P = gy[:, 0].size
+    pad = np.pad(x, ((0, 0), (0, 0), (1, 0), (1, 0), (1, 0)))
+    taps = np.stack([pad[:, :, kd:kd + D:2, kh:kh + H:2, kw:kw + W:2] for kd in range(3) for kh in range(3)
+                     for kw in range(3)], 2).transpose(1, 2, 0, 3, 4, 5).reshape(Ci * 27, P)
+    taps = np.concatenate([taps.reshape(Ci, 27, P), np.ones((Ci, 1, P), f)], 1).reshape(Ci * 28, P)
+    g = gy.transpose(1, 0, 2, 3, 4).reshape(Co, P)
+    total = np.zeros((Co, Ci * 28), f)
+    for p0 in range(0, P, 4096):
+        n = min(4096, P - p0)
+        acc = np.zeros((Co, Ci * 28, 256), f)
+        for i in range(0, n, 256):
+            m = min(256, n - i)
+            at = slice(p0 + i, p0 + i + m)
+            acc[..., :m] = (acc[..., :m].astype(np.float64) + g[:, None, at].astype(np.float64) * taps[None, :, at]).astype(f)
+        v = acc.reshape(Co, Ci * 28, 4, 64)
+        while v.shape[-1] > 1:
+            h = v.shape[-1] // 2
+            v = v[..., :h] + v[..., h:]
+        v = v[..., 0]
+        total = total + (((v[..., 0] + v[..., 1]) + v[..., 2]) + v[..., 3])
+    total = total.reshape(Co, Ci, 28)
+    w = torch.zeros(Co, Ci, 3, 3, 3, device="cuda").requires_grad_()
+    b = torch.zeros(Co, device="cuda").requires_grad_()
+    y = nn.Conv3dS2.apply(torch.from_numpy(x).cuda(), w, b, w.detach(), False)
+    gw, gb = torch.autograd.grad(y, (w, b), torch.from_numpy(gy).cuda())
+    assert np.array_equal(gw.cpu().numpy().reshape(Co, Ci, 27), total[:, :, :27])
+    assert np.array_equal(gb.cpu().numpy(), total[:, 0, 27])
