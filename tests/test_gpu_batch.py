@@ -213,3 +213,44 @@ def test_batch_kinds_alternate_on_one_handle():
             db.sync()
             _compare(res, ref[:nq], k)
             assert sorted(_host(db.tile_order[:have])) == list(range(have))
+
+
+def test_batch_matrix_core_kernel_counts_up_to_its_limit():
+    """The largest grid that the matrix-core kernel takes (16.77 of 2^24 voxels), masks that fill it
+    and boxes of all or nearly all of it, with tiles enough that none is split over blocks: every
+    voxel adds one to a float accumulator, and the counts are the boxes' voxels exactly."""
+    need_gpu()
+    from paper_2205_04550_amd import TumorDB
+    nx, ny, nz = dims = (128, 362, 362)
+    n, nq, k = 8192, 2048, 384                              # 128 tiles of 64 x 8 chunks of 256
+    if torch.cuda.mem_get_info()[0] < (100 << 30):
+        pytest.skip("needs 100 GiB")
+    say(f"batch on matrix cores: {nq} queries, {n} entries, {dims}")
+    conc = torch.ones((64, nz, ny, nx), device="cuda")
+    for e in range(64):                                     # entry e lacks its first e slices
+        conc[e, :e] = 0.0
+    db = TumorDB(*dims, n, T_LO, T_HI)
+    for _ in range(n // 64):
+        db.append(conc)
+    torch.cuda.synchronize()
+    del conc
+    labels = torch.full((nq, nz, ny, nx), 3, dtype=torch.uint8, device="cuda")
+    rois = np.tile((0, 0, 0) + dims, (nq, 1)).astype(np.int32)
+    rois[1::3, 0] = 1
+    rois[2::3, 4] = ny - 5
+    idx, score, counts = (_host(t) for t in db.query_batch(labels, rois, k))
+    db.sync()
+    # The best: the 128 entries without a slice less, then those that lack one, then two.
+    order = [e + 64 * i for e in range(3) for i in range(n // 64)]
+    lacks = np.repeat(np.arange(3), n // 64)
+    side = (rois[:, 3:] - rois[:, :3]).astype(np.int64)
+    box = side.prod(1)
+    b = box[:, None] - lacks[None] * (side[:, 0] * side[:, 1])[:, None]
+    assert (idx == np.array(order)).all()
+    c = counts.view(np.uint32).astype(np.int64)
+    assert (c[..., 0:2] == b[..., None]).all() and (c[..., 4:6] == b[..., None]).all()
+    assert (c[..., 2:4] == box[:, None, None]).all()
+    want = 2.0 * b / (box[:, None] + b)
+    assert np.array_equal(score, want + want)
+    del db, labels
+    torch.cuda.empty_cache()
