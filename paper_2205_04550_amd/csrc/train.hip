@@ -337,20 +337,36 @@ struct AdjArgs {
 };
 constexpr int kAdjNG = 2;                        // groups that go together (shared weights)
 
-// One output by the direct loop.
+// One output by the direct loop, four taps' loads before their sums: along an axis an odd voxel has tap 0
+// on coarse voxel j + 1, then tap 2 on j, an even one tap 1 on j.
 template <class WT>
 __device__ float adjoint_direct(const AdjArgs &a, const WT *Wt, int b, int ci, int id, int ih, int iw)
 {
-    const int OD = a.D / 2, OH = a.H / 2, OW = a.W / 2;
-    const int64_t osp = (int64_t)OD * OH * OW;
+    const int OD = a.D / 2, OH = a.H / 2, OW = a.W / 2, osp = OD * OH * OW;
+    const int z0 = (id + 1) >> 1, y0 = (ih + 1) >> 1, x0 = (iw + 1) >> 1;
+    const int tap0 = (id & 1 ? 0 : 9) + (ih & 1 ? 0 : 3) + (iw & 1 ? 0 : 1);
+    const float *g = a.dY + (int64_t)b * a.Co * osp + (z0 * OH + y0) * OW + x0;
+    const WT *w = Wt + (int64_t)ci * 27 + tap0;
     float s = a.bias ? a.bias[ci] : 0.f;
-    for (int co = 0; co < a.Co; ++co)
-        for (int t = 0; t < 27; ++t) {
-            const int z = id + 1 - t / 9, y = ih + 1 - t / 3 % 3, x = iw + 1 - t % 3;
-            if (((z | y | x) & 1) || (z >> 1) >= OD || (y >> 1) >= OH || (x >> 1) >= OW) continue;
-            const float g = a.dY[((int64_t)b * a.Co + co) * osp + ((z >> 1) * OH + (y >> 1)) * OW + (x >> 1)];
-            s = __builtin_fmaf(wt_f32(Wt[((int64_t)co * a.Ci + ci) * 27 + t]), g, s);
+#pragma unroll 1
+    for (int k = 0; k < 2 * a.Co; ++k) {                 // coarse channel k / 2, neighbour k % 2 in z
+        const int dz = k & 1;
+        const bool in = dz ? id & 1 : z0 < OD;
+        float gv[4], wv[4];
+#pragma unroll
+        for (int e = 0; e < 4; ++e) {
+            const int dy = e >> 1, dx = e & 1;
+            const bool ok = in && (dy ? ih & 1 : y0 < OH) && (dx ? iw & 1 : x0 < OW);
+            gv[e] = ok ? g[-(dz * OH + dy) * OW - dx] : 0.f;
+            wv[e] = ok ? wt_f32(w[18 * dz + 6 * dy + 2 * dx]) : 0.f;
         }
+#pragma unroll
+        for (int e = 0; e < 4; ++e) s = __builtin_fmaf(wv[e], gv[e], s);   // zero by zero adds nothing
+        if (dz) {
+            g += osp;
+            w += (int64_t)a.Ci * 27;
+        }
+    }
     return s;
 }
 
