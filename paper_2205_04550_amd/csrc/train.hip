@@ -337,7 +337,7 @@ struct AdjArgs {
 };
 constexpr int kAdjNG = 2;                        // groups that go together (shared weights)
 
-// One output by the direct loop, four taps' loads before their sums: along an axis an odd voxel has tap 0
+// One output by the direct loop, a coarse channel's loads before their sums: along an axis an odd voxel has tap 0
 // on coarse voxel j + 1, then tap 2 on j, an even one tap 1 on j.
 template <class WT>
 __device__ float adjoint_direct(const AdjArgs &a, const WT *Wt, int b, int ci, int id, int ih, int iw)
@@ -349,23 +349,19 @@ __device__ float adjoint_direct(const AdjArgs &a, const WT *Wt, int b, int ci, i
     const WT *w = Wt + (int64_t)ci * 27 + tap0;
     float s = a.bias ? a.bias[ci] : 0.f;
 #pragma unroll 1
-    for (int k = 0; k < 2 * a.Co; ++k) {                 // coarse channel k / 2, neighbour k % 2 in z
-        const int dz = k & 1;
-        const bool in = dz ? id & 1 : z0 < OD;
-        float gv[4], wv[4];
+    for (int co = 0; co < a.Co; ++co) {
+        float gv[8], wv[8];
 #pragma unroll
-        for (int e = 0; e < 4; ++e) {
-            const int dy = e >> 1, dx = e & 1;
-            const bool ok = in && (dy ? ih & 1 : y0 < OH) && (dx ? iw & 1 : x0 < OW);
+        for (int e = 0; e < 8; ++e) {
+            const int dz = e >> 2, dy = e >> 1 & 1, dx = e & 1;
+            const bool ok = (dz ? id & 1 : z0 < OD) && (dy ? ih & 1 : y0 < OH) && (dx ? iw & 1 : x0 < OW);
             gv[e] = ok ? g[-(dz * OH + dy) * OW - dx] : 0.f;
             wv[e] = ok ? wt_f32(w[18 * dz + 6 * dy + 2 * dx]) : 0.f;
         }
 #pragma unroll
-        for (int e = 0; e < 4; ++e) s = __builtin_fmaf(wv[e], gv[e], s);   // zero by zero adds nothing
-        if (dz) {
-            g += osp;
-            w += (int64_t)a.Ci * 27;
-        }
+        for (int e = 0; e < 8; ++e) s = __builtin_fmaf(wv[e], gv[e], s);   // zero by zero adds nothing
+        g += osp;
+        w += (int64_t)a.Ci * 27;
     }
     return s;
 }
@@ -506,8 +502,12 @@ __device__ __forceinline__ void adjoint_tile(const AdjArgs &a, const WT *Wt, con
 
 // grid (shares of the voxels, tiles): tiles of one fine-channel block are (pz, py) = (1, 1),
 // (1, 0), (0, 1), (0, 0), the longest first.
+// Waves per SIMD for the compiler to schedule for: with more, by its own choice, it issues fewer of the
+// loads ahead (2 <- 8, 16 <- 32: 20 to 60 % slower). Left alone (8) it keeps them for 32 and 64 channels.
 template <class WT, bool ROWS8, int CO>
-__global__ void __launch_bounds__(256) conv_adjoint_kernel(AdjArgs a, const WT *__restrict__ Wt)
+__global__ void __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(
+    ROWS8 && CO == 64 ? 2 : 1, ROWS8 ? (CO == 8 ? 5 : 2) : CO == 16 ? (sizeof(WT) == 2 ? 6 : 4) : 8)))
+conv_adjoint_kernel(AdjArgs a, const WT *__restrict__ Wt)
 {
     constexpr int CIB = ROWS8 ? 2 : 8;
     __shared__ WT wsh[CO * CIB * 27 + 1];                // and a zero for the taps a row lacks
