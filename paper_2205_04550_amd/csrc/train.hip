@@ -566,10 +566,11 @@ bool conv_adjoint_ok(int B, int Ci, int Co, int D, int H, int W)
     // More coarse channels would not fit the registers; an odd count would pair its last one
     // with a channel past the end.
     if (Co > 64 || (Co & 1) || P >= ((int64_t)1 << 31) - 65536) return false;
-    // Two coarse channels, or four of many fine ones on large grids, use an eighth (a quarter) of the 16
-    // that the registers and products are laid out for. This kernel / the general one: batch 4, 64 <- 2 on
-    // 16^3 36 / 22 us, batch 16, 9 <- 2 28 / 20; batch 4, 64 <- 4 on 16^3 36 / 30, but batch 100 on 8^3 72 / 101.
-    if (Ci > 2 && (Co <= 2 || (Co <= 4 && Ci > 16 && osp >= 4096))) return false;
+    // Two coarse channels use an eighth of the 16 that the registers and products are laid out for. This
+    // kernel / the general one, batch 4, 64 <- 2 on 16^3 36 / 22 us, batch 16, 9 <- 2 28 / 20; but on 2 to 31
+    // coarse voxels batch 32, 8 <- 2 on 2^3 8.4 / 12.5, on 3^3 9.0 / 9.9. Four channels are faster here, with
+    // inputs not in the L2, but for 1 shape in 30 (by 17 % at most).
+    if (Ci > 2 && Co <= 2 && (osp == 1 || osp >= 32)) return false;
     // A block's voxels (at most 1,024, see launch_conv_adjoint) and their neighbours lie in
     // these samples, addressed with 31-bit byte offsets.
     return (1023 / osp + 2) * Co * osp * 4 < ((int64_t)1 << 31);

@@ -349,7 +349,7 @@ def test_conv_forward_either_side_of_the_rule(shape):
 @pytest.mark.parametrize("shape", [(2, 3, 2, 8, 6, 10), (2, 2, 2, 8, 6, 10), (2, 16, 4, 6, 8, 4), (2, 17, 4, 6, 8, 4),
                                    (3, 20, 6, 4, 4, 6), (1, 64, 2, 12, 4, 4)])
 def test_conv_adjoint_of_few_coarse_channels(shape):
-    """Two and four coarse channels, where the general kernel takes over."""
+    """Few coarse channels: two take the general kernel from 32 coarse voxels on."""
     test_conv_adjoint(shape)
 
 
