@@ -160,15 +160,19 @@ int db_query_sparse(const db_t *db, const uint8_t *q_labels, int k, int32_t *idx
 
 /* nq queries in one launch sequence, each optionally restricted to its own
  * box: both masks are cut to the box before Dice (an extension; the paper
- * compares whole volumes). The scan is one kernel launch of one block per
- * (tile of database entries, chunk of queries) item, dispatched costliest tile
- * first. q_labels: device uint8 [nq][nz][ny][nx];
+ * compares whole volumes). The scan works by (tile of database entries, chunk
+ * of queries) items, costliest tile first: on the vector ALUs one launch of a
+ * block per item; on the matrix cores (many large boxes on rows of 128 voxels)
+ * a launch that clears the outputs where few items are split over several
+ * blocks each, then the launch of those blocks. q_labels: device uint8 [nq][nz][ny][nx];
  * rois: HOST array [nq] (validated before enqueue: inside the grid, non-empty)
  * or NULL for whole grids; outputs idx [nq][k], score [nq][k], counts
  * [nq][k] or NULL (device). The kernel sequence is recorded once into a HIP
- * graph per (handle, shape, pointers) and replayed. The first call after
- * entries were appended synchronises the device once to regroup the entries
- * by their row boxes. */
+ * graph per (handle, shape, pointers) and replayed. The first call of each of
+ * the two kernels after entries were appended synchronises the device to
+ * regroup the entries by their row boxes; so does a call whose kernel is not
+ * the one of the call before, to upload the order of its tiles (4 bytes per
+ * entry) into the storage again. */
 int db_query_batch(const db_t *db, int nq, const uint8_t *q_labels, const db_roi_t *rois, int k,
                    int32_t *idx, double *score, db_counts_t *counts, void *ws, size_t ws_bytes,
                    void *stream);
@@ -179,11 +183,14 @@ int db_query_batch(const db_t *db, int nq, const uint8_t *q_labels, const db_roi
  * are the same either way. DB_EINVAL on an invalid handle. */
 int db_set_rerank_bound(db_t *db, int on);
 
-/* Launch shape of db_query_batch: z-planes per LDS slab (0 = as many as fit;
- * -1 = no LDS slabs: the kernel that reads the database through L2), block
- * size (0 = 1024; else 256, 512 or 1024), database entries per tile (0 = 4;
- * 4 or 8) and queries per chunk (0 = 256; 1 .. 1024; the queries of a chunk
- * keep their counters in one block's LDS). Results do not depend on it; the
+/* Launch shape of db_query_batch. All four 0 (the default): the handle's own
+ * choice for each call, the matrix-core kernel where it is the faster one,
+ * else the vector kernel with the values named below for 0. Any other value:
+ * the vector kernel with z-planes per LDS slab (0 = as many as fit; -1 = no
+ * LDS slabs: the kernel that reads the database through L2), block size (0 =
+ * 1024; else 256, 512 or 1024), database entries per tile (0 = 4; 4 or 8) and
+ * queries per chunk (0 = 256; 1 .. 1024; the queries of a chunk keep their
+ * counters in one block's LDS). Results do not depend on it; the
  * autotuner (paper_2205_04550_amd/autotune.py) picks it by timing. A change
  * takes effect at the next recording of the batch graph. */
 int db_tune_batch(db_t *db, int slab_planes, int block_threads, int tile_entries,

@@ -247,8 +247,9 @@ int nn_mse_bwd(int dtype, int64_t n, const void *A, const void *B, const void *g
  * w -= lr (m / (1-b1^t)) / (sqrt(v / (1-b2^t)) + eps); w_bf16 may be NULL. */
 int nn_adam_step(int64_t n, float *w, float *m, float *v, const float *g, uint16_t *w_bf16,
                  float lr, float b1, float b2, float eps, int t, void *stream);
-/* nn_adam_step of `count` tensors in one launch: host arrays [count] of sizes and of device
- * pointers (w_bf16[i] may be NULL); all are checked before anything is enqueued. */
+/* nn_adam_step of `count` tensors in one launch (one per 32 tensors or 2^33 elements): host arrays
+ * [count] of sizes and of device pointers (w_bf16[i] may be NULL); all are checked before anything
+ * is enqueued. */
 int nn_adam_step_multi(int count, const int64_t *n, float *const *w, float *const *m,
                        float *const *v, const float *const *g, uint16_t *const *w_bf16, float lr,
                        float b1, float b2, float eps, int t, void *stream);

@@ -429,8 +429,9 @@ class TumorDB:
 
     def tune_batch(self, slab_planes: int = 0, block_threads: int = 0, tile_entries: int = 0,
                    query_chunk: int = 0) -> None:
-        """Launch shape of query_batch (0 = defaults; slab_planes = -1 selects the kernel that
-        reads the database through L2); results are the same for any shape."""
+        """Launch shape of query_batch. All 0: the handle's own choice of kernel and shape; any other
+        value: the vector kernel (0 = its defaults; slab_planes = -1 selects the kernel that reads
+        the database through L2). Results are the same for any shape."""
         _check(LIB.db_tune_batch(self._h, slab_planes, block_threads, tile_entries, query_chunk))
 
     def set_rerank_bound(self, on: bool) -> None:

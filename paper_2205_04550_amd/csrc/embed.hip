@@ -516,7 +516,8 @@ constexpr int kZStage = 128;           // z-slices of per-slice row ranges a wav
 // in flight at once, where loads under conditions wait for one another. NXW = 0: any width, a word
 // at a time. 200 queries on 96 x 112 x 77 and 1,000 candidates, the first 16 of each / the rest:
 // 28 / 151 us, a word at a time 97 / 331. With rows of 128 voxels a full chip is bound by the
-// candidates' bytes (1,024 queries: 220 us either way).
+// candidates' bytes (1,024 queries: 220 us either way). Rows of one to three words on grids of more
+// than kZStage slices take NXW = 0: the 16-byte form was not built or measured there.
 template <int SPLIT, bool ALLZR, int NXW>
 __global__ void __launch_bounds__(SPLIT > 4 ? 64 * SPLIT : 256) rerank_score_kernel(const uint32_t *__restrict__ planes,
                                                            const uint32_t *__restrict__ popcnt,

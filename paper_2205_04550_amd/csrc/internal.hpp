@@ -62,8 +62,8 @@ struct db_t {
     int rerank_bound;   // 1: the rerank scores candidates in bound order and skips the rest
     uint64_t *mom;      // [capacity][4] FLAIR moments: sum x, sum y, sum z, count
     int32_t *tile_order;  // [capacity] entries sorted by row-box centre, in tiles by cost
-    int64_t tile_order_n; // entries the tile order covers (it is rebuilt when count differs)
-    int tile_order_tile;  // entries per tile it was built for
+    int64_t tile_order_n; // entries the tile order covers (it is replaced when count or
+    int tile_order_tile;  // the entries per tile it holds differ from a batch's)
     size_t storage_bytes;
     int cus;                 // compute units of the device the handle was built on
     int device;
